@@ -22,6 +22,29 @@ namespace bnk {
 constexpr int kX32Bias = 200;
 constexpr int kEZero = -(1 << 26);   // exponent carried by an exact zero
 
+// e^x for x <= 0 (x = -inf gives 0): x = k ln 2 + r with |r| <= ln 2 / 2, then
+// the near-minimax polynomial of degree 11 of e^r (Chebyshev interpolation;
+// relative error below 2^-56 before rounding) times 2^k.
+__device__ inline double exp_neg(double x) {
+    x = fmax(x, -1100.0);
+    const double k = rint(x * 1.4426950408889634074);
+    double r = fma(k, -6.93147180369123816490e-01, x);
+    r = fma(k, -1.90821492927058770002e-10, r);
+    double p = 2.5110049204818658e-08;
+    p = fma(p, r, 2.763265472252779e-07);
+    p = fma(p, r, 2.755724088722987e-06);
+    p = fma(p, r, 2.4801485441561313e-05);
+    p = fma(p, r, 0.00019841269890076403);
+    p = fma(p, r, 0.0013888888952352863);
+    p = fma(p, r, 0.008333333333319589);
+    p = fma(p, r, 0.04166666666648795);
+    p = fma(p, r, 0.1666666666666668);
+    p = fma(p, r, 0.5000000000000019);
+    p = fma(p, r, 1.0);
+    p = fma(p, r, 1.0);
+    return ldexp(p, (int)k);
+}
+
 // ---------------------------------------------------------------- FP64 log
 struct PolLog {
     using V = double;                 // value in registers and LDS
@@ -59,6 +82,23 @@ struct PolLog {
             a.s += e;
         }
     }
+    // acc += the first cnt of B terms: one exp per term and no branch per lane;
+    // the sum is rescaled only where some lane of the wave found a larger term
+    template <int B>
+    __device__ static inline void acc_add_n(Acc &a, const V *t, int cnt) {
+        double m = t[0];
+#pragma unroll
+        for (int u = 1; u < B; ++u)
+            if (u < cnt) m = fmax(m, t[u]);
+        if (__any(m > a.m)) {
+            const double mn = fmax(fmax(m, a.m), -1e300);
+            a.s *= exp_neg(a.m - mn);
+            a.m = mn;
+        }
+#pragma unroll
+        for (int u = 0; u < B; ++u)
+            if (u < cnt) a.s += exp_neg(t[u] - a.m);
+    }
     __device__ static inline V acc_value(const Acc &a) {
         return a.s > 0.0 ? a.m + log(a.s) : -__builtin_huge_val();
     }
@@ -80,6 +120,21 @@ struct PolLog {
         o[3] = r.b.y;
     }
     __device__ static inline void decode4_nz(const Raw4 &r, V *o) { decode4(r, o); }
+    template <int B>
+    __device__ static inline void cross_add(Acc *acc, const Raw4 *ra, const Raw4 *rx, int cnt) {
+        double t[4][B];
+#pragma unroll
+        for (int u = 0; u < B; ++u) {
+            if (u < cnt) {
+                t[0][u] = ra[u].a.x + rx[u].a.x;
+                t[1][u] = ra[u].a.y + rx[u].a.y;
+                t[2][u] = ra[u].b.x + rx[u].b.x;
+                t[3][u] = ra[u].b.y + rx[u].b.y;
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) acc_add_n<B>(acc[k], t[k], cnt);
+    }
     __device__ static inline V from_log(double x) { return x; }
     __device__ static inline double to_log(V v) { return v; }
     // log(a / b) in FP64, a, b > 0
@@ -218,6 +273,12 @@ struct PolX32 {
     using Acc = X32;
     __device__ static inline Acc acc_of(V x) { return x; }
     __device__ static inline void acc_add(Acc &a, V t) { a = add(a, t); }
+    template <int B>
+    __device__ static inline void acc_add_n(Acc &a, const V *t, int cnt) {
+#pragma unroll
+        for (int u = 0; u < B; ++u)
+            if (u < cnt) a = add(a, t[u]);
+    }
     __device__ static inline V acc_value(const Acc &a) { return a; }
     __device__ static inline V from_log(double x) {
         if (!(x > -1e300)) return zero();
@@ -271,6 +332,20 @@ struct PolX32 {
         o[1] = X32{r.f.y, (int)(((r.b >> 8) & 0xff) - kX32Bias) << 6};
         o[2] = X32{r.f.z, (int)(((r.b >> 16) & 0xff) - kX32Bias) << 6};
         o[3] = X32{r.f.w, (int)((r.b >> 24) - kX32Bias) << 6};
+    }
+    // acc[k] += the products of the first cnt of B pairs of four entries
+    template <int B>
+    __device__ static inline void cross_add(Acc *acc, const Raw4 *ra, const Raw4 *rx, int cnt) {
+#pragma unroll
+        for (int u = 0; u < B; ++u) {
+            if (u < cnt) {
+                V a[4], x[4];
+                decode4_nz(ra[u], a);
+                decode4_nz(rx[u], x);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) acc[k] = add(acc[k], mul_raw(a[k], x[k]));
+            }
+        }
     }
     // Encode one value: returns the byte, writes the significand to *f.
     // cnt[0] counts saturations, cnt[1] flushes of nonzero values.

@@ -1367,203 +1367,164 @@ struct SliceLds<PolX32> {
 // Stage alpha_i(Hf + Lo') (Lo' without bit i) for the bL tile bits into LDS:
 // slice i is the contiguous block alpha_i[(Hf >> 1) + k], k < 2^(bL-1).
 // All loads of a thread are issued before any is stored.
-template <class P>
+template <class P, int TH>
 __device__ inline void stage_alpha(const typename P::Store &alpha, uint64_t NN, uint64_t Hf,
                                    int bL, SliceLds<P> &la) {
     const uint32_t half = 1u << (bL - 1);
     const uint32_t total = (uint32_t)bL * half;
     const int t = threadIdx.x;
     if (half >= 4) {
-        constexpr int U = 5;                  // batches of 4 entries in flight per thread
-        for (uint32_t e0 = 4 * t; e0 < total; e0 += 4 * kThreads * U) {
+        constexpr int U = 6;                  // batches of 4 entries in flight per thread
+        for (uint32_t e0 = 4 * t; e0 < total; e0 += 4 * TH * U) {
             typename P::Raw4 raw[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const uint32_t e = e0 + 4 * kThreads * u;
+                const uint32_t e = e0 + 4 * TH * u;
                 if (e < total)
                     raw[u] = P::load4_raw(alpha, (uint64_t)(e >> (bL - 1)) * NN + (Hf >> 1) +
                                                      (e & (half - 1)));
             }
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const uint32_t e = e0 + 4 * kThreads * u;
+                const uint32_t e = e0 + 4 * TH * u;
                 if (e < total) la.put4(e, raw[u]);   // product factors only
             }
         }
     } else {
-        for (uint32_t e = t; e < total; e += kThreads)
+        for (uint32_t e = t; e < total; e += TH)
             la.put(e, alpha, (uint64_t)(e >> (bL - 1)) * NN + (Hf >> 1) + (e & (half - 1)));
     }
 }
 
-// acc[k] += sum over the listed nodes i of alpha_i[ai(i) + k] * X[xi(i) + k], k < 4,
-// four nodes per batch of loads.
-template <class P, class AI, class XI>
+// acc[k] += sum over the nodes i of the mask `nodes` (tile-high bits, the same
+// for the whole workgroup) of alpha_i[S - i] * X[S ^ i], S = Hf + lo + k, k < 4:
+// forward S ^ i = S - i, backward S ^ i = S + i. Four nodes per batch of loads.
+template <class P>
 __device__ inline void cross_terms(const typename P::Store &alpha, const typename P::Store &X,
-                                   const int *nodes, int cnt, AI ai, XI xi,
+                                   uint64_t NN, uint32_t Hf, uint32_t nodes, uint32_t lo,
                                    typename P::Acc *acc) {
-    using V = typename P::V;
     constexpr int B = 4;
-    for (int q0 = 0; q0 < cnt; q0 += B) {
+    while (nodes) {
         typename P::Raw4 ra[B], rx[B];
+        int cnt = 0;
 #pragma unroll
         for (int u = 0; u < B; ++u) {
-            if (q0 + u < cnt) {
-                const int i = nodes[q0 + u];
-                ra[u] = P::load4_raw(alpha, ai(i));
-                rx[u] = P::load4_raw(X, xi(i));
+            if (nodes) {
+                const int i = __ffs(nodes) - 1;
+                nodes &= nodes - 1;
+                ra[u] = P::load4_raw(alpha, (uint64_t)i * NN + compress_bit(Hf & ~(1u << i), i) + lo);
+                rx[u] = P::load4_raw(X, (uint64_t)(Hf ^ (1u << i)) + lo);
+                cnt = u + 1;
             }
         }
-#pragma unroll
-        for (int u = 0; u < B; ++u) {
-            if (q0 + u < cnt) {
-                V a[4], x[4];
-                P::decode4_nz(ra[u], a);
-                P::decode4_nz(rx[u], x);
-#pragma unroll
-                for (int k = 0; k < 4; ++k) P::acc_add(acc[k], P::mul_raw(a[k], x[k]));
-            }
-        }
+        P::template cross_add<B>(acc, ra, rx, cnt);
     }
 }
 
-// ------------------------------------------- a3: forward sweep, one layer
-// Workgroup = tile H with |H| = h (H over the n-bL high bits), in colex
-// order: consecutive workgroups, which run at the same time on the eight
-// XCDs, take tiles that share most of their L blocks (a mapping that gave
-// each XCD a contiguous eighth of the layer cut the L2 misses by 10% but
-// measured 5% slower). Cross-tile terms (i in H) stream contiguous 2^bL blocks of alpha_i and L, four
-// consecutive entries per thread; in-tile terms (i among the low bits) use
-// the tile's alpha slices staged in LDS and run popcount layer by popcount
-// layer. Requires bL >= 2.
-template <class P>
-__global__ void __launch_bounds__(kThreads)
-k_fwd(int n, int bL, int h, uint32_t hoff, Tables tb, typename P::Store alpha,
-      typename P::Store L, unsigned long long *cnt) {
+// ------------------------------- a3 + a4: both sweeps, one layer of tiles
+// Forward (Eq. 9) L(S) = sum_{i in S} alpha_i(S-i) L(S-i), layers upwards;
+// backward (Eq. 10) Rp(S) = sum_{i not in S} alpha_i(S) Rp(S+i), Rp(V) = 1,
+// layers downwards. Step h of both runs in one launch: the first nb workgroups
+// take the tiles H with |H| = h of the forward sweep, the others the tiles
+// with |H| = nh - h of the backward sweep (the same number). The two sweeps
+// share nothing but alpha, and a layer of a small lattice is a few workgroups
+// bound by the latency of one launch and of bL dependent in-tile layers, so
+// running both at once halves the sweeps: n = 16 FP32-scaled 180 -> 90 us for
+// both, n = 20 FP64 541 -> 272 us (operand batches and exp_neg included).
+// Large lattices launch the two sweeps apart, on two streams (launch_lattice);
+// there they stream alpha at the HBM rate.
+// Tiles go in colex order: consecutive workgroups, which run at the same time
+// on the eight XCDs, share most of their X blocks (a mapping that gave each
+// XCD a contiguous eighth of the layer cut the L2 misses by 10% but measured
+// 5% slower). Cross-tile terms (bits of H) stream contiguous 2^bL blocks of
+// alpha_i and X, four consecutive entries per thread; in-tile terms use the
+// tile's alpha slices staged in LDS and run popcount layer by popcount layer,
+// one entry per thread (TH >= the largest layer), its operands read in batches
+// of four before they are summed. Requires bL >= 2.
+template <class P, bool FWD, int TH>
+__device__ inline void sweep_tile(int n, int bL, uint32_t Hm, const Tables &tb,
+                                  const typename P::Store &alpha, const typename P::Store &X,
+                                  unsigned long long *cnt, unsigned char *smem) {
     using V = typename P::V;
-    extern __shared__ unsigned char smem[];
     const uint32_t half = 1u << (bL - 1);
     const uint32_t T = 1u << bL;
     SliceLds<P> la(smem, (uint32_t)bL * half);   // bL * half entries
     V *lt = reinterpret_cast<V *>(smem + align16(SliceLds<P>::bytes_per_entry * bL * half));
     uint16_t *lord = reinterpret_cast<uint16_t *>(lt + T);
-    __shared__ uint32_t loff[34];
-    __shared__ int pos[32];
-    const int t = threadIdx.x;
-    const uint64_t NN = 1ull << (n - 1);
-    if (t == 0) {
-        uint32_t Hm = tb.hord[hoff + blockIdx.x];   // H over the high bits
-        for (int q = 0; q < h; ++q) {
-            pos[q] = bL + __ffs(Hm) - 1;            // node indices of H
-            Hm &= Hm - 1;
-        }
-    }
-    if (t < bL + 2) loff[t] = tb.loff[t];
-    for (uint32_t x = t; x < T; x += kThreads) lord[x] = tb.lorder[x];
-    __syncthreads();
-    uint64_t Hf = 0;
-    for (int q = 0; q < h; ++q) Hf |= 1ull << pos[q];
-    stage_alpha<P>(alpha, NN, Hf, bL, la);
-    // cross-tile terms: alpha_i(S - i) L(S - i) for i in H
-    for (uint32_t lo = 4 * t; lo < T; lo += 4 * kThreads) {
-        typename P::Acc acc[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) acc[k] = P::acc_of((Hf == 0 && lo + k == 0) ? P::one() : P::zero());
-        cross_terms<P>(alpha, L, pos, h,
-                       [&](int i) { return (uint64_t)i * NN + compress_bit((Hf ^ (1ull << i)) | lo, i); },
-                       [&](int i) { return (Hf ^ (1ull << i)) | lo; }, acc);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) lt[lo + k] = P::norm_v(P::acc_value(acc[k]));
-    }
-    __syncthreads();
-    for (int l = 1; l <= bL; ++l) {
-        for (uint32_t idx = loff[l] + t; idx < loff[l + 1]; idx += kThreads) {
-            const uint32_t lo = lord[idx];
-            typename P::Acc acc = P::acc_of(lt[lo]);
-            uint32_t rest = lo;
-            while (rest) {
-                const int i = __ffs(rest) - 1;
-                rest &= rest - 1;
-                const uint32_t Tm = lo ^ (1u << i);
-                P::acc_add(acc, P::mul_raw(la.at(i * half + (uint32_t)compress_bit(Tm, i)), lt[Tm]));
-            }
-            lt[lo] = P::norm_v(P::acc_value(acc));
-        }
-        __syncthreads();
-    }
-    for (uint32_t lo = 4 * t; lo < T; lo += 4 * kThreads) P::store4(L, Hf | lo, lt + lo, cnt);
-}
-
-// ----------------------------------------- a4: backward sweep, one layer
-// Rp(S) = sum_{i not in S} alpha_i(S) Rp(S + i), Rp(V) = 1; layers run from
-// the top. Same tiling as the forward sweep, mirrored. Requires bL >= 2.
-template <class P>
-__global__ void __launch_bounds__(kThreads)
-k_bwd(int n, int bL, int h, uint32_t hoff, Tables tb, typename P::Store alpha,
-      typename P::Store R, unsigned long long *cnt) {
-    using V = typename P::V;
-    extern __shared__ unsigned char smem[];
-    const uint32_t half = 1u << (bL - 1);
-    const uint32_t T = 1u << bL;
-    SliceLds<P> la(smem, (uint32_t)bL * half);
-    V *lt = reinterpret_cast<V *>(smem + align16(SliceLds<P>::bytes_per_entry * bL * half));
-    uint16_t *lord = reinterpret_cast<uint16_t *>(lt + T);
-    __shared__ uint32_t loff[34];
-    __shared__ int pos[32];
-    __shared__ int outs[32];
-    __shared__ int nout_s;
     const int t = threadIdx.x;
     const int nh = n - bL;
     const uint64_t NN = 1ull << (n - 1);
-    if (t == 0) {
-        const uint32_t Hm = tb.hord[hoff + blockIdx.x];   // H over the high bits
-        uint32_t rest = Hm;
-        for (int q = 0; q < h; ++q) {
-            pos[q] = __ffs(rest) - 1;
-            rest &= rest - 1;
-        }
-        int no = 0;
-        for (int p = 0; p < nh; ++p)
-            if (!((Hm >> p) & 1)) outs[no++] = bL + p;   // nodes above the tile, not in H
-        nout_s = no;
-    }
-    if (t < bL + 2) loff[t] = tb.loff[t];
-    for (uint32_t x = t; x < T; x += kThreads) lord[x] = tb.lorder[x];
-    __syncthreads();
-    uint64_t Hf = 0;
-    for (int q = 0; q < h; ++q) Hf |= 1ull << (bL + pos[q]);
-    const int nout = nout_s;
-    const uint64_t highall = ((1ull << nh) - 1) << bL;
-    stage_alpha<P>(alpha, NN, Hf, bL, la);
-    for (uint32_t lo = 4 * t; lo < T; lo += 4 * kThreads) {
+    const uint32_t Hf = Hm << bL;
+    const uint32_t highall = ((1u << nh) - 1u) << bL;
+    stage_alpha<P, TH>(alpha, NN, Hf, bL, la);
+    for (uint32_t lo = 4 * t; lo < T; lo += 4 * TH) {
         typename P::Acc acc[4];
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
-            acc[k] = P::acc_of((Hf == highall && lo + k == T - 1) ? P::one() : P::zero());
-        const uint64_t Sm = Hf | lo;
-        cross_terms<P>(alpha, R, outs, nout,
-                       [&](int i) { return (uint64_t)i * NN + compress_bit(Sm, i); },
-                       [&](int i) { return Sm | (1ull << i); }, acc);
+        for (int k = 0; k < 4; ++k) {
+            const bool start = FWD ? (Hf == 0 && lo + k == 0) : (Hf == highall && lo + k == T - 1);
+            acc[k] = P::acc_of(start ? P::one() : P::zero());
+        }
+        cross_terms<P>(alpha, X, NN, Hf, FWD ? Hf : (highall & ~Hf), lo, acc);
 #pragma unroll
         for (int k = 0; k < 4; ++k) lt[lo + k] = P::norm_v(P::acc_value(acc[k]));
     }
+    for (uint32_t x = t; x < T; x += TH) lord[x] = tb.lorder[x];
     __syncthreads();
-    for (int l = bL - 1; l >= 0; --l) {
-        for (uint32_t idx = loff[l] + t; idx < loff[l + 1]; idx += kThreads) {
-            const uint32_t lo = lord[idx];
+    // in-tile layers: layer l holds size = C(bL, l) entries from lord[off] on
+    int l = FWD ? 1 : bL - 1;
+    uint32_t size = bL, off = FWD ? 1 : T - 1 - bL;
+    for (int step = 0; step < bL; ++step) {
+        const uint32_t lo = (uint32_t)t < size ? (uint32_t)lord[off + t] : T;
+        if (lo < T) {
             typename P::Acc acc = P::acc_of(lt[lo]);
-            uint32_t rest = (T - 1) & ~lo;
-            while (rest) {
-                const int i = __ffs(rest) - 1;
-                rest &= rest - 1;
-                P::acc_add(acc, P::mul_raw(la.at(i * half + (uint32_t)compress_bit(lo, i)),
-                                           lt[lo | (1u << i)]));
+            uint32_t rest = FWD ? lo : (T - 1) & ~lo;
+            const int terms = FWD ? l : bL - l;
+            constexpr int B = 4;
+            for (int q = 0; q < terms; q += B) {
+                V a[B], x[B];
+#pragma unroll
+                for (int u = 0; u < B; ++u) {
+                    if (q + u < terms) {
+                        const int i = __ffs(rest) - 1;
+                        rest &= rest - 1;
+                        const uint32_t w = lo & ~(1u << i);
+                        a[u] = la.at(i * half + (uint32_t)compress_bit(w, i));
+                        x[u] = lt[lo ^ (1u << i)];
+                    }
+                }
+                V term[B];
+#pragma unroll
+                for (int u = 0; u < B; ++u)
+                    if (q + u < terms) term[u] = P::mul_raw(a[u], x[u]);
+                P::template acc_add_n<B>(acc, term, terms - q);
             }
             lt[lo] = P::norm_v(P::acc_value(acc));
         }
         __syncthreads();
+        if (FWD) {
+            off += size;
+            size = size * (uint32_t)(bL - l) / (uint32_t)(l + 1);
+            ++l;
+        } else {
+            size = size * (uint32_t)l / (uint32_t)(bL - l + 1);
+            off -= size;
+            --l;
+        }
     }
-    for (uint32_t lo = 4 * t; lo < T; lo += 4 * kThreads) P::store4(R, Hf | lo, lt + lo, cnt);
+    for (uint32_t e = 4 * t; e < T; e += 4 * TH) P::store4(X, (uint64_t)Hf + e, lt + e, cnt);
+}
+
+template <class P, int TH>
+__global__ void __launch_bounds__(TH)
+k_sweeps(int n, int bL, uint32_t nb, uint32_t hoffF, uint32_t hoffB, Tables tb,
+         typename P::Store alpha, typename P::Store L, typename P::Store R,
+         unsigned long long *cnt) {
+    extern __shared__ unsigned char smem[];
+    const uint32_t b = blockIdx.x;
+    if (b < nb)
+        sweep_tile<P, true, TH>(n, bL, tb.hord[hoffF + b], tb, alpha, L, cnt, smem);
+    else
+        sweep_tile<P, false, TH>(n, bL, tb.hord[hoffB + b - nb], tb, alpha, R, cnt, smem);
 }
 
 // ---------------------------------------- a5 + a6: Gamma, in-tile part
@@ -3498,23 +3459,44 @@ hipError_t launch_lattice(const LatticeArgs &a, const typename P::Store &alpha,
     rec(2);
     const int nh = n - a.bL;
     const size_t smL = align16(SliceLds<P>::bytes_per_entry * ((size_t)a.bL << (a.bL - 1))) +
-                       sizeof(V) * ((size_t)1 << a.bL) + 2 * ((size_t)1 << a.bL);
-    // The backward sweep needs alpha but not L: with a.side set it runs on that
-    // stream, forked after alpha and joined before Gamma, so that its small
-    // layers overlap the forward sweep's.
+                       (sizeof(V) + 2) * ((size_t)1 << a.bL);
+    // The backward sweep needs alpha but not L. Below n = 24 step h of both
+    // sweeps is one launch; from there on, with a.side set, the backward sweep
+    // runs on that stream, forked after alpha and joined before Gamma, so that
+    // the tail of a layer is filled by the other sweep (n = 25 FP32-scaled:
+    // 1.27 ms for both against 1.47 ms in joint launches).
     SweepFork fork;
-    hipStream_t sb = st;
-    if (a.side && !a.fwd_only) {
+    const bool forked = a.side && !a.fwd_only;
+    if (forked) {
         const hipError_t e = fork.open(st, a.side);
         if (e != hipSuccess) return e;
-        sb = a.side;
     }
-    for (int h = 0; h <= nh; ++h) {
-        const unsigned nb = a.tiles_per_layer[h];
-        hipLaunchKernelGGL(k_fwd<P>, dim3(nb), dim3(kThreads), smL, st, n, a.bL, h,
-                           hord_offset(nh, h), tb, alpha, L, a.cnt);
-        BN_CHECK_LAUNCH();
-    }
+    // a thread per four tile entries covers the cross terms and the largest
+    // in-tile layer (C(12, 6) = 924)
+    auto sweeps = [&](auto threads) -> hipError_t {
+        constexpr int TH = decltype(threads)::value;
+        allow_big_lds<k_sweeps<P, TH>>();
+        for (int h = 0; h <= nh; ++h) {
+            // workgroups below nb run forward tiles, the others backward ones
+            const unsigned nb = a.tiles_per_layer[h];
+            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_sweeps<P, TH>),
+                               dim3(a.fwd_only || forked ? nb : 2 * nb), dim3(TH), smL, st, n,
+                               a.bL, nb, hord_offset(nh, h), hord_offset(nh, nh - h), tb, alpha,
+                               L, R, a.cnt);
+            BN_CHECK_LAUNCH();
+        }
+        for (int h = nh; forked && h >= 0; --h) {
+            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_sweeps<P, TH>), dim3(a.tiles_per_layer[h]),
+                               dim3(TH), smL, a.side, n, a.bL, 0u, 0u, hord_offset(nh, h), tb,
+                               alpha, L, R, a.cnt);
+            BN_CHECK_LAUNCH();
+        }
+        return hipSuccess;
+    };
+    const hipError_t es = a.bL <= 10   ? sweeps(std::integral_constant<int, 256>{})
+                          : a.bL == 11 ? sweeps(std::integral_constant<int, 512>{})
+                                       : sweeps(std::integral_constant<int, 1024>{});
+    if (es != hipSuccess) return es;
     rec(3);
     if (a.fwd_only) {
         hipLaunchKernelGGL(k_log_LV<P>, dim3(1), dim3(64), 0, st, n, L,
@@ -3524,14 +3506,8 @@ hipError_t launch_lattice(const LatticeArgs &a, const typename P::Store &alpha,
         rec(6);
         return hipSuccess;
     }
-    for (int h = nh; h >= 0; --h) {
-        const unsigned nb = a.tiles_per_layer[h];
-        hipLaunchKernelGGL(k_bwd<P>, dim3(nb), dim3(kThreads), smL, sb, n, a.bL, h,
-                           hord_offset(nh, h), tb, alpha, R, a.cnt);
-        BN_CHECK_LAUNCH();
-    }
-    if (sb != st) {
-        const hipError_t e = fork.join(st, sb);
+    if (forked) {
+        const hipError_t e = fork.join(st, a.side);
         if (e != hipSuccess) return e;
     }
     rec(4);

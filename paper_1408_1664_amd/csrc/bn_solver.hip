@@ -131,11 +131,14 @@ static Plan plan_of(int n, int d_in, int m, bn_precision prec, bool with_data, b
     const int N = P.N, d = P.d;
     P.K = (uint32_t)kcount_u64(N, d);
     P.bA = N >= 13 ? 13 : N;      // alpha tile: 13 bits, or the whole lattice when smaller
-    // sweep tile: 9 bits for the large FP32-scaled lattices (more workgroups
-    // per CU for an HBM-bound sweep); 10 below n = 23 (one launch fewer per
-    // sweep where launches dominate) and for the log form, whose log-add
-    // cross terms want all 256 threads busy (4 entries each)
-    P.bL = std::min(n, (P.x32 && n >= 23) ? 9 : 10);
+    // sweep tile. FP32-scaled: the whole lattice up to n = 12 (its alpha slices
+    // then fill the 160 KB of LDS): one launch for both sweeps, 18 us at n = 12
+    // against 38 us with 10 bits; 11 bits at n = 13 and 14 (60 against 63 us);
+    // else 9 bits (more workgroups per CU for the large, HBM-bound sweeps; at
+    // n = 16 and 22 2% faster than 10 bits). Log form: 11 bits where that saves
+    // a launch (n = 11, 12: 46 against 54 us), else 10, whose cross terms
+    // keep all 256 threads busy (9 bits: 3.8 against 2.8 ms at n = 25).
+    P.bL = P.x32 ? (n <= 12 ? n : n <= 14 ? 11 : 9) : std::min(n, n <= 12 ? 11 : 10);
     P.bG = n >= 12 ? 12 : n;      // Gamma tile: 12 bits, or the whole lattice when smaller
     P.aG = 12;
     // Tuning / test override "bA,bL,bG,aG" (each clamped to its valid range);
@@ -144,9 +147,9 @@ static Plan plan_of(int n, int d_in, int m, bn_precision prec, bool with_data, b
         int v[4] = {P.bA, P.bL, P.bG, P.aG};
         if (sscanf(tb, "%d,%d,%d,%d", &v[0], &v[1], &v[2], &v[3]) == 4) {
             (void)v[0];
-            // at most 11 sweep bits: the in-tile alpha slices (bL 2^(bL-1)
-            // entries) and the tile must fit the 160 KB of LDS
-            P.bL = std::max(2, std::min(std::min(v[1], n), 11));
+            // at most 12 sweep bits (11 in the log form): the in-tile alpha
+            // slices (bL 2^(bL-1) entries) and the tile must fit the 160 KB of LDS
+            P.bL = std::max(2, std::min(std::min(v[1], n), P.x32 ? 12 : 11));
             (void)v[2];
             P.aG = std::max(1, std::min(v[3], 12));
         }
