@@ -132,12 +132,13 @@ uint32_t hord_offset(int nh, int h);
 hipError_t launch_add_log(double *logp, const double *log_f, size_t count, hipStream_t st);
 // Local scores of every family (Eq. 3). bits non-null: all-binary data with
 // d <= 4, counted from bit planes built there; uniform_r > 0: every variable
-// has arity uniform_r and d <= 4, so the log-gamma values come from tables;
-// lgt: room for the tables, 10 (m + 1) doubles.
+// has arity uniform_r and d <= 4, so all families of a set of variables are
+// scored together, with log-gamma values from tables (`tables`) or evaluated
+// in place; lgt: room for the tables, 10 (m + 1) doubles.
 hipError_t launch_scores(int n, int m, const uint8_t *data, const uint8_t *arity, uint32_t K,
                          int kind, double ess, const uint32_t *famask, int max_bins,
-                         double *out, hipStream_t st, uint32_t *bits, int uniform_r,
-                         double *lgt);
+                         double *out, hipStream_t st, uint32_t *bits, int uniform_r, int d,
+                         bool tables, double *lgt);
 template <class P>
 hipError_t launch_lattice(const LatticeArgs &a, const typename P::Store &alpha,
                           const typename P::Store &L, const typename P::Store &R,

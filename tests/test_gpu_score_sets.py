@@ -1,0 +1,27 @@
+"""Local scores by sets of variables (one arity, d <= 4): every family of a set
+from one table of counts. Sizes at the edges: sample counts below one group of
+four and around a wave's step, in-degree bounds of n - 1 and above, tables from
+one variable to 2048 cells. Against the oracle, with the tolerance of the other
+score tests."""
+import numpy as np
+import pytest
+
+import paper_1408_1664_amd as bn
+from oracle import oracle as O
+from paper_1408_1664_amd import datagen
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kind", ["bdeu", "k2"])
+@pytest.mark.parametrize("n,r,d,m", [(2, 3, 1, 1), (4, 3, 7, 3), (6, 3, 4, 255), (9, 4, 4, 259),
+                                     (7, 6, 3, 64), (12, 3, 0, 130), (20, 3, 2, 1001)])
+def test_scores_by_sets(n, r, d, m, kind):
+    ds = datagen.random_dag_dataset(n, m, r, min(3, n - 1), 1.0, seed=50 + n + r)
+    print(f"score sets n={n} r={r} d={d} m={m} {kind}", flush=True)
+    got = bn.local_scores(ds.data, ds.arity, d, score=kind, ess=1.5)
+    ref = O.local_scores(ds.data, ds.arity, d, O.K2 if kind == "k2" else O.BDEU, 1.5)
+    masks = [x for k in range(min(d, n - 1) + 1) for x in range(1 << (n - 1))
+             if bin(x).count("1") == k]
+    for i in range(n):
+        at = [(x & ((1 << i) - 1)) | ((x >> i) << (i + 1)) for x in masks]
+        np.testing.assert_allclose(got[i], ref[i, at], rtol=1e-12, atol=1e-10)
