@@ -7,7 +7,7 @@
 
 namespace bnk {
 
-// Device tables generated by k_tables inside the workspace.
+// Device tables generated by k_setup inside the workspace.
 struct Tables {
     uint32_t *binom;     // 33 x 33 binomial coefficients
     uint16_t *lorder;    // 2^bL tile masks, by popcount then value
@@ -54,6 +54,7 @@ struct LatticeArgs {
     double *gauge_exp;   // 2n exponents (E_i, then F_k)
     double *post, *resid, *diag;
     unsigned long long *cnt;
+    uint32_t *done;      // workgroup counters of k_finish, zero before a solve
     const uint32_t *tiles_per_layer;  // host array: C(n - bL, h)
     GammaGeom gg;
     // Linear tiles (k_alpha_lin, k_gamma_tile_lin) with fallback lists
@@ -124,17 +125,40 @@ struct PhaseEvents {
     hipEvent_t ev[10];
 };
 
+// Parameters passed by value to the set-up kernel (host arrays are consumed at
+// launch, so no caller pointer is kept).
+struct ParamBlock {
+    uint8_t arity[32];
+    double log_rho[33];
+    double log_q[32];
+    int has_rho, has_q;
+};
+// What the set-up kernel prepares besides the tables: the parameters in the
+// workspace, zeroed counters (cnt: 2, done: 17 of a cache line each), and for the scores the bit planes of binary
+// data (bits, or null) and the log-gamma tables of arity table_r (0: none).
+struct SetupArgs {
+    uint8_t *arity;
+    double *log_rho, *log_q;
+    unsigned long long *cnt;
+    uint32_t *done;
+    const uint8_t *data;
+    int m, kind, table_r;
+    double ess;
+    uint32_t *bits;
+    double *lgt;
+};
 hipError_t launch_setup(const Tables &tb, int bL, int W, int bG, int bA, int d, uint32_t N,
-                        uint32_t K, hipStream_t st);
+                        uint32_t K, const ParamBlock &pb, const SetupArgs &sa, hipStream_t st);
 // sum_{k < h} C(nh, k): the first entry of layer h in Tables::hord
 uint32_t hord_offset(int nh, int h);
 // logp[x] += log_f[x], x < count (scores times a modular feature's factors)
 hipError_t launch_add_log(double *logp, const double *log_f, size_t count, hipStream_t st);
 // Local scores of every family (Eq. 3). bits non-null: all-binary data with
-// d <= 4, counted from bit planes built there; uniform_r > 0: every variable
+// d <= 4, counted from the bit planes there; uniform_r > 0: every variable
 // has arity uniform_r and d <= 4, so all families of a set of variables are
 // scored together, with log-gamma values from tables (`tables`) or evaluated
-// in place; lgt: room for the tables, 10 (m + 1) doubles.
+// in place; lgt: the tables, 10 (m + 1) doubles.
+// Planes and tables are those of launch_setup.
 hipError_t launch_scores(int n, int m, const uint8_t *data, const uint8_t *arity, uint32_t K,
                          int kind, double ess, const uint32_t *famask, int max_bins,
                          double *out, hipStream_t st, uint32_t *bits, int uniform_r, int d,

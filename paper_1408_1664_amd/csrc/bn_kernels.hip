@@ -116,12 +116,20 @@ __device__ inline void ranked_chunk(const uint32_t *bn, int w, int d, uint32_t x
 //   the alpha tile's ranked seed masks over bA bits (range A);
 //   the ranked high-bit items of an alpha tile over n - 1 - bA bits (I);
 //   the compressed parent-set masks in rank order, K(n - 1, d) (F);
-//   the sweep tiles' high parts over n - bL bits by popcount, then colex (H).
+//   the sweep tiles' high parts over n - bL bits by popcount, then colex (H);
+//   the problem's parameters and zeroed counters (P, one workgroup), the bit
+//   planes of binary data (B) and the log-gamma tables of the scores (G).
+// A launch of a few workgroups takes 4 to 5 us whatever it does, so what a
+// solve prepares before its scores is one launch (n = 10: four before, 24 us).
 struct TableGrid {
-    uint32_t s, a, i, f, h;   // cumulative ends of the ranges
+    uint32_t s, a, i, f, h, p, b, g;   // cumulative ends of the ranges
 };
-__global__ void k_tables(Tables tb, LaneOrder oc, TableGrid g, int bL, int W, int bG, int bA,
-                         int d, int N, uint32_t K) {
+__device__ void pack2(uint32_t id, int n, int m, int W, const uint8_t *__restrict__ data,
+                      uint32_t *__restrict__ bits);
+__device__ void lgamma_table(uint32_t x0, uint32_t step, int m, int r, int kind, double ess,
+                             double *__restrict__ lgt);
+__global__ void k_setup(Tables tb, LaneOrder oc, TableGrid g, int bL, int W, int bG, int bA,
+                        int d, int N, uint32_t K, ParamBlock pb, SetupArgs sa) {
     const uint32_t *bn = kBinomTab.v;
     const uint32_t blk = blockIdx.x;
     const int t = threadIdx.x;
@@ -183,8 +191,27 @@ __global__ void k_tables(Tables tb, LaneOrder oc, TableGrid g, int bL, int W, in
         uint32_t msk = 0;
         for (int q = 0; q < k; ++q) msk |= 1u << pos[q];
         tb.famask[r] = msk;
-    } else {
+    } else if (blk < g.h) {
         ranked_chunk(bn, N + 1 - bL, 64, (blk - g.f) * kThreads + t, tb.hord);
+    } else if (blk < g.p) {
+        const int n = N + 1;
+        if (t < n) {
+            sa.arity[t] = pb.arity[t];
+            sa.log_q[t] = pb.has_q ? pb.log_q[t] : 0.0;
+        }
+        if (t <= d) {
+            // default rho(k) = 1 / C(n-1, k)
+            sa.log_rho[t] = pb.has_rho ? pb.log_rho[t]
+                                       : -(lgamma((double)n) - lgamma((double)t + 1.0) -
+                                           lgamma((double)(n - t)));
+        }
+        if (t < 2) sa.cnt[t] = 0ull;
+        if (t < 17) sa.done[32 * t] = 0u;
+    } else if (blk < g.b) {
+        pack2((blk - g.p) * kThreads + t, N + 1, sa.m, (sa.m + 31) / 32, sa.data, sa.bits);
+    } else {
+        lgamma_table((blk - g.b) * kThreads + t, (g.g - g.b) * kThreads, sa.m, sa.table_r,
+                     sa.kind, sa.ess, sa.lgt);
     }
 }
 
@@ -360,6 +387,17 @@ k_scores_w(int n, int m, const uint8_t *__restrict__ data, const uint8_t *__rest
 // for q(k) with a per-layer exponent F_k.
 // Scores of one row per workgroup row (blockIdx.x = node), kPrepChunk
 // entries per workgroup (blockIdx.y).
+//
+// Per-node scale for the linear alpha tiles. Every alpha_i(S) / q(|S|) is a
+// sum of B_i(G) over G subset S that includes B_i(empty), and none exceeds
+// K(n-1, d) max_G B_i(G). Node i therefore gets one power of two (a log
+// offset for the log-space system) that puts B_i(empty) near 2^-1000, and
+// the node is held in plain doubles when max_G B_i(G) / B_i(empty) is below
+// 2^1900: no partial sum can then leave the double range (K(n-1, d) <
+// 2^31). betal_i(r) = B_i(r) under that scale. Nodes that do not qualify
+// (linok = 0) are computed in the number system proper.
+// emax (nullable) receives floor(log2 max_G B_i(G)) + 1 per node (the bound
+// the fused sweeps test their blocks against).
 constexpr uint32_t kPrepChunk = 2048;
 template <class P>
 __global__ void k_prep(int n, int d, uint32_t K, const uint32_t *binom,
@@ -367,7 +405,9 @@ __global__ void k_prep(int n, int d, uint32_t K, const uint32_t *binom,
                        const double *__restrict__ log_q, int gauge,
                        typename P::V *__restrict__ beta, typename P::V *__restrict__ qt,
                        double *__restrict__ gauge_exp, uint32_t *fbA, uint32_t *fbG,
-                       uint32_t *rtG) {
+                       uint32_t *rtG, double *__restrict__ betal,
+                       typename P::Anchor *__restrict__ anc, int *__restrict__ linok,
+                       int *__restrict__ emax) {
     __shared__ double red[kThreads];
     const int i = blockIdx.x;
     const uint32_t chunk = blockIdx.y;      // entries [chunk * kPrepChunk, ...) of row i
@@ -393,10 +433,26 @@ __global__ void k_prep(int n, int d, uint32_t K, const uint32_t *binom,
         mx = fmax(mx, log_rho[size_of(r)] + logp[(size_t)i * K + r]);
     mx = block_reduce(mx, red, [](double a, double b) { return fmax(a, b); });
     const double E = (gauge && mx > -1e300) ? rint(mx * 1.4426950408889634074) : 0.0;
+    // the row's linear scale (nullable outputs): anchored at B_i(empty), held in
+    // doubles when the largest score lies less than 2^1900 above it
+    auto gauged = [&](double lb) { return P::from_log(lb - E * 0.69314718055994530942); };
+    typename P::Anchor T{};
+    bool lin = false;
+    if (betal) {
+        const typename P::V b0 = gauged(log_rho[0] + logp[(size_t)i * K]);
+        const double l2 = P::log2_of(gauged(mx));
+        lin = P::anchor_of(b0, &T) && l2 - P::log2_of(b0) <= 1900.0;
+        if (chunk == 0 && t == 0) {
+            anc[i] = T;
+            linok[i] = lin ? 1 : 0;
+            if (emax) emax[i] = l2 > -1e300 ? (int)l2 + 1 : -(1 << 26);
+        }
+    }
     const uint32_t r1 = min(K, (chunk + 1) * kPrepChunk);
     for (uint32_t r = chunk * kPrepChunk + t; r < r1; r += kThreads) {
-        const double lb = log_rho[size_of(r)] + logp[(size_t)i * K + r];
-        beta[(size_t)i * K + r] = P::from_log(lb - E * 0.69314718055994530942);
+        const typename P::V b = gauged(log_rho[size_of(r)] + logp[(size_t)i * K + r]);
+        beta[(size_t)i * K + r] = b;
+        if (lin) betal[(size_t)i * K + r] = P::to_lin(b, T);
     }
     if (chunk == 0 && t == 0) gauge_exp[i] = E;
     if (i == 0 && chunk == 0) {
@@ -654,45 +710,6 @@ __device__ inline void lin_zeta_up(double *v, int q) {
 #pragma unroll
     for (int r = 0; r < NR; ++r)
         if ((r >> q) & 1) v[r] += v[r ^ (1 << q)];
-}
-
-// Per-node scale for the linear alpha tiles. Every alpha_i(S) / q(|S|) is a
-// sum of B_i(G) over G subset S that includes B_i(empty), and none exceeds
-// K(n-1, d) max_G B_i(G). Node i therefore gets one power of two (a log
-// offset for the log-space system) that puts B_i(empty) near 2^-1000, and
-// the node is held in plain doubles when max_G B_i(G) / B_i(empty) is below
-// 2^1900: no partial sum can then leave the double range (K(n-1, d) <
-// 2^31). betal_i(r) = B_i(r) under that scale. Nodes that do not qualify
-// (linok = 0) are computed in the number system proper.
-// emax (nullable) receives floor(log2 max_G B_i(G)) + 1 per node (the bound
-// the fused sweeps test their blocks against).
-template <class P>
-__global__ void k_prep_lin(int n, uint32_t K, const typename P::V *__restrict__ beta,
-                           double *__restrict__ betal, typename P::Anchor *__restrict__ anc,
-                           int *__restrict__ linok, int *__restrict__ emax) {
-    using A = typename P::Anchor;
-    __shared__ double red[kThreads];
-    __shared__ int sok;
-    __shared__ A sT;
-    const int i = blockIdx.x;
-    const int t = threadIdx.x;
-    const typename P::V *bi = beta + (size_t)i * K;
-    double mx = -1e300;
-    for (uint32_t r = t; r < K; r += kThreads) mx = fmax(mx, P::log2_of(bi[r]));
-    mx = block_reduce(mx, red, [](double a, double b) { return fmax(a, b); });
-    if (t == 0) {
-        A T{};
-        const bool ok = P::anchor_of(bi[0], &T) && mx - P::log2_of(bi[0]) <= 1900.0;
-        sok = ok ? 1 : 0;
-        sT = T;
-        anc[i] = T;
-        linok[i] = sok;
-        if (emax) emax[i] = mx > -1e300 ? (int)mx + 1 : -(1 << 26);
-    }
-    __syncthreads();
-    if (!sok) return;
-    const A T = sT;
-    for (uint32_t r = t; r < K; r += kThreads) betal[(size_t)i * K + r] = P::to_lin(bi[r], T);
 }
 
 // Binomial coefficient for small arguments; folds to a constant when its
@@ -2056,13 +2073,16 @@ k_gamma_tile_lin(int n, int d, int force_fb, int vsplit, GammaGeom gg, Tables tb
 // needed one is at least 2^-1000, since the products that fell below 2^-1074
 // (at most 4096) then change none by more than 2^-62 of itself. Outputs below
 // that get a third chance under the first scale (below); an endpoint with an
-// output valid under neither goes to the fallback list of k_gamma_tile_fb.
+// output valid under neither is recomputed in the number system proper
+// (gamma_tile), here as well: it is rare, and a launch of its own cost every
+// solve 4.6 us.
 // Same layouts as k_gamma_tile_lin, layout C for every thread.
 template <class P>
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 k_gamma_tile_retry(int n, int d, GammaGeom gg, Tables tb, typename P::Store L,
                    typename P::Store R, const typename P::V *__restrict__ qt,
-                   typename P::V *__restrict__ Y1, const uint32_t *list, uint32_t *fb) {
+                   typename P::V *__restrict__ Y1, typename P::V *__restrict__ part,
+                   const uint32_t *list, uint32_t *fb) {
     using V = typename P::V;
     using R16 = typename P::Raw16;
     using A = typename P::Anchor;
@@ -2170,7 +2190,7 @@ k_gamma_tile_retry(int n, int d, GammaGeom gg, Tables tb, typename P::Store L,
         // the two scales lie less than 2024 binary orders apart). Each needed
         // output is taken from the pass where it is at least 2^-1000 and
         // finite; an endpoint with an output valid in neither goes to
-        // k_gamma_tile_fb. Outputs of the first pass wait in registers
+        // gamma_tile. Outputs of the first pass wait in registers
         // (at most 4 per thread, K(12, d) <= 1024).
         constexpr int kMaxOut = 4;
         double keep1[kMaxOut];
@@ -2215,7 +2235,11 @@ k_gamma_tile_retry(int n, int d, GammaGeom gg, Tables tb, typename P::Store L,
                 ok = __syncthreads_or(fail ? 1 : 0) == 0;
             }
             if (!ok) {
-                if (t == 0) fb_push(fb, (H << 6) | (uint32_t)(v + 1));   // this endpoint only
+                // this endpoint in the number system proper (same LDS layout: the
+                // tables in LDS are written again with the same values)
+                if (t == 0) atomicAdd(fb, 1u);
+                __syncthreads();
+                gamma_tile<P>(n, d, gg, tb, L, R, qt, Y1, part, H, v);
                 continue;
             }
             two = true;
@@ -2890,22 +2914,53 @@ k_gamma_highB(int n, int d, int a, uint32_t KA, uint32_t K, GammaGeom gg, Tables
 // against L(V) (the residual) and, when asked for, the parent-set
 // posteriors w_v(G) / L(V); j = u + 1: P(u->v) = sum_{G containing u}
 // w_v(G) / L(V), the last division in FP64.
+// An 8-byte result that another workgroup of the same launch reads: stored to,
+// and loaded from, the device's point of coherence (each XCD has an L2 of its
+// own), so that no workgroup has to write back its L2 for it.
+template <class T>
+__device__ inline void store_shared_result(T *p, T x) {
+    static_assert(sizeof(T) == 8, "8-byte values");
+    uint64_t w;
+    __builtin_memcpy(&w, &x, 8);
+    __hip_atomic_store(reinterpret_cast<uint64_t *>(p), w, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+}
+template <class T>
+__device__ inline T load_shared_result(const T *p) {
+    static_assert(sizeof(T) == 8, "8-byte values");
+    const uint64_t w = __hip_atomic_load(reinterpret_cast<const uint64_t *>(p), __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_AGENT);
+    T x;
+    __builtin_memcpy(&x, &w, 8);
+    return x;
+}
+// Counts the calling thread, whose shared results are then at the point of
+// coherence, and returns true for the last of `total`: first in one of 16
+// counters (a cache line each, `done` + 32 * (1 + group)), the last of a group
+// in done[0]. One counter for all took 10 us more at n = 16 (544 workgroups).
+__device__ inline bool count_done(uint32_t *done, uint32_t id, uint32_t total) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    const uint32_t g = id & 15u, size = (total - g + 15u) / 16u;
+    auto add = [](uint32_t *p) {
+        return __hip_atomic_fetch_add(p, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    if (add(done + 32 * (1 + g)) != size - 1) return false;
+    return add(done) == min(total, 16u) - 1;
+}
+
 template <class P>
-__global__ void __launch_bounds__(kThreads)
-k_edges(int n, uint32_t K, const uint32_t *__restrict__ famask,
-        const typename P::V *__restrict__ beta, const typename P::V *__restrict__ gam,
-        typename P::Store L, double *__restrict__ post, double *__restrict__ resid,
-        double *__restrict__ ps) {
+__device__ inline void edge_sum(int v, int u, int n, uint32_t K,
+                                const uint32_t *__restrict__ famask,
+                                const typename P::V *__restrict__ beta,
+                                const typename P::V *__restrict__ gam, typename P::V LV,
+                                double *post, double *resid, double *__restrict__ ps,
+                                typename P::V *red) {
     using V = typename P::V;
-    __shared__ V red[kThreads];
-    const int v = blockIdx.x;
-    const int u = (int)blockIdx.y - 1;
     const int t = threadIdx.x;
     if (u == v) {
         if (t == 0) post[(size_t)u * n + v] = 0.0;
         return;
     }
-    const V LV = P::load(L, (1ull << n) - 1);
     auto add = [](V a, V b) { return P::add(a, b); };
     // parent-set posteriors P(G_v = G | D) = w_v(G) / L(V), when asked for
     if (ps && u < 0) {
@@ -2924,23 +2979,22 @@ k_edges(int n, uint32_t K, const uint32_t *__restrict__ famask,
     const V tot = block_reduce(P::acc_value(acc), red, add);
     if (t == 0) {
         const double lr = P::log_ratio(tot, LV);
-        if (u < 0) resid[v] = fabs(lr);
+        if (u < 0) store_shared_result(resid + v, fabs(lr));
         else post[(size_t)u * n + v] = (lr > -1e300) ? exp(lr) : 0.0;
     }
 }
 
 // -------------------------------------------------------- invariants
-// Per tile H (blockIdx.x) and in-tile layer l (blockIdx.y): sum of
-// L(S) Rp(S); then per layer k of the whole lattice. Every layer sum must
-// equal L(V).
+// Every layer sum over |S| = k of L(S) Rp(S) must equal L(V). inv_tile: the
+// sum over in-tile layer l of tile H, to part; inv_layer: the layer-k sum over
+// the c-th of `chunks` ranges of tiles, to layer[k * chunks + c].
+constexpr int kInvChunks = 32;   // at most, about 256 tiles each
 template <class P>
-__global__ void __launch_bounds__(kThreads)
-k_inv1(int n, int bL, Tables tb, typename P::Store L, typename P::Store R,
-       typename P::V *__restrict__ part) {
+__device__ inline void inv_tile(uint32_t H, int l, int bL, const Tables &tb,
+                                const typename P::Store &L, const typename P::Store &R,
+                                typename P::V *part, typename P::V *red) {
     using V = typename P::V;
-    __shared__ V red[kThreads];
-    const uint64_t Hf = (uint64_t)blockIdx.x << bL;
-    const int l = blockIdx.y;
+    const uint64_t Hf = (uint64_t)H << bL;
     const int t = threadIdx.x;
     auto add = [](V a, V b) { return P::add(a, b); };
     V acc = P::zero();
@@ -2949,22 +3003,15 @@ k_inv1(int n, int bL, Tables tb, typename P::Store L, typename P::Store R,
         acc = P::add(acc, P::mul(P::load(L, S), P::load(R, S)));
     }
     V s = block_reduce(acc, red, add);
-    if (t == 0) part[(size_t)blockIdx.x * (bL + 1) + l] = s;
+    if (t == 0) store_shared_result(part + (size_t)H * (bL + 1) + l, s);
 }
-
-// Workgroup (k, c): the layer-k sum over the c-th of kInvChunks ranges of
-// tiles, to layer[k * kInvChunks + c]; k_finalize adds the ranges in order.
-constexpr int kInvChunks = 32;
 template <class P>
-__global__ void __launch_bounds__(kThreads)
-k_inv2(int n, int bL, const typename P::V *__restrict__ part, typename P::V *__restrict__ layer) {
+__device__ inline void inv_layer(int k, int c, int chunks, int n, int bL, const typename P::V *part,
+                                 typename P::V *layer, typename P::V *red) {
     using V = typename P::V;
-    __shared__ V red[kThreads];
-    const int k = blockIdx.x;
-    const int c = blockIdx.y;
     const int t = threadIdx.x;
     const uint32_t ntile = 1u << (n - bL);
-    const uint32_t per = (ntile + kInvChunks - 1) / kInvChunks;
+    const uint32_t per = (ntile + chunks - 1) / chunks;
     const uint32_t h0 = c * per, h1 = min(ntile, h0 + per);
     auto add = [](V a, V b) { return P::add(a, b); };
     V acc = P::zero();
@@ -2974,36 +3021,72 @@ k_inv2(int n, int bL, const typename P::V *__restrict__ part, typename P::V *__r
         acc = P::add(acc, part[(size_t)H * (bL + 1) + l]);
     }
     V s = block_reduce(acc, red, add);
-    if (t == 0) layer[k * kInvChunks + c] = s;
+    if (t == 0) store_shared_result(layer + k * chunks + c, s);
 }
 
+// Edge sums, invariants and diagnostics in one launch: workgroups below
+// n (n + 1) take an edge sum (v, u) each, u = -1 the sum over all parent sets;
+// the others an invariant sum, per chunk of tiles (tiled > 0 chunks: the Gamma
+// tile kernel left the tiles' sums in part, bI = 12) or per tile and in-tile
+// layer (tiled = 0, bI = the sweep tile, at most 2^9 small tiles). Each counts
+// itself in `done` (zero at the start) and the last one writes the
+// diagnostics. As three or four launches of 4 to 6 us each this was 17 us of
+// an n = 10 solve.
 // diag: [0] log L(V), [1] max residual, [2] saturated, [3] flushed,
-//       [4] |log Rp(0) - log L(V)|, [5] max layer residual, [6] max edge-sum residual
+//       [4] |log Rp(0) - log L(V)|, [5] max layer residual, [6] max edge-sum
+//       residual, [7] fallback tiles
 template <class P>
-__global__ void k_finalize(int n, typename P::Store L, typename P::Store R,
-                           const typename P::V *__restrict__ layer,
-                           const double *__restrict__ resid, const double *__restrict__ gauge_exp,
-                           const unsigned long long *__restrict__ cnt,
-                           const uint32_t *__restrict__ fbA, const uint32_t *__restrict__ fbG,
-                           double *__restrict__ diag) {
+__global__ void __launch_bounds__(kThreads)
+k_finish(int n, uint32_t K, int tiled, int bI, Tables tb, const uint32_t *__restrict__ famask,
+         const typename P::V *__restrict__ beta, const typename P::V *__restrict__ gam,
+         typename P::Store L, typename P::Store R, typename P::V *part, typename P::V *layer,
+         double *post, double *resid, double *__restrict__ ps,
+         const double *__restrict__ gauge_exp, const unsigned long long *__restrict__ cnt,
+         const uint32_t *__restrict__ fbA, const uint32_t *__restrict__ fbG, uint32_t *done,
+         double *__restrict__ diag) {
     using V = typename P::V;
+    __shared__ V red[kThreads];
+    __shared__ uint32_t last;
     const int t = threadIdx.x;
+    const uint32_t b = blockIdx.x, ne = (uint32_t)(n * (n + 1));
     const V LV = P::load(L, (1ull << n) - 1);
-    // lane k sums layer k's chunks in order; the largest deviation over the
-    // wave (one wave of 64 lanes, n + 1 <= 32 layers)
+    if (b < ne)
+        edge_sum<P>((int)(b % n), (int)(b / n) - 1, n, K, famask, beta, gam, LV, post, resid, ps,
+                    red);
+    else if (tiled)
+        inv_layer<P>((int)((b - ne) / tiled), (int)((b - ne) % tiled), tiled, n, bI, part, layer,
+                     red);
+    else
+        inv_tile<P>((b - ne) / (bI + 1), (int)((b - ne) % (bI + 1)), bI, tb, L, R, part, red);
+    if (t == 0) last = count_done(done, b, gridDim.x) ? 1u : 0u;
+    __syncthreads();
+    if (!last || t >= 64) return;
+    // lane k sums layer k's parts in order; the largest deviation over the
+    // wave (n + 1 <= 32 layers)
     double rl = 0.0;
     if (t <= n) {
-        V lk = layer[t * kInvChunks];
-        for (int c = 1; c < kInvChunks; ++c) lk = P::add(lk, layer[t * kInvChunks + c]);
+        V lk = P::zero();
+        if (tiled) {
+            for (int c = 0; c < tiled; ++c)
+                lk = P::add(lk, load_shared_result(layer + t * tiled + c));
+        } else {
+            for (uint32_t H = 0; H < (1u << (n - bI)); ++H) {
+                const int l = t - __popc(H);
+                if (l >= 0 && l <= bI)
+                    lk = P::add(lk, load_shared_result(part + (size_t)H * (bI + 1) + l));
+            }
+        }
         rl = fabs(P::log_ratio(lk, LV));
     }
-    for (int o = 32; o > 0; o >>= 1) rl = fmax(rl, __shfl_xor(rl, o));
+    double re = t < n ? load_shared_result(resid + t) : 0.0;
+    double g = t < 2 * n ? gauge_exp[t] : 0.0;
+    for (int o = 32; o > 0; o >>= 1) {
+        rl = fmax(rl, __shfl_xor(rl, o));
+        re = fmax(re, __shfl_xor(re, o));
+        g += __shfl_xor(g, o);                   // integers: exact in any order
+    }
     if (t != 0) return;
-    double g = 0.0;
-    for (int k = 0; k < 2 * n; ++k) g += gauge_exp[k];
     const double rLR = fabs(P::log_ratio(P::load(R, 0), LV));
-    double re = 0.0;
-    for (int v = 0; v < n; ++v) re = fmax(re, resid[v]);
     diag[0] = P::to_log(LV) + g * 0.69314718055994530942;
     diag[1] = fmax(rLR, fmax(rl, re));
     diag[2] = (double)cnt[0];
@@ -3049,21 +3132,18 @@ hipError_t launch_add_log(double *logp, const double *log_f, size_t count, hipSt
 // All-binary data as two bit planes per variable: plane 1 marks the samples
 // with value 1, plane 0 those with value 0 (a value out of range is in
 // neither, and so ignored, as in k_scores). W 32-bit words per plane.
-__global__ void k_pack2(int n, int m, int W, const uint8_t *__restrict__ data,
-                        uint32_t *__restrict__ bits) {
-    const uint32_t id = blockIdx.x * kThreads + threadIdx.x;
-    if (id >= (uint32_t)(n * W)) return;
-    const int j = id / W, w = id % W;
-    uint32_t one = 0, zero = 0;
-    for (int b = 0; b < 32; ++b) {
-        const int s = w * 32 + b;
-        if (s >= m) break;
-        const uint8_t x = data[(size_t)j * m + s];
-        one |= (uint32_t)(x == 1) << b;
-        zero |= (uint32_t)(x == 0) << b;
+__device__ void pack2(uint32_t id, int n, int m, int W, const uint8_t *__restrict__ data,
+                      uint32_t *__restrict__ bits) {
+    const uint32_t W2 = (uint32_t)(W + 1) / 2, wave = id >> 6, lane = id & 63;
+    const uint32_t j = wave / W2, w = 2 * (wave - j * W2);
+    if (j >= (uint32_t)n) return;
+    const uint32_t s = w * 32 + lane;
+    const int x = s < (uint32_t)m ? data[(size_t)j * m + s] : 255;
+    const uint64_t zero = __ballot(x == 0), one = __ballot(x == 1);
+    if (lane < 2 && w + lane < (uint32_t)W) {
+        bits[((size_t)j * 2 + 0) * W + w + lane] = (uint32_t)(zero >> (32 * lane));
+        bits[((size_t)j * 2 + 1) * W + w + lane] = (uint32_t)(one >> (32 * lane));
     }
-    bits[((size_t)j * 2 + 1) * W + w] = one;
-    bits[((size_t)j * 2 + 0) * W + w] = zero;
 }
 
 // One step of count_cells2's butterfly, at lane bit B.
@@ -3131,9 +3211,10 @@ __device__ inline void count_cells2(const uint32_t *__restrict__ bits, int W, in
 // lgt[(2k) * (m+1) + c] = lgamma(a_j + c) and lgt[(2k+1) * (m+1) + c] =
 // lgamma(a_jk + c), c = 0..m, with the BDeu (a_j = ess / q, a_jk =
 // ess / (q r)) or K2 (a_j = r, a_jk = 1) hyperparameters.
-__global__ void k_lgamma_table(int m, int r, int kind, double ess, double *__restrict__ lgt) {
+__device__ void lgamma_table(uint32_t x0, uint32_t step, int m, int r, int kind, double ess,
+                             double *__restrict__ lgt) {
     const int m1 = m + 1;
-    for (int x = blockIdx.x * kThreads + threadIdx.x; x < 10 * m1; x += gridDim.x * kThreads) {
+    for (int x = (int)x0; x < 10 * m1; x += (int)step) {
         const int row = x / m1, c = x - row * m1, k = row >> 1;
         int qi = 1;
         for (int j = 0; j < k; ++j) qi *= r;
@@ -3166,7 +3247,7 @@ __device__ inline uint32_t binom5(uint32_t p, int t) {
 // and load) bounds it: at n = 20, r = 3, m = 1000, d = 4 the 15,504 + 6,195
 // sets take about 55 us where a wave per family (100,720 of them) took 306 us.
 // Sets in order of size, then colex. Values >= r are counted nowhere. TAB: the
-// log-gamma values come from k_lgamma_table, else each is evaluated in place
+// log-gamma values come from lgamma_table, else each is evaluated in place
 // (the same values).
 template <bool TAB>
 __global__ void __launch_bounds__(kThreads)
@@ -3279,7 +3360,7 @@ k_scores_sets(int n, int m, int d, const uint8_t *__restrict__ data, int r, uint
 // (all variables binary: q = 2^k configurations, r = 2 values); lane L < q
 // takes configuration L (the counts count_cells2 left it), partial sums met
 // by a fixed butterfly. The log-gamma values come from the tables of
-// k_lgamma_table.
+// lgamma_table.
 template <int KP>
 __device__ inline double family_score2(const uint32_t *cnt, int lane, const double *lgt,
                                        int m1) {
@@ -3302,7 +3383,7 @@ __device__ inline double family_score2(const uint32_t *cnt, int lane, const doub
 }
 
 // Local scores of all-binary data with d <= 4: 16 lanes per family, 16
-// families per workgroup, counts from the bit planes of k_pack2.
+// families per workgroup, counts from the bit planes of pack2.
 __global__ void __launch_bounds__(kThreads)
 k_scores2(int n, int W, int m, uint32_t K, const uint32_t *__restrict__ famask,
           const uint32_t *__restrict__ bits, const double *__restrict__ lgt,
@@ -3359,7 +3440,7 @@ static void allow_big_lds() {
     } while (0)
 
 hipError_t launch_setup(const Tables &tb, int bL, int W, int bG, int bA, int d, uint32_t N,
-                        uint32_t K, hipStream_t st) {
+                        uint32_t K, const ParamBlock &pb, const SetupArgs &sa, hipStream_t st) {
     static const struct OrdTable {
         LaneOrder o[9];
         OrdTable() {
@@ -3375,8 +3456,12 @@ hipError_t launch_setup(const Tables &tb, int bL, int W, int bG, int bA, int d, 
     g.i = g.a + blocks(1ull << (N - bA));
     g.f = g.i + blocks(K);
     g.h = g.f + blocks(1ull << (N + 1 - bL));
-    hipLaunchKernelGGL(k_tables, dim3(g.h), dim3(kThreads), 0, st, tb,
-                       ord_tables.o[std::min(std::max(d, 0), 8)], g, bL, W, bG, bA, d, (int)N, K);
+    g.p = g.h + 1;
+    g.b = g.p + (sa.bits ? blocks((uint64_t)(N + 1) * ((sa.m + 63) / 64) * 64) : 0);
+    g.g = g.b + (sa.table_r > 0 ? std::min(blocks(10ull * (sa.m + 1)), 1024u) : 0);
+    hipLaunchKernelGGL(k_setup, dim3(g.g), dim3(kThreads), 0, st, tb,
+                       ord_tables.o[std::min(std::max(d, 0), 8)], g, bL, W, bG, bA, d, (int)N, K,
+                       pb, sa);
     BN_CHECK_LAUNCH();
     return hipSuccess;
 }
@@ -3404,15 +3489,9 @@ hipError_t launch_scores(int n, int m, const uint8_t *data, const uint8_t *arity
                          int kind, double ess, const uint32_t *famask, int max_bins,
                          double *out, hipStream_t st, uint32_t *bits, int uniform_r, int d,
                          bool tables, double *lgt) {
-    const dim3 tgrid((unsigned)std::min((10 * (m + 1) + kThreads - 1) / kThreads, 1024));
     if (bits) {
-        // all-binary data, d <= 4: counts from bit planes
+        // all-binary data, d <= 4: counts from the bit planes
         const int W = (m + 31) / 32;
-        hipLaunchKernelGGL(k_pack2, dim3((unsigned)((n * W + kThreads - 1) / kThreads)),
-                           dim3(kThreads), 0, st, n, m, W, data, bits);
-        BN_CHECK_LAUNCH();
-        hipLaunchKernelGGL(k_lgamma_table, tgrid, dim3(kThreads), 0, st, m, 2, kind, ess, lgt);
-        BN_CHECK_LAUNCH();
         hipLaunchKernelGGL(k_scores2, dim3((unsigned)((n * K + 15) / 16)), dim3(kThreads), 0, st,
                            n, W, m, K, famask, (const uint32_t *)bits, (const double *)lgt, out);
         BN_CHECK_LAUNCH();
@@ -3424,9 +3503,6 @@ hipError_t launch_scores(int n, int m, const uint8_t *data, const uint8_t *arity
         const dim3 grid((sets + 3) / 4);
         const size_t sm = (size_t)4 * max_bins * sizeof(int);
         if (tables) {
-            hipLaunchKernelGGL(k_lgamma_table, tgrid, dim3(kThreads), 0, st, m, uniform_r, kind,
-                               ess, lgt);
-            BN_CHECK_LAUNCH();
             hipLaunchKernelGGL(k_scores_sets<true>, grid, dim3(kThreads), sm, st, n, m, d, data,
                                uniform_r, K, sets, max_bins, kind, ess, (const double *)lgt, out);
         } else
@@ -3492,11 +3568,13 @@ hipError_t launch_lattice(const LatticeArgs &a, const typename P::Store &alpha,
     auto rec = [&](int idx) {
         if (ev && ev->ev[idx]) (void)hipEventRecord(ev->ev[idx], st);
     };
+    const bool lin = a.fused || (a.bA == 13 && a.lin_mode && a.Zs);
     hipLaunchKernelGGL(k_prep<P>, dim3(n, (a.K + kPrepChunk - 1) / kPrepChunk), dim3(kThreads),
                        0, st, n, d, a.K,
                        (const uint32_t *)tb.binom, (const double *)a.logp,
                        (const double *)a.log_rho, (const double *)a.log_q, a.gauge, beta, qt,
-                       a.gauge_exp, a.fbA, a.fbG, a.rtG);
+                       a.gauge_exp, a.fbA, a.fbG, a.rtG, lin ? a.betal : nullptr,
+                       (typename P::Anchor *)a.anc, a.linok, a.fused ? a.emax : nullptr);
     BN_CHECK_LAUNCH();
     rec(1);
     if constexpr (std::is_same<P, PolX32>::value) {
@@ -3511,9 +3589,6 @@ hipError_t launch_lattice(const LatticeArgs &a, const typename P::Store &alpha,
         const unsigned nblkA = (unsigned)(n << (N - 13));
         if (a.lin_mode && a.Zs) {
             using A = typename P::Anchor;
-            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_prep_lin<P>), dim3(n), dim3(kThreads), 0, st, n,
-                               a.K, (const V *)beta, a.betal, (A *)a.anc, a.linok, nullptr);
-            BN_CHECK_LAUNCH();
             // block-wise seeds: 2^bS tiles per workgroup, 4 <= bS <= 8, with at
             // least 4 high bits left so that the grid holds n * 16 workgroups
             const int hA = N - 13, bS = hA - 4 < 8 ? hA - 4 : 8;
@@ -3681,12 +3756,16 @@ static hipError_t launch_gamma_edges(const LatticeArgs &a, const typename P::Sto
                 allow_big_lds<k_gamma_tile_retry<P>>();
                 hipLaunchKernelGGL(HIP_KERNEL_NAME(k_gamma_tile_retry<P>),
                                    dim3(std::min(nblkG, 1024u)), dim3(kThreads), sm, st, n, d, gg,
-                                   tb, L, R, (const V *)qt, Y1, (const uint32_t *)a.rtG, a.fbG);
-                BN_CHECK_LAUNCH();
-                allow_big_lds<k_gamma_tile_fb<P>>();
-                hipLaunchKernelGGL(HIP_KERNEL_NAME(k_gamma_tile_fb<P>),
-                                   dim3(std::min(nblkG, 1024u)), dim3(kThreads), sm, st, n, d, gg,
-                                   tb, L, R, (const V *)qt, Y1, part, (const uint32_t *)a.fbG);
+                                   tb, L, R, (const V *)qt, Y1, part, (const uint32_t *)a.rtG,
+                                   a.fbG);
+                if (a.lin_mode == 2) {   // every tile was sent there
+                    BN_CHECK_LAUNCH();
+                    allow_big_lds<k_gamma_tile_fb<P>>();
+                    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_gamma_tile_fb<P>),
+                                       dim3(std::min(nblkG, 1024u)), dim3(kThreads), sm, st, n, d,
+                                       gg, tb, L, R, (const V *)qt, Y1, part,
+                                       (const uint32_t *)a.fbG);
+                }
             } else {
                 hipLaunchKernelGGL(HIP_KERNEL_NAME(k_gamma_tile<P>), dim3(nblkG), dim3(kThreads),
                                    sm, st, n, d, gg, tb, L, R, (const V *)qt, Y1, part);
@@ -3765,26 +3844,16 @@ static hipError_t launch_gamma_edges(const LatticeArgs &a, const typename P::Sto
         }
     }
     rec(5);
-    hipLaunchKernelGGL(k_edges<P>, dim3(n, n + 1), dim3(kThreads), 0, st, n, a.K,
-                       (const uint32_t *)tb.famask, (const V *)beta, (const V *)gam, L, a.post,
-                       a.resid, a.ps);
-    BN_CHECK_LAUNCH();
     // layer sums of L(S) Rp(S): partials per tile come from the Gamma tile
-    // kernel (12-bit tiles) or from k_inv1 (sweep tiles, small lattices)
-    int bI = 12;
-    if (a.bG != 12) {
-        bI = a.bL;
-        hipLaunchKernelGGL(k_inv1<P>, dim3(1u << nh, a.bL + 1), dim3(kThreads), 0, st, n, a.bL,
-                           tb, L, R, part);
-        BN_CHECK_LAUNCH();
-    }
-    hipLaunchKernelGGL(k_inv2<P>, dim3(n + 1, kInvChunks), dim3(kThreads), 0, st, n, bI,
-                       (const V *)part, layer);
-    BN_CHECK_LAUNCH();
-    hipLaunchKernelGGL(k_finalize<P>, dim3(1), dim3(64), 0, st, n, L, R, (const V *)layer,
-                       (const double *)a.resid, (const double *)a.gauge_exp,
-                       (const unsigned long long *)a.cnt, (const uint32_t *)a.fbA,
-                       (const uint32_t *)a.fbG, a.diag);
+    // kernel (12-bit tiles), else they are taken per sweep tile
+    const int tiled = a.bG == 12 ? std::min(kInvChunks, std::max(1, (1 << (n - 12)) / 256)) : 0;
+    const unsigned ninv = tiled ? (unsigned)((n + 1) * tiled) : (unsigned)(a.bL + 1) << nh;
+    hipLaunchKernelGGL(k_finish<P>, dim3((unsigned)(n * (n + 1)) + ninv), dim3(kThreads), 0, st, n,
+                       a.K, tiled, tiled ? 12 : a.bL, tb, (const uint32_t *)tb.famask,
+                       (const V *)beta, (const V *)gam, L, R, part, layer, a.post, a.resid, a.ps,
+                       (const double *)a.gauge_exp, (const unsigned long long *)a.cnt,
+                       (const uint32_t *)a.fbA, (const uint32_t *)a.fbG,
+                       a.done, a.diag);
     BN_CHECK_LAUNCH();
     rec(6);
     return hipSuccess;
@@ -3822,9 +3891,6 @@ static hipError_t launch_lattice_fused(const LatticeArgs &a, const PolX32::Store
     f.loff = a.tb.loff;
     f.hord = a.tb.hord;
     f.cnt = a.cnt;
-    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_prep_lin<PolX32>), dim3(n), dim3(kThreads), 0, st, n,
-                       a.K, (const X32 *)a.beta, a.betal, (int *)a.anc, a.linok, a.emax);
-    BN_CHECK_LAUNCH();
     rec(8);
     // the alpha tiles' seeds by blocks of 13-bit tiles (doubles, linear-scale
     // nodes), when the grouped kernel applies; the 9-bit seeds come from them

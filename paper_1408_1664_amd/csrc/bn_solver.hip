@@ -51,31 +51,6 @@ struct Range {
     Range &operator=(const Range &) = delete;
 };
 
-// Parameters passed by value to the parameter kernel (host arrays are
-// consumed at launch, so no caller pointer is kept).
-struct ParamBlock {
-    uint8_t arity[32];
-    double log_rho[33];
-    double log_q[32];
-    int has_rho, has_q;
-};
-
-__global__ void k_params(ParamBlock pb, int n, int d, uint8_t *arity, double *log_rho,
-                         double *log_q, unsigned long long *cnt) {
-    const int t = threadIdx.x;
-    if (t < n) {
-        arity[t] = pb.arity[t];
-        log_q[t] = pb.has_q ? pb.log_q[t] : 0.0;
-    }
-    if (t <= d) {
-        // default rho(k) = 1 / C(n-1, k)
-        log_rho[t] = pb.has_rho ? pb.log_rho[t]
-                                : -(lgamma((double)n) - lgamma((double)t + 1.0) -
-                                    lgamma((double)(n - t)));
-    }
-    if (t < 2) cnt[t] = 0ull;
-}
-
 bn_status validate(const bn_problem *p, bool host_data, bool check_values) {
     if (!p) return BN_EINVAL;
     if (p->n < 2 || p->n > 31) return BN_EINVAL;
@@ -227,7 +202,8 @@ static Plan plan_of(int n, int d_in, int m, bn_precision prec, bool with_data, b
     P.o_arity = take(64);
     P.o_rho = take(34 * 8);
     P.o_q = take(32 * 8);
-    P.o_cnt = take(4 * 8);
+    P.o_cnt = take(2 * 8);
+    P.o_done = take(17 * 128);
     P.o_diag = take(16 * 8);
     P.o_resid = take(32 * 8);
     P.o_layer = take(33 * 32 * V);     // layer sums of L(S) Rp(S), 32 tile ranges each
@@ -358,14 +334,7 @@ static bn_status enqueue_scores(const Plan &P, const bn_problem *p, const uint8_
         for (int k = 0; k <= P.d; ++k) pb.log_rho[k] = p->log_rho[k];
     if (p->log_q)
         for (int k = 0; k < P.n; ++k) pb.log_q[k] = p->log_q[k];
-    auto *cnt = reinterpret_cast<unsigned long long *>(ws + P.o_cnt);
-    hipLaunchKernelGGL(k_params, dim3(1), dim3(64), 0, st, pb, P.n, P.d,
-                       reinterpret_cast<uint8_t *>(ws + P.o_arity),
-                       reinterpret_cast<double *>(ws + P.o_rho),
-                       reinterpret_cast<double *>(ws + P.o_q), cnt);
-    HIPCHK(hipGetLastError());
     Tables tb = tables_of(P, ws);
-    HIPCHK(launch_setup(tb, P.bL, P.W, P.bG, P.bA, P.d, P.N, P.K, st));
     const int kind = p->score == BN_SCORE_K2 ? 1 : 0;
     // all-binary data with d <= 4: the bit-plane counting path; one arity r
     // for every variable and d <= 4: scores by sets of variables (q = r^k)
@@ -379,9 +348,23 @@ static bn_status enqueue_scores(const Plan &P, const bn_problem *p, const uint8_
         if (e[0] == '0') tables = false;
     uint32_t *bits = reinterpret_cast<uint32_t *>(ws + P.o_bits);
     double *lgt = reinterpret_cast<double *>(bits + (size_t)2 * P.n * ((std::max(P.m, 1) + 31) / 32));
-    HIPCHK(launch_scores(P.n, P.m, dev_data, reinterpret_cast<const uint8_t *>(ws + P.o_arity), P.K,
-                         kind, p->ess, tb.famask, max_bins_of(p, P.d),
-                         reinterpret_cast<double *>(ws + P.o_logp), st, binary ? bits : nullptr,
+    const int max_bins = max_bins_of(p, P.d);
+    SetupArgs sa{};
+    sa.arity = reinterpret_cast<uint8_t *>(ws + P.o_arity);
+    sa.log_rho = reinterpret_cast<double *>(ws + P.o_rho);
+    sa.log_q = reinterpret_cast<double *>(ws + P.o_q);
+    sa.cnt = reinterpret_cast<unsigned long long *>(ws + P.o_cnt);
+    sa.done = reinterpret_cast<uint32_t *>(ws + P.o_done);
+    sa.data = dev_data;
+    sa.m = P.m;
+    sa.kind = kind;
+    sa.ess = p->ess;
+    sa.bits = binary ? bits : nullptr;
+    sa.table_r = uniform && (binary || tables) ? p->arity[0] : 0;
+    sa.lgt = lgt;
+    HIPCHK(launch_setup(tb, P.bL, P.W, P.bG, P.bA, P.d, P.N, P.K, pb, sa, st));
+    HIPCHK(launch_scores(P.n, P.m, dev_data, sa.arity, P.K, kind, p->ess, tb.famask, max_bins,
+                         reinterpret_cast<double *>(ws + P.o_logp), st, sa.bits,
                          uniform ? p->arity[0] : 0, P.d, tables, lgt));
     return BN_OK;
 }
@@ -418,6 +401,7 @@ static LatticeArgs lattice_args(const Plan &P, char *ws, double *dev_post, doubl
     a.resid = reinterpret_cast<double *>(ws + P.o_resid);
     a.diag = dev_diag ? dev_diag : reinterpret_cast<double *>(ws + P.o_diag);
     a.cnt = reinterpret_cast<unsigned long long *>(ws + P.o_cnt);
+    a.done = reinterpret_cast<uint32_t *>(ws + P.o_done);
     a.tiles_per_layer = P.tiles.data();
     a.gg = P.gg;
     a.lin_mode = P.lin_mode;
