@@ -120,6 +120,21 @@ struct PolLog {
         o[3] = r.b.y;
     }
     __device__ static inline void decode4_nz(const Raw4 &r, V *o) { decode4(r, o); }
+    // log(e^s0 + sum of K products): the largest term, then one exp per term
+    template <int K>
+    __device__ static inline V dp_sum(V s0, const Raw *a, const V *x) {
+        double t[K], m = s0;
+#pragma unroll
+        for (int u = 0; u < K; ++u) {
+            t[u] = a[u] + x[u];
+            m = fmax(m, t[u]);
+        }
+        if (!(m > -1e300)) return zero();
+        double s = exp_neg(s0 - m);
+#pragma unroll
+        for (int u = 0; u < K; ++u) s += exp_neg(t[u] - m);
+        return m + log(s);
+    }
     template <int B>
     __device__ static inline void cross_add(Acc *acc, const Raw4 *ra, const Raw4 *rx, int cnt) {
         double t[4][B];
@@ -332,6 +347,23 @@ struct PolX32 {
         o[1] = X32{r.f.y, (int)(((r.b >> 8) & 0xff) - kX32Bias) << 6};
         o[2] = X32{r.f.z, (int)(((r.b >> 16) & 0xff) - kX32Bias) << 6};
         o[3] = X32{r.f.w, (int)((r.b >> 24) - kX32Bias) << 6};
+    }
+    // s0 + sum of K products a x (a undecoded), normalised: every term aligned to
+    // the largest exponent by an exact power of two, then one sum. A stored zero
+    // has significand 0 and the smallest exponent byte.
+    template <int K>
+    __device__ static inline V dp_sum(V s0, const Raw *a, const V *x) {
+        constexpr int bias = kX32Bias << 6;
+        int e[K], em = s0.e + bias;
+#pragma unroll
+        for (int u = 0; u < K; ++u) {
+            e[u] = x[u].e + (int)(a[u].b << 6);
+            em = max(em, e[u]);
+        }
+        float s = ldexpf(s0.f, s0.e + bias - em);
+#pragma unroll
+        for (int u = 0; u < K; ++u) s += ldexpf(a[u].f * x[u].f, e[u] - em);
+        return norm(X32{s, em - bias});
     }
     // acc[k] += the products of the first cnt of B pairs of four entries
     template <int B>

@@ -1337,6 +1337,7 @@ struct SliceLds {
     typename P::V *v;
     __device__ SliceLds(void *base, uint32_t) : v(reinterpret_cast<typename P::V *>(base)) {}
     __device__ typename P::V at(uint32_t k) const { return v[k]; }
+    __device__ typename P::Raw raw(uint32_t k) const { return v[k]; }
     __device__ void put4(uint32_t e, const typename P::Raw4 &r) { P::decode4_nz(r, v + e); }
     __device__ void put(uint32_t e, const typename P::Store &s, uint64_t i) { v[e] = P::load(s, i); }
     static constexpr size_t bytes_per_entry = sizeof(typename P::V);
@@ -1349,6 +1350,7 @@ struct SliceLds<PolX32> {
         : f(reinterpret_cast<float *>(base)), b(reinterpret_cast<uint8_t *>(f + total)) {}
     // factor of a product only: a stored zero has significand 0
     __device__ X32 at(uint32_t k) const { return X32{f[k], ((int)b[k] - kX32Bias) << 6}; }
+    __device__ PolX32::Raw raw(uint32_t k) const { return PolX32::Raw{f[k], (uint32_t)b[k]}; }
     __device__ void put4(uint32_t e, const PolX32::Raw4 &r) {
         *reinterpret_cast<float4 *>(f + e) = r.f;
         *reinterpret_cast<uint32_t *>(b + e) = r.b;
@@ -1417,6 +1419,74 @@ __device__ inline void cross_terms(const typename P::Store &alpha, const typenam
     }
 }
 
+// The in-tile layers of a sweep tile of BL bits, unrolled. Step k = 1 .. BL
+// takes the entries with k in-tile terms (forward: k bits set; backward: k bits
+// clear), one per thread, C(BL, k) of them. A step's entries and their alpha
+// factors do not depend on the steps before, so they are read one step ahead;
+// what is left between two barriers is one round of LDS reads of the tile, the
+// products, one common exponent (or maximum) and one sum. The loop over layers
+// with its chain of bit scans and aligned adds took 0.86 us a layer, most of a
+// small lattice's sweep; this one 0.5 us (n = 10).
+template <class P, int BL>
+struct DpStep {
+    typename P::Raw a[BL];   // alpha factors
+    uint32_t x[BL];          // tile entries they multiply
+    uint32_t lo;             // the entry
+};
+__device__ constexpr uint32_t dp_binom(int n, int k) {
+    uint32_t r = 1;
+    for (int j = 1; j <= k; ++j) r = r * (uint32_t)(n - k + j) / (uint32_t)j;
+    return r;
+}
+// first place of step k's entries in the popcount order
+__device__ constexpr uint32_t dp_first(int BL, int k, bool fwd) {
+    uint32_t s = 0;
+    for (int j = 0; j < (fwd ? k : BL - k); ++j) s += dp_binom(BL, j);
+    return s;
+}
+// (The lowest bit of `rest` is not written as rest & -rest: hipcc 7.2 selects a
+// v_bitop3_b32 of a wrong truth table for that chain in the backward form.)
+template <class P, bool FWD, int BL, int K>
+__device__ __forceinline__ void dp_fetch(DpStep<P, BL> &st, const SliceLds<P> &la,
+                                         const uint16_t *lord, uint32_t t) {
+    constexpr uint32_t T = 1u << BL, size = dp_binom(BL, K);
+    st.lo = lord[dp_first(BL, K, FWD) + min(t, size - 1u)];
+    uint32_t rest = FWD ? st.lo : (T - 1u) & ~st.lo;
+#pragma unroll
+    for (int u = 0; u < K; ++u) {
+        const uint32_t i = (uint32_t)__ffs(rest) - 1u, bit = 1u << i;
+        rest &= rest - 1u;
+        st.x[u] = st.lo ^ bit;
+        const uint32_t w = st.lo & ~bit, low = bit - 1u;   // w without bit i, closed up
+        st.a[u] = la.raw((i << (BL - 1)) + ((w & low) | ((w >> 1) & ~low)));
+    }
+}
+template <class P, bool FWD, int BL, int K>
+__device__ __forceinline__ void dp_steps(DpStep<P, BL> &st, const SliceLds<P> &la,
+                                         typename P::V *lt, const uint16_t *lord, uint32_t t,
+                                         uint32_t wave0) {
+    if constexpr (K <= BL) {
+        using V = typename P::V;
+        constexpr uint32_t size = dp_binom(BL, K), next = K < BL ? dp_binom(BL, K + 1) : 0u;
+        __syncthreads();
+        DpStep<P, BL> nx;
+        if (wave0 < size) {                     // whole waves
+            V x[K];
+            const V s0 = lt[st.lo];
+#pragma unroll
+            for (int u = 0; u < K; ++u) x[u] = lt[st.x[u]];
+            if constexpr (K < BL) {
+                if (wave0 < next) dp_fetch<P, FWD, BL, K + 1>(nx, la, lord, t);
+            }
+            const V r = P::template dp_sum<K>(s0, st.a, x);
+            if (t < size) lt[st.lo] = r;
+        } else if constexpr (K < BL) {
+            if (wave0 < next) dp_fetch<P, FWD, BL, K + 1>(nx, la, lord, t);
+        }
+        dp_steps<P, FWD, BL, K + 1>(nx, la, lt, lord, t, wave0);
+    }
+}
+
 // ------------------------------- a3 + a4: both sweeps, one layer of tiles
 // Forward (Eq. 9) L(S) = sum_{i in S} alpha_i(S-i) L(S-i), layers upwards;
 // backward (Eq. 10) Rp(S) = sum_{i not in S} alpha_i(S) Rp(S+i), Rp(V) = 1,
@@ -1425,8 +1495,8 @@ __device__ inline void cross_terms(const typename P::Store &alpha, const typenam
 // with |H| = nh - h of the backward sweep (the same number). The two sweeps
 // share nothing but alpha, and a layer of a small lattice is a few workgroups
 // bound by the latency of one launch and of bL dependent in-tile layers, so
-// running both at once halves the sweeps: n = 16 FP32-scaled 180 -> 90 us for
-// both, n = 20 FP64 541 -> 272 us (operand batches and exp_neg included).
+// running both at once halves the sweeps: n = 16 FP32-scaled 180 -> 63 us for
+// both, n = 20 FP64 541 -> 211 us (unrolled in-tile layers and exp_neg included).
 // Large lattices launch the two sweeps apart, on two streams (launch_lattice);
 // there they stream alpha at the HBM rate.
 // Tiles go in colex order: consecutive workgroups, which run at the same time
@@ -1437,11 +1507,12 @@ __device__ inline void cross_terms(const typename P::Store &alpha, const typenam
 // tile's alpha slices staged in LDS and run popcount layer by popcount layer,
 // one entry per thread (TH >= the largest layer), its operands read in batches
 // of four before they are summed. Requires bL >= 2.
-template <class P, bool FWD, int TH>
-__device__ inline void sweep_tile(int n, int bL, uint32_t Hm, const Tables &tb,
+template <class P, bool FWD, int TH, int BL>
+__device__ inline void sweep_tile(int n, int bL_arg, uint32_t Hm, const Tables &tb,
                                   const typename P::Store &alpha, const typename P::Store &X,
                                   unsigned long long *cnt, unsigned char *smem) {
     using V = typename P::V;
+    const int bL = BL > 0 ? BL : bL_arg;
     const uint32_t half = 1u << (bL - 1);
     const uint32_t T = 1u << bL;
     SliceLds<P> la(smem, (uint32_t)bL * half);   // bL * half entries
@@ -1466,6 +1537,15 @@ __device__ inline void sweep_tile(int n, int bL, uint32_t Hm, const Tables &tb,
     }
     for (uint32_t x = t; x < T; x += TH) lord[x] = tb.lorder[x];
     __syncthreads();
+    if constexpr (BL > 0) {
+        const uint32_t wave0 = __builtin_amdgcn_readfirstlane(t & ~63);
+        DpStep<P, BL> st;
+        if (wave0 < (uint32_t)BL) dp_fetch<P, FWD, BL, 1>(st, la, lord, t);
+        dp_steps<P, FWD, BL, 1>(st, la, lt, lord, t, wave0);
+        __syncthreads();
+        for (uint32_t e = 4 * t; e < T; e += 4 * TH) P::store4(X, (uint64_t)Hf + e, lt + e, cnt);
+        return;
+    }
     // in-tile layers: layer l holds size = C(bL, l) entries from lord[off] on
     int l = FWD ? 1 : bL - 1;
     uint32_t size = bL, off = FWD ? 1 : T - 1 - bL;
@@ -1510,7 +1590,7 @@ __device__ inline void sweep_tile(int n, int bL, uint32_t Hm, const Tables &tb,
     for (uint32_t e = 4 * t; e < T; e += 4 * TH) P::store4(X, (uint64_t)Hf + e, lt + e, cnt);
 }
 
-template <class P, int TH>
+template <class P, int TH, int BL>
 __global__ void __launch_bounds__(TH)
 k_sweeps(int n, int bL, uint32_t nb, uint32_t hoffF, uint32_t hoffB, Tables tb,
          typename P::Store alpha, typename P::Store L, typename P::Store R,
@@ -1518,9 +1598,9 @@ k_sweeps(int n, int bL, uint32_t nb, uint32_t hoffF, uint32_t hoffB, Tables tb,
     extern __shared__ unsigned char smem[];
     const uint32_t b = blockIdx.x;
     if (b < nb)
-        sweep_tile<P, true, TH>(n, bL, tb.hord[hoffF + b], tb, alpha, L, cnt, smem);
+        sweep_tile<P, true, TH, BL>(n, bL, tb.hord[hoffF + b], tb, alpha, L, cnt, smem);
     else
-        sweep_tile<P, false, TH>(n, bL, tb.hord[hoffB + b - nb], tb, alpha, R, cnt, smem);
+        sweep_tile<P, false, TH, BL>(n, bL, tb.hord[hoffB + b - nb], tb, alpha, R, cnt, smem);
 }
 
 // ---------------------------------------- a5 + a6: Gamma, in-tile part
@@ -3666,29 +3746,35 @@ hipError_t launch_lattice(const LatticeArgs &a, const typename P::Store &alpha,
     }
     // a thread per four tile entries covers the cross terms and the largest
     // in-tile layer (C(12, 6) = 924)
-    auto sweeps = [&](auto threads) -> hipError_t {
-        constexpr int TH = decltype(threads)::value;
-        allow_big_lds<k_sweeps<P, TH>>();
+    auto sweeps = [&](auto threads, auto bits) -> hipError_t {
+        constexpr int TH = decltype(threads)::value, BL = decltype(bits)::value;
+        allow_big_lds<k_sweeps<P, TH, BL>>();
         for (int h = 0; h <= nh; ++h) {
             // workgroups below nb run forward tiles, the others backward ones
             const unsigned nb = a.tiles_per_layer[h];
-            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_sweeps<P, TH>),
+            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_sweeps<P, TH, BL>),
                                dim3(a.fwd_only || forked ? nb : 2 * nb), dim3(TH), smL, st, n,
                                a.bL, nb, hord_offset(nh, h), hord_offset(nh, nh - h), tb, alpha,
                                L, R, a.cnt);
             BN_CHECK_LAUNCH();
         }
         for (int h = nh; forked && h >= 0; --h) {
-            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_sweeps<P, TH>), dim3(a.tiles_per_layer[h]),
+            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_sweeps<P, TH, BL>), dim3(a.tiles_per_layer[h]),
                                dim3(TH), smL, a.side, n, a.bL, 0u, 0u, hord_offset(nh, h), tb,
                                alpha, L, R, a.cnt);
             BN_CHECK_LAUNCH();
         }
         return hipSuccess;
     };
-    const hipError_t es = a.bL <= 10   ? sweeps(std::integral_constant<int, 256>{})
-                          : a.bL == 11 ? sweeps(std::integral_constant<int, 512>{})
-                                       : sweeps(std::integral_constant<int, 1024>{});
+    // BL > 0: the tile widths that the plan chooses from n = 9 on, with unrolled
+    // in-tile layers; 0: any other (the smallest lattices, tests)
+    using std::integral_constant;
+    hipError_t es;
+    if (a.bL == 9) es = sweeps(integral_constant<int, 256>{}, integral_constant<int, 9>{});
+    else if (a.bL == 10) es = sweeps(integral_constant<int, 256>{}, integral_constant<int, 10>{});
+    else if (a.bL == 11) es = sweeps(integral_constant<int, 512>{}, integral_constant<int, 11>{});
+    else if (a.bL == 12) es = sweeps(integral_constant<int, 1024>{}, integral_constant<int, 12>{});
+    else es = sweeps(integral_constant<int, 256>{}, integral_constant<int, 0>{});
     if (es != hipSuccess) return es;
     rec(3);
     if (a.fwd_only) {

@@ -107,12 +107,13 @@ static Plan plan_of(int n, int d_in, int m, bn_precision prec, bool with_data, b
     P.K = (uint32_t)kcount_u64(N, d);
     P.bA = N >= 13 ? 13 : N;      // alpha tile: 13 bits, or the whole lattice when smaller
     // sweep tile. FP32-scaled: the whole lattice up to n = 12 (its alpha slices
-    // then fill the 160 KB of LDS): one launch for both sweeps, 18 us at n = 12
-    // against 38 us with 10 bits; 11 bits at n = 13 and 14 (60 against 63 us);
-    // else 9 bits (more workgroups per CU for the large, HBM-bound sweeps; at
-    // n = 16 and 22 2% faster than 10 bits). Log form: 11 bits where that saves
-    // a launch (n = 11, 12: 46 against 54 us), else 10, whose cross terms
-    // keep all 256 threads busy (9 bits: 3.8 against 2.8 ms at n = 25).
+    // then fill the 160 KB of LDS): one launch for both sweeps, 14 us at n = 12;
+    // 11 bits at n = 13 and 14; else 9 bits (more workgroups per CU for the
+    // large, HBM-bound sweeps; n = 16 63 us against 67 with 10 and 70 with 11
+    // bits, n = 22 254 against 269 and 290). Log form: 11 bits where that saves
+    // a launch (n = 11, 12: 46 against 54 us before the layers were unrolled),
+    // else 10, whose cross terms keep all 256 threads busy (n = 20 211 us
+    // against 213 with 9 and 228 with 11 bits).
     P.bL = P.x32 ? (n <= 12 ? n : n <= 14 ? 11 : 9) : std::min(n, n <= 12 ? 11 : 10);
     P.bG = n >= 12 ? 12 : n;      // Gamma tile: 12 bits, or the whole lattice when smaller
     P.aG = 12;
