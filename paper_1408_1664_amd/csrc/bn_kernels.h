@@ -37,7 +37,8 @@ struct GammaGeom {
     uint32_t blk1x4[33], blkAx4[33];
     uint32_t KT;      // K(bT, d): ranked seed masks over the tile bits
     uint32_t npat;    // K(bT - 1, d): LDS patterns of the tile zeta
-    int hmax1;        // largest hv among one-level endpoints (LDS of high1)
+    uint32_t kg[32];  // K(bv, d): ranks of Y1_v
+    int hmin1;        // smallest hv among one-level endpoints
 };
 
 struct LatticeArgs {

@@ -2585,50 +2585,6 @@ __device__ inline int find_v(const uint32_t *pref, int n, uint32_t b) {
     return v;
 }
 
-// ---------------------------------- a6: Gamma, high bits, one level
-// Workgroup (v, seed): the vector Y1_v[seed][.] over v's hv high bits;
-// truncated downward zeta keeping |G_H| <= d - |G_L|; writes Gamma_v.
-template <class P>
-__global__ void __launch_bounds__(kThreads)
-k_gamma_high1(int n, int d, uint32_t K, GammaGeom gg, Tables tb,
-              const typename P::V *__restrict__ Y1, typename P::V *__restrict__ gam) {
-    using V = typename P::V;
-    extern __shared__ unsigned char smem[];
-    V *vec = reinterpret_cast<V *>(smem);
-    const int N = n - 1;
-    const int v = find_v(gg.blk1, n, blockIdx.x);
-    const uint32_t s = y1_reader_item(blockIdx.x - gg.blk1[v], 0, gg.kg4[v]);
-    const int t = threadIdx.x;
-    const uint32_t *bn = tb.binom;
-    const int bv = gg.bv[v], hv = gg.hv[v];
-    int sigma;
-    uint32_t cl;
-    seed_of(bn, bv, s, &sigma, &cl);
-    const int tr = d - sigma;
-    const V *src = Y1 + gg.y1off[v] + y1_at(s, 0, hv, gg.kg4[v]);
-    const uint32_t st = y1_stride(s, gg.kg4[v]);
-    for (uint32_t x = t; x < (1u << hv); x += kThreads) vec[x] = src[(size_t)x * st];
-    __syncthreads();
-    for (int j = 0; j < hv; ++j) {
-        const uint32_t cntj = Kcount(bn, j, d);  // walk the d-table, skip > tr
-        const uint32_t tot = cntj << (hv - 1 - j);
-        for (uint32_t idx = t; idx < tot; idx += kThreads) {
-            const uint32_t hi = idx / cntj;
-            const uint32_t p = tb.pat[idx - hi * cntj];
-            if (__popc(p) > tr) continue;
-            const uint32_t Tm = (hi << (j + 1)) | p;
-            vec[Tm] = P::add(vec[Tm], vec[Tm | (1u << j)]);
-        }
-        __syncthreads();
-    }
-    const uint32_t npat = Kcount(bn, hv, d);
-    for (uint32_t idx = t; idx < npat; idx += kThreads) {
-        const uint32_t x = tb.pat[idx];
-        if (__popc(x) > tr) continue;
-        gam[(size_t)v * K + out_rank(bn, N, sigma, cl, x, bv)] = vec[x];
-    }
-}
-
 // ------------------------------- a6: Gamma, high bits, two levels (A, B)
 // Level A, workgroup (v, seed, Ht): the low a bits of Hc; output for every
 // a-bit pattern p with at most d ones: Y2_v[seed][p][Ht].
@@ -2849,7 +2805,7 @@ k_gamma_highA12_log(int n, int d, uint32_t KA, int force_trunc, GammaGeom gg, Ta
         return;
     }
 #pragma unroll
-    for (int r = 0; r < 16; ++r) g[r] = g[r] > -1e300 ? ldexp(exp(g[r] - mx), 960) : 0.0;
+    for (int r = 0; r < 16; ++r) g[r] = g[r] > -1e300 ? ldexp(exp_neg(g[r] - mx), 960) : 0.0;
     dense_zeta_down12_regs<Lin64>(g, vec, t);
     bool small = false;
     for (uint32_t pi = t; pi < KA; pi += kThreads) {
@@ -2860,7 +2816,7 @@ k_gamma_highA12_log(int n, int d, uint32_t KA, int force_trunc, GammaGeom gg, Ta
         const double off = mx - 960.0 * 0.69314718055994530942;
         for (uint32_t pi = t; pi < KA; pi += kThreads) {
             const double y = vec[padx(tb.pat[pi])];
-            out_at(pi) = y > 0.0 ? log(y) + off : -__builtin_huge_val();
+            out_at(pi) = y > 0.0 ? log_pos(y) + off : -__builtin_huge_val();
         }
         return;
     }
@@ -2880,6 +2836,190 @@ k_gamma_highA12_log(int n, int d, uint32_t KA, int force_trunc, GammaGeom gg, Ta
         __syncthreads();
     }
     for (uint32_t pi = t; pi < KA; pi += kThreads) out_at(pi) = vec[tb.pat[pi]];
+}
+
+// Downward zeta of 4096 entries over the index bits of `bits`, one after the
+// other as in dense_zeta_down12_regsC (layout C in g, the results in vec[padx]).
+template <class P>
+__device__ __forceinline__ void masked_zeta_down12(typename P::V (&g)[16], typename P::V *vec,
+                                                   uint32_t bits, uint32_t t) {
+    constexpr int NR = 16;
+    auto zeta4 = [&](int first) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if ((bits >> (first + q)) & 1) {
+#pragma unroll
+                for (int r = 0; r < NR; ++r)
+                    if (!((r >> q) & 1)) g[r] = P::add(g[r], g[r | (1 << q)]);
+            }
+    };
+    zeta4(8);
+#pragma unroll
+    for (int r = 0; r < NR; ++r) vec[padx((r << 8) | t)] = g[r];
+    __syncthreads();
+    const uint32_t tlo = t & 15, thi = t >> 4;
+    if (bits & 0xf0u) {
+#pragma unroll
+        for (int r = 0; r < NR; ++r) g[r] = vec[padx((thi << 8) | (r << 4) | tlo)];
+        zeta4(4);
+#pragma unroll
+        for (int r = 0; r < NR; ++r) vec[padx((thi << 8) | (r << 4) | tlo)] = g[r];
+        __syncthreads();
+    }
+    if (bits & 0xfu) {
+#pragma unroll
+        for (int r = 0; r < NR; ++r) g[r] = vec[padx((t << 4) | r)];
+        zeta4(0);
+#pragma unroll
+        for (int r = 0; r < NR; ++r) vec[padx((t << 4) | r)] = g[r];
+        __syncthreads();
+    }
+}
+
+// ---------------------------------- a6: Gamma, high bits, one level
+// The vectors Y1_v[rank][.] over v's hv <= 12 high bits, 2^(12 - hv) ranks (4096
+// entries) per workgroup: downward zeta over the hv bits, outputs with at most
+// d - |G_L| of them to Gamma_v. While a group of four ranks fits (hv <= 10) the
+// entries keep their order in Y1 (rank mod 4 fastest), so every load is
+// consecutive, and the zeta runs over index bits 2 .. hv + 1; the ranks past
+// the groups, and all ranks for hv = 11 and 12, lie row after row.
+// Log form: each row's logarithms become plain doubles under a scale of the
+// row, exp(x - M) 2^960 with M >= its largest by less than ln 2, and the adds
+// are FP64 adds; the outputs are kept only if every needed one is at least
+// 2^-1000 (the values that fell below 2^-1074, at most 4096, then change none
+// by more than 2^-62 of itself); otherwise, or with force_log (tests), the
+// workgroup runs the zeta in log-adds. One row per workgroup, truncated by
+// pattern lists and, in the log form, in log-adds, this was 98 us at n = 20
+// (FP64, d = 4), 1.04 ms at n = 25 and 48 us at n = 22 (FP32-scaled, d = 3);
+// now 41 us, 0.28 ms and 24 us.
+template <class P>
+__global__ void __launch_bounds__(kThreads)
+k_gamma_high1(int n, int d, uint32_t K, int force_log, GammaGeom gg, Tables tb,
+              const typename P::V *__restrict__ Y1, typename P::V *__restrict__ gam) {
+    using V = typename P::V;
+    constexpr bool kLog = std::is_same<P, PolLog>::value;
+    extern __shared__ unsigned char smem[];
+    V *vec = reinterpret_cast<V *>(smem);                              // 2^12 entries, padded
+    uint32_t *bn = reinterpret_cast<uint32_t *>(vec + 4096 + 256);     // binomials
+    uint32_t *cum = bn + 33 * 33;                                      // cum[k] = K(n - 1, k - 1)
+    uint32_t *rowinfo = cum + 34;          // per row: colex rank of G_L, |G_L| in the top bits
+    int *rowmax = reinterpret_cast<int *>(rowinfo + (4096u >> gg.hmin1));
+    const int N = n - 1;
+    const int v = find_v(gg.blk1, n, blockIdx.x);
+    const uint32_t item = blockIdx.x - gg.blk1[v];
+    const uint32_t t = threadIdx.x;
+    const int bv = gg.bv[v], hv = gg.hv[v];
+    const uint32_t kg4 = gg.kg4[v], kg = gg.kg[v];
+    const uint32_t rows = 4096u >> hv, ymask = (1u << hv) - 1u;
+    const uint32_t nG = hv <= 10 ? (kg4 + rows - 1) / rows : 0u;       // grouped chunks
+    const bool grouped = item < nG;
+    const uint32_t s0 = grouped ? item * rows
+                        : hv <= 10 ? kg4 + (item - nG) * rows
+                        : hv == 12 ? y1_reader_item(item, 0, kg4) : item * rows;
+    const uint32_t s1 = min(grouped ? kg4 : kg, s0 + rows);
+    const V *src = Y1 + gg.y1off[v];
+    // entry x of the chunk: rank s0 + row(x), high part y(x)
+    auto row_of = [&](uint32_t x) {
+        return grouped ? ((x >> (hv + 2)) << 2) | (x & 3u) : x >> hv;
+    };
+    auto y_of = [&](uint32_t x) { return grouped ? (x >> 2) & ymask : x & ymask; };
+    const uint32_t bits = grouped ? ymask << 2 : ymask;
+    const V *gsrc = src + ((size_t)s0 << hv);   // grouped: the chunk is contiguous
+    auto load = [&](uint32_t x) -> V {
+        const uint32_t s = s0 + row_of(x);
+        return s < s1 ? (grouped ? gsrc[x] : src[y1_at(s, y_of(x), hv, kg4)]) : P::zero();
+    };
+    V g[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) g[r] = load((r << 8) | t);
+    for (int x = t; x < 33 * 33; x += kThreads) bn[x] = tb.binom[x];
+    __syncthreads();
+    if (t <= (uint32_t)d + 1) cum[t] = Kcount(bn, N, (int)t - 1);
+    for (uint32_t x = t; x < rows && s0 + x < s1; x += kThreads) {
+        int sigma;
+        uint32_t cl;
+        seed_of(bn, bv, s0 + x, &sigma, &cl);
+        rowinfo[x] = cl | ((uint32_t)sigma << 27);
+    }
+    bool lin = false;
+    if constexpr (kLog) {
+        if (!force_log) {
+            lin = true;
+            for (uint32_t x = t; x < rows; x += kThreads) rowmax[x] = -(1 << 30);
+            __syncthreads();
+            // largest of the row's entries held by a thread, then, where lanes
+            // share a row, by the wave, then one LDS maximum per row and wave
+            int e[16];
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                e[r] = (int)ceil(fmax(g[r], -7e8) * 1.4426950408889634074);
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if ((bits >> (8 + q)) & 1) {
+#pragma unroll
+                    for (int r = 0; r < 16; ++r)
+                        if (!((r >> q) & 1)) e[r] = max(e[r], e[r | (1 << q)]);
+                }
+            const int first = grouped ? 2 : 0;
+            const bool lead = hv < 6 || ((t & 63u) >> first) == 0;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                if (((uint32_t)r << 8) & bits) continue;         // uniform
+                if (hv >= 6)
+                    for (int b = first; b < 6; ++b) e[r] = max(e[r], __shfl_xor(e[r], 1 << b));
+                if (lead) atomicMax(&rowmax[row_of((r << 8) | t)], e[r]);
+            }
+            __syncthreads();
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const double M = rowmax[row_of((r << 8) | t)] * 0.69314718055994530942;
+                g[r] = g[r] > -1e300 ? ldexp(exp_neg(g[r] - M), 960) : 0.0;
+            }
+        }
+    }
+    // needed outputs of the chunk: calls f(x, row info, y)
+    auto outputs = [&](auto f) {
+        for (uint32_t x = t; x < 4096u; x += kThreads) {
+            const uint32_t row = row_of(x), y = y_of(x);
+            if (s0 + row >= s1) continue;
+            const uint32_t ri = rowinfo[row];
+            if (__popc(y) + (int)(ri >> 27) <= d) f(x, ri, y);
+        }
+    };
+    auto put = [&](uint32_t ri, uint32_t y, V z) {
+        int k = (int)(ri >> 27);
+        uint32_t rank = ri & 0x7ffffffu;
+        while (y) {
+            const int p = __ffs(y) - 1;
+            y &= y - 1;
+            rank += bn[(bv + p) * 33 + (++k)];
+        }
+        gam[(size_t)v * K + cum[k] + rank] = z;
+    };
+    if constexpr (kLog) {
+        if (lin) {
+            masked_zeta_down12<Lin64>(g, vec, bits, t);
+            bool small = false;
+            outputs([&](uint32_t x, uint32_t, uint32_t) {
+                const double z = vec[padx(x)];
+                // an empty row is zero throughout
+                small = small || !(z >= 0x1p-1000 || rowmax[row_of(x)] <= -(1 << 29));
+            });
+            if (!__syncthreads_or(small ? 1 : 0)) {
+                outputs([&](uint32_t x, uint32_t ri, uint32_t y) {
+                    const double z = vec[padx(x)];
+                    put(ri, y,
+                        z > 0.0 ? log_pos(z) + (rowmax[row_of(x)] - 960) * 0.69314718055994530942
+                                : -__builtin_huge_val());
+                });
+                return;
+            }
+#pragma unroll
+            for (int r = 0; r < 16; ++r) g[r] = load((r << 8) | t);
+        }
+    }
+    masked_zeta_down12<P>(g, vec, bits, t);
+    outputs([&](uint32_t x, uint32_t ri, uint32_t y) { put(ri, y, vec[padx(x)]); });
 }
 
 // Level A for a = 12, FP32-scaled form: the outputs of k_gamma_highA from
@@ -3879,8 +4019,8 @@ static hipError_t launch_gamma_edges(const LatticeArgs &a, const typename P::Sto
         BN_CHECK_LAUNCH();
         if (!(a.bG == 12 && a.lin_mode)) rec(7);
         if (gg.blk1[n] > 0) {
-            // every one-level endpoint with 12 high bits (n = 25): the dense
-            // form, as for level A
+            // every one-level endpoint with 12 high bits (n = 25): the four ranks
+            // of a group per workgroup
             bool all12 = std::is_same<P, PolX32>::value;
             for (int v = 0; v < n && all12; ++v)
                 if (gg.blk1[v + 1] > gg.blk1[v]) all12 = gg.hv[v] == 12;
@@ -3890,10 +4030,14 @@ static hipError_t launch_gamma_edges(const LatticeArgs &a, const typename P::Sto
                                        sizeof(V) * (4096 + 256), st, n, d, a.K, gg, tb,
                                        (const V *)Y1, gam);
             }
-            if (!all12)
+            if (!all12) {
+                allow_big_lds<k_gamma_high1<P>>();
                 hipLaunchKernelGGL(k_gamma_high1<P>, dim3(gg.blk1[n]), dim3(kThreads),
-                                   sizeof(V) << gg.hmax1, st, n, d, a.K, gg, tb, (const V *)Y1,
-                                   gam);
+                                   sizeof(V) * (4096 + 256) + (33 * 33 + 34) * 4 +
+                                       ((size_t)8 << (12 - gg.hmin1)),
+                                   st, n, d,
+                                   a.K, a.lin_mode == 1 ? 0 : 1, gg, tb, (const V *)Y1, gam);
+            }
             BN_CHECK_LAUNCH();
         }
         if (gg.blkA[n] > 0) {

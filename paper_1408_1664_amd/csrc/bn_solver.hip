@@ -150,20 +150,29 @@ static Plan plan_of(int n, int d_in, int m, bn_precision prec, bool with_data, b
     {
         GammaGeom &g = P.gg;
         memset(&g, 0, sizeof(g));
+        g.hmin1 = 12;
         uint64_t y1 = 0, y2 = 0;
-        int hmax1 = 0;
         for (int v = 0; v < n; ++v) {
             g.bv[v] = v < P.bG ? P.bG - 1 : P.bG;
             g.hv[v] = N - g.bv[v];
             const uint64_t kg = kcount_u64(g.bv[v], d);
             g.y1off[v] = y1;
             g.kg4[v] = (uint32_t)kg & ~3u;
+            g.kg[v] = (uint32_t)kg;
             y1 += kg << g.hv[v];
             const bool two = g.hv[v] > P.aG;
             g.y2off[v] = y2;
             if (two) y2 += (kg * P.KA) << (g.hv[v] - P.aG);
-            else hmax1 = std::max(hmax1, g.hv[v]);
-            g.blk1[v + 1] = g.blk1[v] + (two ? 0 : (uint32_t)kg);
+            // one-level workgroups: 2^(12 - hv) ranks each, the ranks past the
+            // groups of four apart (k_gamma_high1)
+            uint32_t one = 0;
+            if (!two) {
+                const uint32_t rows = 4096u >> g.hv[v];
+                g.hmin1 = std::min(g.hmin1, g.hv[v]);
+                one = g.hv[v] <= 10 ? (g.kg4[v] + rows - 1) / rows + (kg > g.kg4[v] ? 1 : 0)
+                                    : ((uint32_t)kg + rows - 1) / rows;
+            }
+            g.blk1[v + 1] = g.blk1[v] + one;
             g.blkA[v + 1] = g.blkA[v] + (two ? (uint32_t)(kg << (g.hv[v] - P.aG)) : 0);
             const uint32_t items4 = g.kg4[v] / 4 + ((uint32_t)kg - g.kg4[v]);
             g.blk1x4[v + 1] = g.blk1x4[v] + (two ? 0 : items4);
@@ -172,7 +181,6 @@ static Plan plan_of(int n, int d_in, int m, bn_precision prec, bool with_data, b
         }
         g.KT = P.KG;
         g.npat = (uint32_t)kcount_u64(std::max(P.bG - 1, 0), d);
-        g.hmax1 = hmax1;
         P.y1_elems = y1;
         P.y2_elems = y2;
         P.two_level = y2 > 0;
