@@ -429,8 +429,12 @@ __global__ void k_prep(int n, int d, uint32_t K, const uint32_t *binom,
     };
     // the row's maximum (every chunk of the row reads the whole row)
     double mx = -__builtin_huge_val();
-    for (uint32_t r = t; r < K; r += kThreads)
-        mx = fmax(mx, log_rho[size_of(r)] + logp[(size_t)i * K + r]);
+    for (int k = 0; k <= d; ++k) {               // size by size: one log rho each
+        double mk = -__builtin_huge_val();
+        for (uint32_t r = (k ? cum[k - 1] : 0u) + t; r < cum[k]; r += kThreads)
+            mk = fmax(mk, logp[(size_t)i * K + r]);
+        mx = fmax(mx, log_rho[k] + mk);
+    }
     mx = block_reduce(mx, red, [](double a, double b) { return fmax(a, b); });
     const double E = (gauge && mx > -1e300) ? rint(mx * 1.4426950408889634074) : 0.0;
     // the row's linear scale (nullable outputs): anchored at B_i(empty), held in
@@ -1219,12 +1223,11 @@ __device__ __forceinline__ void alpha_lin_half(int d, const double *__restrict__
 // force_fb sends every tile there (tests).
 // Four workgroups per CU (LDS allows it): registers are capped to match.
 template <class P>
-__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 4)))
-k_alpha_lin(int n, int d, uint32_t KS, int force_fb, int tl, const double *__restrict__ Zs,
-            const double *__restrict__ betal, uint32_t K, uint32_t offd,
-            const typename P::Anchor *__restrict__ anc, const int *__restrict__ linok,
-            const typename P::V *__restrict__ qt, typename P::Store alpha,
-            unsigned long long *cnt, uint32_t *fb) {
+__device__ __forceinline__ void alpha_lin_tiles(
+    int n, int d, uint32_t KS, int tl, const double *__restrict__ Zs,
+    const double *__restrict__ betal, uint32_t K, uint32_t offd,
+    const typename P::Anchor *__restrict__ anc, const typename P::V *__restrict__ qt,
+    typename P::Store alpha, unsigned long long *cnt) {
     using V = typename P::V;
     using A = typename P::Anchor;
     constexpr int bA = 13, NR = 16;
@@ -1245,10 +1248,6 @@ k_alpha_lin(int n, int d, uint32_t KS, int force_fb, int tl, const double *__res
     const uint32_t tile0 = blockIdx.x << tl;   // 2^tl consecutive tiles of one node
     const int i = tile0 >> hA;
     const int t = threadIdx.x;
-    if (force_fb || !linok[i]) {
-        if (t < (1 << tl)) fb_push(fb, tile0 + t);
-        return;
-    }
     const A T = anc[i];
     if (t < n) sq[t] = qt[t];
     if (t < 14 * 14) cb[t] = (uint16_t)cbin(t / 14, t % 14);
@@ -1291,41 +1290,127 @@ k_alpha_lin(int n, int d, uint32_t KS, int force_fb, int tl, const double *__res
     }
 }
 
-// Generic form for lattices smaller than the 13-bit tile (n - 1 < 13): one
-// tile of bA = n - 1 bits, seeds as above, truncated zeta in LDS.
+template <class P>
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 4)))
+k_alpha_lin(int n, int d, uint32_t KS, int force_fb, int tl, const double *__restrict__ Zs,
+            const double *__restrict__ betal, uint32_t K, uint32_t offd,
+            const typename P::Anchor *__restrict__ anc, const int *__restrict__ linok,
+            const typename P::V *__restrict__ qt, typename P::Store alpha,
+            unsigned long long *cnt, uint32_t *fb) {
+    const uint32_t tile0 = blockIdx.x << tl;   // 2^tl consecutive tiles of one node
+    if (force_fb || !linok[tile0 >> (n - 14)]) {
+        if ((int)threadIdx.x < (1 << tl)) fb_push(fb, tile0 + threadIdx.x);
+        return;
+    }
+    alpha_lin_tiles<P>(n, d, KS, tl, Zs, betal, K, offd, anc, qt, alpha, cnt);
+}
+
+// The same for few tiles (n < 20): a tile that the linear form cannot hold is
+// computed in the number system at once, rather than by a launch of its own
+// that most solves leave at once (4.6 us). The larger LDS tile of that path
+// halves the workgroups per CU, which a grid of this size does not fill.
+template <class P>
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 4)))
+k_alpha_lin_few(int n, int d, uint32_t KS, int force_fb, const double *__restrict__ Zs,
+                const double *__restrict__ betal, uint32_t K, uint32_t offd,
+                const typename P::Anchor *__restrict__ anc, const int *__restrict__ linok,
+                const typename P::V *__restrict__ qt, typename P::Store alpha,
+                unsigned long long *cnt, uint32_t *fb, int use_prk, Tables tb,
+                const typename P::V *__restrict__ beta) {
+    if (force_fb || !linok[blockIdx.x >> (n - 14)]) {
+        if (threadIdx.x == 0) atomicAdd(fb, 1u);
+        alpha_tile<P>(n, d, K, use_prk, tb, beta, qt, alpha, cnt, blockIdx.x);
+        return;
+    }
+    alpha_lin_tiles<P>(n, d, KS, 0, Zs, betal, K, offd, anc, qt, alpha, cnt);
+}
+
+// Plain doubles for the dense zetas.
+struct Lin64 {
+    using V = double;
+    __device__ static inline V add(V a, V b) { return a + b; }
+};
+
+// Upward zeta of the 2^N entries (N <= 12) in vec (padx indices, zero beyond),
+// in three register layouts of four bits each.
+template <class A>
+__device__ __forceinline__ void zeta_up12(typename A::V *vec, int N, uint32_t t) {
+    constexpr int NR = 16;
+    const uint32_t size = 1u << N, tlo = t & 15, thi = t >> 4;
+    typename A::V g[NR];
+    auto zeta4 = [&](int first) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if (first + q < N) {
+#pragma unroll
+                for (int r = 0; r < NR; ++r)
+                    if ((r >> q) & 1) g[r] = A::add(g[r], g[r ^ (1 << q)]);
+            }
+    };
+    auto pass = [&](int first, auto at, bool active) {
+        if (active) {
+#pragma unroll
+            for (int r = 0; r < NR; ++r) g[r] = vec[padx(at(r))];
+            zeta4(first);
+#pragma unroll
+            for (int r = 0; r < NR; ++r) vec[padx(at(r))] = g[r];
+        }
+        __syncthreads();
+    };
+    pass(0, [&](uint32_t r) { return (t << 4) | r; }, (t << 4) < size);
+    if (N > 4) pass(4, [&](uint32_t r) { return (thi << 8) | (r << 4) | tlo; }, (thi << 8) < size);
+    if (N > 8) pass(8, [&](uint32_t r) { return (r << 8) | t; }, true);
+}
+
+// alpha of a small lattice (n - 1 <= 12 bits, n < 14), one workgroup per node:
+// with no high bits every seed is a single family, Z(G) = beta_i(G). A node
+// with a linear scale runs on its scores as plain doubles, any other in the
+// number system. Bound by latency; the scores scattered to LDS and a dense zeta
+// in registers take 5.8 us at n = 10 (FP32-scaled) and 6.8 us at n = 12 (FP64)
+// where truncated passes over LDS, each step's pattern read from memory, took
+// 10 and 26.
 template <class P>
 __global__ void __launch_bounds__(kThreads)
-k_alpha_small(int n, int d, uint32_t K, Tables tb, const typename P::V *__restrict__ beta,
+k_alpha_small(int n, int d, uint32_t K, int use_lin, Tables tb,
+              const typename P::V *__restrict__ beta, const double *__restrict__ betal,
+              const typename P::Anchor *__restrict__ anc, const int *__restrict__ linok,
               const typename P::V *__restrict__ qt, typename P::Store alpha,
               unsigned long long *cnt) {
     using V = typename P::V;
     extern __shared__ unsigned char smem[];
-    V *tile = reinterpret_cast<V *>(smem);
+    V *tile = reinterpret_cast<V *>(smem);                  // 2^12 entries, padded
+    double *lin = reinterpret_cast<double *>(smem);
     __shared__ V sq[32];
     const int N = n - 1;
-    const int bA = N;
     const int i = blockIdx.x;
-    const int t = threadIdx.x;
-    const uint32_t *bn = tb.binom;
-    if (t < n) sq[t] = qt[t];
-    const V *bi = beta + (size_t)i * K;
-    // with no high bits every seed is a single family: Z(G) = beta_i(G)
-    for (uint32_t x = t; x < (1u << bA); x += kThreads) tile[x] = P::zero();
-    __syncthreads();
-    for (uint32_t r = t; r < K; r += kThreads) tile[tb.famask[r]] = bi[r];
-    __syncthreads();
-    for (int j = 0; j < bA; ++j) {
-        const uint32_t cntj = Kcount(bn, bA - 1 - j, d) << j;
-        for (uint32_t idx = t; idx < cntj; idx += kThreads) {
-            const uint32_t lo = idx & ((1u << j) - 1);
-            const uint32_t S = ((uint32_t)tb.pat[idx >> j] << (j + 1)) | (1u << j) | lo;
-            tile[S] = P::add(tile[S], tile[S ^ (1u << j)]);
-        }
-        __syncthreads();
+    const uint32_t t = threadIdx.x, size = 1u << N;
+    const bool is_lin = use_lin && linok[i];
+    if (t < (uint32_t)n) sq[t] = qt[t];
+    for (uint32_t x = t; x < 4096u + 256u; x += kThreads) {
+        if (is_lin) lin[x] = 0.0;
+        else tile[x] = P::zero();
     }
+    __syncthreads();
+    for (uint32_t r = t; r < K; r += kThreads) {
+        const uint32_t x = padx(tb.famask[r]);
+        if (is_lin) lin[x] = betal[(size_t)i * K + r];
+        else tile[x] = beta[(size_t)i * K + r];
+    }
+    __syncthreads();
     const uint64_t base = (uint64_t)i << N;
-    for (uint32_t x = t; x < (1u << bA); x += kThreads)
-        P::store(alpha, base + x, P::mul(sq[__popc(x)], tile[x]), cnt);
+    if (is_lin) {
+        zeta_up12<Lin64>(lin, N, t);
+        const typename P::Anchor T = anc[i];
+        uint32_t nsat = 0, nfl = 0;
+        for (uint32_t x = t; x < size; x += kThreads)
+            P::store_lin_q(alpha, base + x, lin[padx(x)], sq[__popc(x)], T, nsat, nfl);
+        if (nsat) atomicAdd(cnt, (unsigned long long)nsat);
+        if (nfl) atomicAdd(cnt + 1, (unsigned long long)nfl);
+    } else {
+        zeta_up12<P>(tile, N, t);
+        for (uint32_t x = t; x < size; x += kThreads)
+            P::store(alpha, base + x, P::mul(sq[__popc(x)], tile[padx(x)]), cnt);
+    }
 }
 
 // ------------------------------------------- a3/a4: sweep helpers
@@ -2755,12 +2840,6 @@ __device__ __forceinline__ void dense_zeta_down12_x4(const X32 *__restrict__ Y1v
     }
 }
 
-// Plain doubles for dense_zeta_down12_regs.
-struct Lin64 {
-    using V = double;
-    __device__ static inline V add(V a, V b) { return a + b; }
-};
-
 // Level A for a = 12 in the log form. The row's logarithms become plain
 // doubles under one scale, exp(x - M) 2^960 with M the row's largest (so the
 // sum of 4096 of them stays below 2^972), the dense 12-bit zeta runs in FP64
@@ -3788,7 +3867,7 @@ hipError_t launch_lattice(const LatticeArgs &a, const typename P::Store &alpha,
     auto rec = [&](int idx) {
         if (ev && ev->ev[idx]) (void)hipEventRecord(ev->ev[idx], st);
     };
-    const bool lin = a.fused || (a.bA == 13 && a.lin_mode && a.Zs);
+    const bool lin = a.fused || (a.bA == 13 ? a.lin_mode && a.Zs : a.lin_mode == 1);
     hipLaunchKernelGGL(k_prep<P>, dim3(n, (a.K + kPrepChunk - 1) / kPrepChunk), dim3(kThreads),
                        0, st, n, d, a.K,
                        (const uint32_t *)tb.binom, (const double *)a.logp,
@@ -3837,20 +3916,32 @@ hipError_t launch_lattice(const LatticeArgs &a, const typename P::Store &alpha,
             // colex terms of the thread's pattern)
             // (tl < hA keeps the shift count nonnegative: at n = 14 there
             // is a single tile per node and tl stays 0)
-            int tl = 0;
-            while (tl < 6 && tl < hA && ((uint64_t)n << (hA - tl - 1)) >= 4096) ++tl;
-            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_alpha_lin<P>), dim3(nblkA >> tl), dim3(kThreads), smL,
-                               st, n, d, a.KS, a.lin_mode == 2 ? 1 : 0, tl, (const double *)a.Zs,
-                               (const double *)a.betal, a.K,
-                               host_kcount(N, d - 1), (const A *)a.anc, (const int *)a.linok, (const V *)qt, alpha,
-                               a.cnt, a.fbA);
-            BN_CHECK_LAUNCH();
-            rec(9);
-            // tiles the linear form could not hold: a grid that walks the list
-            allow_big_lds<k_alpha_fb<P>>();
-            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_alpha_fb<P>), dim3(std::min(nblkA, 1024u)),
-                               dim3(kThreads), sm, st, n, d, a.K, use_prk, tb, (const V *)beta,
-                               (const V *)qt, alpha, a.cnt, (const uint32_t *)a.fbA);
+            if (n < 20) {
+                allow_big_lds<k_alpha_lin_few<P>>();
+                hipLaunchKernelGGL(HIP_KERNEL_NAME(k_alpha_lin_few<P>), dim3(nblkA),
+                                   dim3(kThreads), std::max(sm, smL), st, n, d, a.KS,
+                                   a.lin_mode == 2 ? 1 : 0, (const double *)a.Zs,
+                                   (const double *)a.betal, a.K, host_kcount(N, d - 1),
+                                   (const A *)a.anc, (const int *)a.linok, (const V *)qt, alpha,
+                                   a.cnt, a.fbA, use_prk, tb, (const V *)beta);
+                BN_CHECK_LAUNCH();
+                rec(9);
+            } else {
+                int tl = 0;
+                while (tl < 6 && tl < hA && ((uint64_t)n << (hA - tl - 1)) >= 4096) ++tl;
+                hipLaunchKernelGGL(HIP_KERNEL_NAME(k_alpha_lin<P>), dim3(nblkA >> tl), dim3(kThreads), smL,
+                                   st, n, d, a.KS, a.lin_mode == 2 ? 1 : 0, tl, (const double *)a.Zs,
+                                   (const double *)a.betal, a.K,
+                                   host_kcount(N, d - 1), (const A *)a.anc, (const int *)a.linok, (const V *)qt, alpha,
+                                   a.cnt, a.fbA);
+                BN_CHECK_LAUNCH();
+                rec(9);
+                // tiles the linear form could not hold: a grid that walks the list
+                allow_big_lds<k_alpha_fb<P>>();
+                hipLaunchKernelGGL(HIP_KERNEL_NAME(k_alpha_fb<P>), dim3(std::min(nblkA, 1024u)),
+                                   dim3(kThreads), sm, st, n, d, a.K, use_prk, tb, (const V *)beta,
+                                   (const V *)qt, alpha, a.cnt, (const uint32_t *)a.fbA);
+            }
         } else {
             allow_big_lds<k_alpha<P>>();
             rec(8);
@@ -3863,8 +3954,10 @@ hipError_t launch_lattice(const LatticeArgs &a, const typename P::Store &alpha,
     } else {
         rec(8);
         hipLaunchKernelGGL(HIP_KERNEL_NAME(k_alpha_small<P>), dim3((unsigned)n), dim3(kThreads),
-                           sizeof(V) << N, st, n, d, a.K, tb, (const V *)beta, (const V *)qt,
-                           alpha, a.cnt);
+                           sizeof(V) * (4096 + 256), st, n, d, a.K, lin ? 1 : 0, tb,
+                           (const V *)beta, (const double *)a.betal,
+                           (const typename P::Anchor *)a.anc, (const int *)a.linok,
+                           (const V *)qt, alpha, a.cnt);
         BN_CHECK_LAUNCH();
         rec(9);
     }

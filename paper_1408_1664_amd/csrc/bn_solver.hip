@@ -242,7 +242,7 @@ static Plan plan_of(int n, int d_in, int m, bn_precision prec, bool with_data, b
     P.o_part = take(std::max(((size_t)1 << nh) * (P.bL + 1),
                              n >= 12 ? ((size_t)1 << (n - 12)) * 13 : (size_t)0) * V);
     P.o_fbA = P.fused ? take(8) : (P.bA == 13 ? take(4 * (1 + ((size_t)n << (N - 13)))) : 0);
-    P.o_betal = (P.bA == 13 || P.fused) ? take((size_t)n * P.K * 8) : 0;
+    P.o_betal = take((size_t)n * P.K * 8);
     // Linear alpha tiles keep their seeds (K(13, d) doubles per tile) in the
     // workspace when those take at most 16 GiB; otherwise alpha runs in the
     // number system proper.
@@ -417,7 +417,7 @@ static LatticeArgs lattice_args(const Plan &P, char *ws, double *dev_post, doubl
     a.fbA = (P.bA == 13 || P.fused) ? reinterpret_cast<uint32_t *>(ws + P.o_fbA) : nullptr;
     a.fbG = P.bG == 12 ? reinterpret_cast<uint32_t *>(ws + P.o_fbG) : nullptr;
     a.rtG = P.bG == 12 ? reinterpret_cast<uint32_t *>(ws + P.o_rtG) : nullptr;
-    a.betal = (P.bA == 13 || P.fused) ? reinterpret_cast<double *>(ws + P.o_betal) : nullptr;
+    a.betal = reinterpret_cast<double *>(ws + P.o_betal);
     a.anc = ws + P.o_anc;
     a.linok = reinterpret_cast<int *>(ws + P.o_linok);
     a.Zs = P.o_Zs ? reinterpret_cast<double *>(ws + P.o_Zs) : nullptr;
