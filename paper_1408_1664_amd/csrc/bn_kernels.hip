@@ -107,8 +107,7 @@ __device__ inline void ranked_chunk(const uint32_t *bn, int w, int d, uint32_t x
 }
 
 // Every per-problem table in one launch; the grid is split into ranges of
-// workgroups, one range per table (TableGrid), all reading the binomials
-// from constant memory:
+// workgroups, one range per table (TableGrid):
 //   binomials, layer offsets and popcount-ordered masks of the sweep tile,
 //   patterns of at most d ones over W bits (numeric order: the w-bit
 //   patterns are exactly the first K(w, d) entries), the lane order of the
@@ -130,9 +129,15 @@ __device__ void lgamma_table(uint32_t x0, uint32_t step, int m, int r, int kind,
                              double *__restrict__ lgt);
 __global__ void k_setup(Tables tb, LaneOrder oc, TableGrid g, int bL, int W, int bG, int bA,
                         int d, int N, uint32_t K, ParamBlock pb, SetupArgs sa) {
-    const uint32_t *bn = kBinomTab.v;
     const uint32_t blk = blockIdx.x;
     const int t = threadIdx.x;
+    // the ranking loops below read binomials one after the other: from LDS
+    // (from constant memory they took the set-up of n = 10 from 8.4 to 9.6 us)
+    __shared__ uint32_t bn[33 * 33];
+    if (blk < g.h) {
+        for (int x = t; x < 33 * 33; x += kThreads) bn[x] = kBinomTab.v[x];
+        __syncthreads();
+    }
     if (blk < g.s) {
         __shared__ uint32_t loff[34];
         if (blk == 0)
@@ -2448,197 +2453,6 @@ k_gamma_tile_retry(int n, int d, GammaGeom gg, Tables tb, typename P::Store L,
     }
 }
 
-// ------------------------- a5 + a6: Gamma, in-tile part, tiles of any size
-// Generic form used when the lattice is smaller than the 12-bit tile of
-// k_gamma_tile (n < 12): the whole lattice is one tile of bT = n bits.
-// Workgroup = full-mask tile H (the low bT bits vary; entry x = reg * 256 + t)
-// and, when the lattice is that one tile, one endpoint (vsplit = n workgroups;
-// otherwise vsplit = 1). L(H + x) and Rp(H + x) stay in registers for the
-// whole workgroup; each of its endpoints v not in H is served in turn:
-//   g_v(S) = q(|S|) L(S) Rp(S + v) for S = H + x. For v a tile bit, x runs
-//   over the entries without bit v and Rp(S + v) is the partner entry: the
-//   same thread's register when v is a register bit, else read through LDS.
-//   For v above the tile Rp(S + v) is the tile H + v, prefetched while the
-//   previous endpoint is reduced. Products are left unnormalised: the
-//   alignment in add() is exact for any FP32 significand.
-//   Truncated downward zeta over the tile bits other than v: the register
-//   bits densely, then the low 8 bits in LDS, where bit j only updates masks
-//   with at most d ones among the bits already processed (Def. 2; the
-//   predicate of Alg. 3).
-//   The entries with at most d ones go to Y1_v[seed][Hc_v].
-// Consecutive tiles run on the same XCD so that its L2 merges the 8-byte Y1
-// writes of neighbouring tiles.
-template <class P, int RB>
-__global__ void __launch_bounds__(kThreads)
-k_gamma_tile_gen(int n, int d, int bT, int vsplit, GammaGeom gg, Tables tb, typename P::Store L,
-             typename P::Store R, const typename P::V *__restrict__ qt,
-             typename P::V *__restrict__ Y1) {
-    using V = typename P::V;
-    constexpr int NR = 1 << RB;
-    extern __shared__ unsigned char smem[];
-    const uint32_t T = 1u << bT;
-    V *gb = reinterpret_cast<V *>(smem);
-    uint32_t *sbin = reinterpret_cast<uint32_t *>(gb + T);
-    uint32_t *seedT = sbin + 33 * 33;
-    uint16_t *spat = reinterpret_cast<uint16_t *>(seedT + gg.KT);
-    __shared__ V sq[32];
-    const int t = threadIdx.x;
-    const int lb = bT < 8 ? bT : 8;          // thread bits of the tile
-    const int hbits = n - bT;
-    const uint32_t nblk = 1u << hbits;
-    // vsplit workgroups share a tile, workgroup v0 taking the endpoints
-    // v = v0 (mod vsplit)
-    const uint32_t blk = blockIdx.x / (uint32_t)vsplit;
-    const int v0 = (int)(blockIdx.x % (uint32_t)vsplit);
-    uint32_t H = blk;
-    if (nblk >= 64) H = (blk & 7) * (nblk >> 3) + (blk >> 3);
-    const uint64_t Hf = (uint64_t)H << bT;
-    for (int x = t; x < 33 * 33; x += kThreads) sbin[x] = tb.binom[x];
-    for (uint32_t x = t; x < gg.KT; x += kThreads) seedT[x] = tb.seedmask[x];
-    for (uint32_t x = t; x < gg.npat; x += kThreads) spat[x] = tb.pat[x];
-    if (t < n) sq[t] = qt[t];
-    using Raw = typename P::Raw;
-    V Lr[NR], Rr[NR], g[NR];
-    Raw Rv[NR];                               // next endpoint's Rp tile, undecoded
-    uint32_t pc[NR];
-    const bool full = RB > 0 || T >= kThreads;   // every (r, t) maps to an entry
-    {
-        Raw l0[NR], r0[NR];
-#pragma unroll
-        for (int r = 0; r < NR; ++r) {
-            const uint32_t x = r * kThreads + t;
-            pc[r] = __popcll(Hf | x);
-            if (full || x < T) {
-                l0[r] = P::load_raw(L, Hf | x);
-                r0[r] = P::load_raw(R, Hf | x);
-            }
-        }
-#pragma unroll
-        for (int r = 0; r < NR; ++r) {
-            Lr[r] = P::decode_raw(l0[r]);
-            Rr[r] = P::decode_raw(r0[r]);
-        }
-    }
-    int vn = v0;                              // next endpoint above the tile, not in H
-    while (vn < bT) vn += vsplit;
-    while (vn < n && ((Hf >> vn) & 1)) vn += vsplit;
-    if (vn < n) {
-#pragma unroll
-        for (int r = 0; r < NR; ++r) {
-            const uint32_t x = r * kThreads + t;
-            if (full || x < T) Rv[r] = P::load_raw(R, Hf | x | (1ull << vn));
-        }
-    }
-    __syncthreads();
-    const uint32_t *bn = sbin;
-    for (int v = v0; v < n; v += vsplit) {
-        const bool low = v < bT;
-        if (!low && ((Hf >> v) & 1)) continue;
-        if (low && v < lb) {
-            // partner Rp(S + v) lives in another thread: exchange through LDS
-#pragma unroll
-            for (int r = 0; r < NR; ++r) {
-                const uint32_t x = r * kThreads + t;
-                if (full || x < T) gb[x] = Rr[r];
-            }
-            __syncthreads();
-#pragma unroll
-            for (int r = 0; r < NR; ++r) {
-                const uint32_t x = r * kThreads + t;
-                if (!full && x >= T) continue;
-                if ((x >> v) & 1) {
-                    g[r] = P::zero();
-                } else {
-                    g[r] = P::mul_raw(sq[pc[r]], P::mul_raw(Lr[r], gb[x | (1u << v)]));
-                }
-            }
-            __syncthreads();
-        } else if (low) {
-            // v is register bit q: the partner is register r + 2^q of this thread
-#pragma unroll
-            for (int q = 0; q < RB; ++q) {
-                if (v - lb != q) continue;
-#pragma unroll
-                for (int r = 0; r < NR; ++r) {
-                    if ((r >> q) & 1) {
-                        g[r] = P::zero();
-                    } else {
-                        const uint32_t x = r * kThreads + t;
-                        if (full || x < T)
-                            g[r] = P::mul_raw(sq[pc[r]], P::mul_raw(Lr[r], Rr[r | (1 << q)]));
-                    }
-                }
-            }
-        } else {
-#pragma unroll
-            for (int r = 0; r < NR; ++r) {
-                const uint32_t x = r * kThreads + t;
-                if (full || x < T)
-                    g[r] = P::mul_raw(sq[pc[r]], P::mul_raw(Lr[r], P::decode_raw(Rv[r])));
-            }
-            vn = v + vsplit;                  // prefetch the next endpoint's Rp tile
-            while (vn < n && ((Hf >> vn) & 1)) vn += vsplit;
-            if (vn < n) {
-#pragma unroll
-                for (int r = 0; r < NR; ++r) {
-                    const uint32_t x = r * kThreads + t;
-                    if (full || x < T) Rv[r] = P::load_raw(R, Hf | x | (1ull << vn));
-                }
-            }
-        }
-        // register bits (downward, dense), skipping bit v
-#pragma unroll
-        for (int q = 0; q < RB; ++q) {
-            if (low && v == lb + q) continue;
-#pragma unroll
-            for (int r = 0; r < NR; ++r)
-                if (!((r >> q) & 1)) g[r] = P::add(g[r], g[r | (1 << q)]);
-        }
-#pragma unroll
-        for (int r = 0; r < NR; ++r) {
-            const uint32_t x = r * kThreads + t;
-            if (full || x < T) gb[x] = g[r];
-        }
-        __syncthreads();
-        // thread bits in LDS, truncated on the bits already processed
-        for (int j = 0; j < lb; ++j) {
-            if (j == v) continue;
-            const int fb = lb - 1 - j;           // free bits above j
-            const uint32_t cnt = Kcount(bn, j + RB, d) << fb;
-            const uint32_t jm = (1u << j) - 1, fm = (1u << fb) - 1;
-            for (uint32_t idx = t; idx < cnt; idx += kThreads) {
-                const uint32_t p = spat[idx >> fb];
-                const uint32_t Tm = (p & jm) | ((p >> j) << lb) | ((idx & fm) << (j + 1));
-                gb[Tm] = P::add(gb[Tm], gb[Tm | (1u << j)]);
-            }
-            __syncthreads();
-        }
-        // outputs: masks with at most d ones (and without bit v)
-        const int hv = gg.hv[v];
-        const uint32_t Hc = low ? H : (uint32_t)compress_bit(H, v - bT);
-        V *dst = Y1 + gg.y1off[v];
-        for (uint32_t si = t; si < gg.KT; si += kThreads) {
-            const uint32_t msk = seedT[si];
-            uint32_t rank = si;
-            if (low) {
-                if ((msk >> v) & 1) continue;
-                const uint32_t cm = (uint32_t)compress_bit(msk, v);
-                const int sg = __popc(cm);
-                rank = Kcount(bn, bT - 1, sg - 1);
-                int k = 0;
-                uint32_t rest = cm;
-                while (rest) {
-                    const int p = __ffs(rest) - 1;
-                    rest &= rest - 1;
-                    rank += C(bn, p, ++k);
-                }
-            }
-            dst[y1_at(rank, Hc, hv, gg.kg4[v])] = P::norm_v(gb[msk]);
-        }
-        __syncthreads();
-    }
-}
-
 // Output rank (within node v's ranked parent sets) of G_L + (high pattern
 // x shifted by shift), |G_L| = sigma with colex rank cl.
 __device__ inline uint32_t out_rank(const uint32_t *bn, int N, int sigma, uint32_t cl,
@@ -2953,6 +2767,67 @@ __device__ __forceinline__ void masked_zeta_down12(typename P::V (&g)[16], typen
         for (int r = 0; r < NR; ++r) vec[padx((t << 4) | r)] = g[r];
         __syncthreads();
     }
+}
+
+// ------------------------------------- a5 + a6: Gamma of a small lattice
+// n < 12: workgroup = endpoint v, the whole lattice in one block of 4096 (zero
+// beyond 2^n): products q(|S|) L(S) Rp(S + v), downward zeta over every bit but
+// v, outputs straight to Gamma_v. Log form: as in k_gamma_high1, plain doubles
+// under one scale when every output is at least 2^-1000 there, else (or with
+// force_log) log-adds. Latency bound: 5 to 6 us where the tile kernel with its
+// truncated passes over LDS and the copy of its outputs took 17 (n = 10).
+template <class P>
+__global__ void __launch_bounds__(kThreads)
+k_gamma_small(int n, uint32_t K, int force_log, Tables tb, typename P::Store L,
+              typename P::Store R, const typename P::V *__restrict__ qt,
+              typename P::V *__restrict__ gam) {
+    using V = typename P::V;
+    constexpr bool kLog = std::is_same<P, PolLog>::value;
+    extern __shared__ unsigned char smem[];
+    V *vec = reinterpret_cast<V *>(smem);                  // 2^12 entries, padded
+    __shared__ V sq[32];
+    __shared__ double red[kThreads];
+    const int v = blockIdx.x;
+    const uint32_t t = threadIdx.x, size = 1u << n, vb = 1u << v;
+    const uint32_t bits = (size - 1u) & ~vb;
+    if (t < (uint32_t)n) sq[t] = qt[t];
+    __syncthreads();
+    V g[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const uint32_t S = ((uint32_t)r << 8) | t;
+        g[r] = P::zero();
+        if (S < size && !(S & vb))
+            g[r] = P::norm_v(P::mul_raw(P::mul_raw(sq[__popc(S)], P::load(L, S)),
+                                        P::load(R, S | vb)));
+    }
+    auto each = [&](auto f) {
+        for (uint32_t r = t; r < K; r += kThreads)
+            f(r, padx((uint32_t)expand_bit(tb.famask[r], v)));
+    };
+    V *out = gam + (size_t)v * K;
+    if constexpr (kLog) {
+        double mx = -__builtin_huge_val();
+#pragma unroll
+        for (int r = 0; r < 16; ++r) mx = fmax(mx, g[r]);
+        mx = block_reduce(mx, red, [](double x, double y) { return fmax(x, y); });
+        if (!force_log && mx > -1e300) {
+            double y[16];
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                y[r] = g[r] > -1e300 ? ldexp(exp_neg(g[r] - mx), 960) : 0.0;
+            masked_zeta_down12<Lin64>(y, vec, bits, t);
+            bool small = false;
+            each([&](uint32_t, uint32_t at) { small = small || !(vec[at] >= 0x1p-1000); });
+            if (!__syncthreads_or(small ? 1 : 0)) {
+                const double off = mx - 960.0 * 0.69314718055994530942;
+                each([&](uint32_t r, uint32_t at) { out[r] = log_pos(vec[at]) + off; });
+                return;
+            }
+        }
+    }
+    masked_zeta_down12<P>(g, vec, bits, t);
+    each([&](uint32_t r, uint32_t at) { out[r] = P::norm_v(vec[at]); });
 }
 
 // ---------------------------------- a6: Gamma, high bits, one level
@@ -4047,6 +3922,8 @@ static hipError_t launch_gamma_edges(const LatticeArgs &a, const typename P::Sto
     };
     {
         const GammaGeom &gg = a.gg;
+        // n = 12: no high bits, so Y1_v is Gamma_v rank by rank (y1off[v] = v K)
+        if (n == 12) Y1 = gam;
         if (a.bG == 12) {
             const size_t sm = sizeof(V) * (4096 + 256) + 33 * 33 * 4 + (size_t)gg.KT * 4;
             const unsigned nblkG = 1u << (n - 12);
@@ -4090,28 +3967,15 @@ static hipError_t launch_gamma_edges(const LatticeArgs &a, const typename P::Sto
                                    sm, st, n, d, gg, tb, L, R, (const V *)qt, Y1, part);
             }
         } else {
-            const int bT = a.bG;
-            const size_t sm = sizeof(V) * ((size_t)1 << bT) + 33 * 33 * 4 + (size_t)gg.KT * 4 +
-                              (size_t)gg.npat * 2;
-            // a lattice of one tile: one workgroup per endpoint
-            const int vsplit = n == bT ? n : 1;
-            const dim3 g((1u << (n - bT)) * (unsigned)vsplit);
-            const int RB = bT > 8 ? bT - 8 : 0;
-#define BN_GTILE(rb)                                                                           \
-    allow_big_lds<k_gamma_tile_gen<P, rb>>();                                                  \
-    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_gamma_tile_gen<P, rb>), g, dim3(kThreads), sm, st, n, \
-                       d, bT, vsplit, gg, tb, L, R, (const V *)qt, Y1)
-            switch (RB) {
-                case 0: BN_GTILE(0); break;
-                case 1: BN_GTILE(1); break;
-                case 2: BN_GTILE(2); break;
-                default: BN_GTILE(3); break;
-            }
-#undef BN_GTILE
+            hipLaunchKernelGGL(k_gamma_small<P>, dim3((unsigned)n), dim3(kThreads),
+                               sizeof(V) * (4096 + 256), st, n, a.K, a.lin_mode == 1 ? 0 : 1, tb,
+                               L, R, (const V *)qt, gam);
         }
         BN_CHECK_LAUNCH();
         if (!(a.bG == 12 && a.lin_mode)) rec(7);
-        if (gg.blk1[n] > 0) {
+        // up to n = 12 no endpoint has bits above the tile: the tile kernels wrote
+        // Gamma itself
+        if (n > 12 && gg.blk1[n] > 0) {
             // every one-level endpoint with 12 high bits (n = 25): the four ranks
             // of a group per workgroup
             bool all12 = std::is_same<P, PolX32>::value;
