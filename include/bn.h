@@ -140,7 +140,8 @@ bn_status bn_workspace_bytes(int32_t n, int32_t d, int32_t m, bn_precision prec,
  * All n(n-1) edge posteriors from host data: the whole of Algorithm 1 (local
  * scores by Eq. 6, alpha by Eq. 7, the forward and backward sums of Eqs. 9
  * and 10, Gamma by Eq. 12, and P(u -> v | D) by Eq. 11, divided by F(V) =
- * P(D)). Allocates its own device workspace, copies the data, runs every
+ * P(D)). Uses a device workspace of its own (up to 64 MiB of it is kept for
+ * later blocking calls, by at most four of them), copies the data, runs every
  * step on the current HIP device and blocks until done.
  *   post: host, n*n doubles, post[u*n + v] = P(u -> v | D); diagonal 0.
  *   rep:  nullable; per-phase times are measured with HIP events.
@@ -280,7 +281,7 @@ bn_status bn_server_destroy(void *server);
  *   expectation: host, one double, E[f | D] (0 when P(f, D) = 0).
  *   log_pair: nullable host double[2], {log P(D), log P(f, D)} up to the
  *          same constant.
- * Allocates and frees its own workspace; blocks until done. BN_EINVAL as for
+ * Uses a workspace of its own, as bn_edge_posteriors; blocks until done. BN_EINVAL as for
  * bn_edge_posteriors, and for a NULL log_f or expectation or an entry of
  * log_f that is NaN or +inf (checked before any device work).
  */

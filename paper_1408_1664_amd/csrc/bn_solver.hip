@@ -265,7 +265,7 @@ static Plan plan_of(int n, int d_in, int m, bn_precision prec, bool with_data, b
     // per tile when every tile is forced there)
     P.o_fbG = P.bG == 12 ? take(4 * (1 + ((size_t)(n + 1) << (n - 12)))) : 0;
     P.o_rtG = P.bG == 12 ? take(4 * (1 + ((size_t)n << (n - 12)))) : 0;
-    if (with_post) P.o_post = take((size_t)n * n * 8);
+    if (with_post) P.o_post = take(((size_t)n * n + 8) * 8);   // and the diagnostics
     if (with_post) P.o_ps = take((size_t)n * P.K * 8);
     if (with_data) P.o_data = take((size_t)n * (size_t)std::max(m, 1));
     P.total = o;
@@ -501,30 +501,135 @@ bn_status enqueue_solve(const Plan &P, const bn_problem *p, const uint8_t *dev_d
     return run_lattice(P, ws, a, st, ev);
 }
 
+// What a blocking call needs besides its problem: device memory, a pinned
+// staging block and the phase events. hipMalloc, hipFree and seven events cost a
+// small solve as much as its kernels (n = 18: 200 of 430 us), so finished
+// calls leave theirs for the next one: at most kIdleSessions of them in a
+// process, with at most kKeepBytes of device memory each (larger blocks are
+// freed by the call that made them), and all of it is freed when an allocation
+// of these calls fails. A session belongs to one call at a time and is idle only
+// after its stream was synchronised, so threads and streams never share one.
+constexpr size_t kKeepBytes = (size_t)64 << 20;
+constexpr size_t kIdleSessions = 4;
+constexpr size_t kPinBytes = (size_t)1 << 20;   // larger transfers go straight to the caller
+struct HostSession {
+    int dev = -1;
+    char *ws = nullptr;
+    size_t bytes = 0;
+    char *pin = nullptr;
+    PhaseEvents ev{};
+    bool events = false;
+    void free_ws() {
+        if (ws) (void)hipFree(ws);
+        ws = nullptr;
+        bytes = 0;
+    }
+    void destroy() {
+        free_ws();
+        if (pin) (void)hipHostFree(pin);
+        for (hipEvent_t &e : ev.ev)
+            if (e) (void)hipEventDestroy(e);
+        *this = HostSession{};
+    }
+};
+static std::mutex g_idle_mu;
+static std::vector<HostSession> g_idle;
+
+// a session on the current device with at least `bytes` of device memory
+static bn_status take_session(size_t bytes, bool events, HostSession *out) {
+    HostSession s;
+    if (hipGetDevice(&s.dev) != hipSuccess) return BN_EDEVICE;
+    {
+        std::lock_guard<std::mutex> lk(g_idle_mu);
+        // the smallest idle block that fits, else any session of the device
+        int best = -1;
+        for (int k = 0; k < (int)g_idle.size(); ++k) {
+            const HostSession &c = g_idle[k];
+            if (c.dev != s.dev) continue;
+            if (best < 0) best = k;
+            const size_t cur = g_idle[best].bytes;
+            if (c.bytes >= bytes && (cur < bytes || c.bytes < cur)) best = k;
+        }
+        if (best >= 0) {
+            s = g_idle[best];
+            g_idle.erase(g_idle.begin() + best);
+        }
+    }
+    if (s.bytes < bytes) {
+        s.free_ws();
+        auto fits = [&] {
+            size_t free_b = 0, total_b = 0;
+            return hipMemGetInfo(&free_b, &total_b) == hipSuccess && bytes <= free_b &&
+                   hipMalloc(&s.ws, bytes) == hipSuccess;
+        };
+        if (!fits()) {
+            (void)hipGetLastError();
+            std::vector<HostSession> idle;
+            {
+                std::lock_guard<std::mutex> lk(g_idle_mu);
+                idle.swap(g_idle);
+            }
+            for (HostSession &c : idle) c.destroy();
+            s.ws = nullptr;
+            if (!fits()) {
+                (void)hipGetLastError();
+                s.ws = nullptr;
+                s.destroy();
+                return BN_ENOMEM;
+            }
+        }
+        s.bytes = bytes;
+    }
+    if (!s.pin && hipHostMalloc((void **)&s.pin, kPinBytes) != hipSuccess) {
+        (void)hipGetLastError();
+        s.pin = nullptr;                     // transfers then use the caller's memory
+    }
+    if (events && !s.events) {
+        for (int k = 0; k < 7; ++k) (void)hipEventCreate(&s.ev.ev[k]);
+        s.events = true;
+    }
+    *out = s;
+    return BN_OK;
+}
+static void give_session(HostSession &s) {
+    if (s.bytes > kKeepBytes) s.free_ws();
+    std::lock_guard<std::mutex> lk(g_idle_mu);
+    if (g_idle.size() < kIdleSessions) g_idle.push_back(s);
+    else s.destroy();
+}
+
+// Sample data to the device, through the pinned block where it fits.
+static bool put_data(const HostSession &s, uint8_t *dev, const uint8_t *host, size_t bytes,
+                     hipStream_t st) {
+    if (bytes == 0) return true;
+    if (s.pin && bytes <= kPinBytes) {
+        memcpy(s.pin, host, bytes);
+        host = reinterpret_cast<const uint8_t *>(s.pin);
+    }
+    return hipMemcpyAsync(dev, host, bytes, hipMemcpyHostToDevice, st) == hipSuccess;
+}
+
 bn_status local_scores_host(const bn_problem *p, double *log_score) {
     bn_status s = validate(p, true, true);
     if (s != BN_OK) return s;
     if (!log_score) return BN_EINVAL;
     Plan P = make_plan(p->n, p->d, p->m, BN_FP64_LOG, true, false);
     // the parameters, tables, counters and scores all lie below o_scores_end
-    char *ws = nullptr;
     const size_t small = P.o_scores_end;
-    size_t data_bytes = (size_t)P.n * std::max(P.m, 1);
-    if (hipMalloc(&ws, small + align256(data_bytes)) != hipSuccess) return BN_ENOMEM;
-    uint8_t *dev_data = reinterpret_cast<uint8_t *>(ws + small);
+    const size_t data_bytes = (size_t)P.n * P.m;
+    HostSession hs;
+    s = take_session(small + align256(std::max<size_t>(data_bytes, 1)), false, &hs);
+    if (s != BN_OK) return s;
+    uint8_t *dev_data = reinterpret_cast<uint8_t *>(hs.ws + small);
     hipStream_t st = nullptr;
-    bn_status rs = BN_OK;
-    if (P.m > 0 &&
-        hipMemcpyAsync(dev_data, p->data, (size_t)P.n * P.m, hipMemcpyHostToDevice, st) !=
-            hipSuccess)
-        rs = BN_EDEVICE;
-    if (rs == BN_OK) rs = enqueue_scores(P, p, dev_data, ws, st);
+    bn_status rs = put_data(hs, dev_data, p->data, data_bytes, st) ? BN_OK : BN_EDEVICE;
+    if (rs == BN_OK) rs = enqueue_scores(P, p, dev_data, hs.ws, st);
     if (rs == BN_OK &&
-        hipMemcpyAsync(log_score, ws + P.o_logp, (size_t)P.n * P.K * 8, hipMemcpyDeviceToHost,
+        hipMemcpyAsync(log_score, hs.ws + P.o_logp, (size_t)P.n * P.K * 8, hipMemcpyDeviceToHost,
                        st) != hipSuccess)
         rs = BN_EDEVICE;
     if (hipStreamSynchronize(st) != hipSuccess) rs = BN_EDEVICE;
-    (void)hipFree(ws);
+    give_session(hs);
     return rs;
 }
 
@@ -535,43 +640,50 @@ bn_status edge_posteriors_host(const bn_problem *p, bn_precision prec, double *p
     if (!post && !ps) return BN_EINVAL;
     if (prec != BN_FP64_LOG && prec != BN_FP32_SCALED) return BN_EINVAL;
     Plan P = make_plan(p->n, p->d, p->m, prec, true, true);
-    size_t free_b = 0, total_b = 0;
-    if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) return BN_EDEVICE;
-    if (P.total > free_b) return BN_ENOMEM;
-    char *ws = nullptr;
-    if (hipMalloc(&ws, P.total) != hipSuccess) return BN_ENOMEM;
+    HostSession hs;
+    const bool timing = rep != nullptr;
+    s = take_session(P.total, timing, &hs);
+    if (s != BN_OK) return s;
+    char *ws = hs.ws;
+    PhaseEvents &ev = hs.ev;
     hipStream_t st = nullptr;
-    PhaseEvents ev{};
-    bool timing = rep != nullptr;
-    if (timing)
-        for (int k = 0; k < 7; ++k) (void)hipEventCreate(&ev.ev[k]);
     uint8_t *dev_data = reinterpret_cast<uint8_t *>(ws + P.o_data);
+    // the diagnostics follow the posteriors, the parent sets follow both: one
+    // transfer back
+    const size_t npost = (size_t)P.n * P.n;
     double *dev_post = reinterpret_cast<double *>(ws + P.o_post);
-    double *dev_diag = reinterpret_cast<double *>(ws + P.o_diag);
+    double *dev_diag = dev_post + npost;
     double *dev_ps = ps ? reinterpret_cast<double *>(ws + P.o_ps) : nullptr;
-    bn_status rs = BN_OK;
-    if (P.m > 0 &&
-        hipMemcpyAsync(dev_data, p->data, (size_t)P.n * P.m, hipMemcpyHostToDevice, st) !=
-            hipSuccess)
-        rs = BN_EDEVICE;
+    bn_status rs = put_data(hs, dev_data, p->data, (size_t)P.n * P.m, st) ? BN_OK : BN_EDEVICE;
     if (rs == BN_OK)
         rs = enqueue_solve(P, p, dev_data, ws, st, dev_post, dev_diag, timing ? &ev : nullptr,
                            dev_ps);
     double diag[16] = {0};
-    if (rs == BN_OK && post &&
-        hipMemcpyAsync(post, dev_post, (size_t)P.n * P.n * 8, hipMemcpyDeviceToHost, st) !=
-            hipSuccess)
-        rs = BN_EDEVICE;
-    if (rs == BN_OK && ps &&
-        hipMemcpyAsync(ps, dev_ps, (size_t)P.n * P.K * 8, hipMemcpyDeviceToHost, st) !=
-            hipSuccess)
-        rs = BN_EDEVICE;
-    if (rs == BN_OK &&
-        hipMemcpyAsync(diag, dev_diag, 8 * 8, hipMemcpyDeviceToHost, st) != hipSuccess)
-        rs = BN_EDEVICE;
+    const size_t ps_bytes = (size_t)P.n * P.K * 8;
+    const size_t back = ps ? P.o_ps - P.o_post + ps_bytes : (npost + 8) * 8;
+    const bool pinned = hs.pin && back <= kPinBytes;
+    if (rs == BN_OK) {
+        bool ok;
+        if (pinned) {
+            ok = hipMemcpyAsync(hs.pin, dev_post, back, hipMemcpyDeviceToHost, st) == hipSuccess;
+        } else {
+            ok = !post || hipMemcpyAsync(post, dev_post, npost * 8, hipMemcpyDeviceToHost, st) ==
+                              hipSuccess;
+            ok = ok && (!ps || hipMemcpyAsync(ps, dev_ps, ps_bytes, hipMemcpyDeviceToHost, st) ==
+                                   hipSuccess);
+            ok = ok &&
+                 hipMemcpyAsync(diag, dev_diag, 8 * 8, hipMemcpyDeviceToHost, st) == hipSuccess;
+        }
+        if (!ok) rs = BN_EDEVICE;
+    }
     {
         Range rw("bn.wait");
         if (hipStreamSynchronize(st) != hipSuccess) rs = BN_EDEVICE;
+    }
+    if (rs == BN_OK && pinned) {
+        if (post) memcpy(post, hs.pin, npost * 8);
+        if (ps) memcpy(ps, hs.pin + (P.o_ps - P.o_post), ps_bytes);
+        memcpy(diag, hs.pin + npost * 8, 8 * 8);
     }
     if (rs == BN_OK && rep) {
         memset(rep, 0, sizeof(*rep));
@@ -611,9 +723,7 @@ bn_status edge_posteriors_host(const bn_problem *p, bn_precision prec, double *p
                     cnt[0], cnt[1], cnt[2]);
         }
     }
-    if (timing)
-        for (int k = 0; k < 7; ++k) (void)hipEventDestroy(ev.ev[k]);
-    (void)hipFree(ws);
+    give_session(hs);
     return rs;
 }
 
@@ -630,11 +740,10 @@ bn_status feature_posterior_host(const bn_problem *p, bn_precision prec, const d
     const size_t cnt = (size_t)P.n * P.K;
     for (size_t x = 0; x < cnt; ++x)
         if (std::isnan(log_f[x]) || log_f[x] == HUGE_VAL) return BN_EINVAL;
-    size_t free_b = 0, total_b = 0;
-    if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) return BN_EDEVICE;
-    if (P.total > free_b) return BN_ENOMEM;
-    char *ws = nullptr;
-    if (hipMalloc(&ws, P.total) != hipSuccess) return BN_ENOMEM;
+    HostSession hs;
+    s = take_session(P.total, false, &hs);
+    if (s != BN_OK) return s;
+    char *ws = hs.ws;
     hipStream_t st = nullptr;
     uint8_t *dev_data = reinterpret_cast<uint8_t *>(ws + P.o_data);
     double *dev_diag = reinterpret_cast<double *>(ws + P.o_diag);
@@ -642,11 +751,7 @@ bn_status feature_posterior_host(const bn_problem *p, bn_precision prec, const d
     LatticeArgs a = lattice_args(P, ws, nullptr, dev_diag, nullptr);
     a.fwd_only = 1;
     double d0[8] = {0}, d1[8] = {0};
-    bn_status rs = BN_OK;
-    if (P.m > 0 &&
-        hipMemcpyAsync(dev_data, p->data, (size_t)P.n * P.m, hipMemcpyHostToDevice, st) !=
-            hipSuccess)
-        rs = BN_EDEVICE;
+    bn_status rs = put_data(hs, dev_data, p->data, (size_t)P.n * P.m, st) ? BN_OK : BN_EDEVICE;
     if (rs == BN_OK) rs = enqueue_scores(P, p, dev_data, ws, st);
     if (rs == BN_OK) rs = run_lattice(P, ws, a, st, nullptr);
     if (rs == BN_OK && hipMemcpyAsync(d0, dev_diag, 64, hipMemcpyDeviceToHost, st) != hipSuccess)
@@ -661,7 +766,7 @@ bn_status feature_posterior_host(const bn_problem *p, bn_precision prec, const d
     if (rs == BN_OK && hipMemcpyAsync(d1, dev_diag, 64, hipMemcpyDeviceToHost, st) != hipSuccess)
         rs = BN_EDEVICE;
     if (hipStreamSynchronize(st) != hipSuccess) rs = BN_EDEVICE;
-    (void)hipFree(ws);
+    give_session(hs);
     if (rs != BN_OK) return rs;
     *out = d1[0] > -HUGE_VAL ? std::exp(d1[0] - d0[0]) : 0.0;
     if (log_pair) {
