@@ -167,20 +167,33 @@ struct PolLog {
         for (int u = 0; u < K; ++u) s += exp_neg(t[u] - m);
         return m + log_pos(s);
     }
-    template <int B>
-    __device__ static inline void cross_add(Acc *acc, const Raw4 *ra, const Raw4 *rx, int cnt) {
-        double t[4][B];
+    // E consecutive entries (2 or 4), undecoded
+    template <int E>
+    struct RawN {
+        double2 v[E / 2];
+        __device__ void load(const Store &s, uint64_t i) {
+#pragma unroll
+            for (int k = 0; k < E / 2; ++k)
+                v[k] = *reinterpret_cast<const double2 *>(s.p + i + 2 * k);
+        }
+    };
+    // acc[k] += the products of the first cnt of B pairs of E entries
+    template <int E, int B>
+    __device__ static inline void cross_add(Acc *acc, const RawN<E> *ra, const RawN<E> *rx,
+                                            int cnt) {
+        double t[E][B];
 #pragma unroll
         for (int u = 0; u < B; ++u) {
             if (u < cnt) {
-                t[0][u] = ra[u].a.x + rx[u].a.x;
-                t[1][u] = ra[u].a.y + rx[u].a.y;
-                t[2][u] = ra[u].b.x + rx[u].b.x;
-                t[3][u] = ra[u].b.y + rx[u].b.y;
+#pragma unroll
+                for (int k = 0; k < E / 2; ++k) {
+                    t[2 * k][u] = ra[u].v[k].x + rx[u].v[k].x;
+                    t[2 * k + 1][u] = ra[u].v[k].y + rx[u].v[k].y;
+                }
             }
         }
 #pragma unroll
-        for (int k = 0; k < 4; ++k) acc_add_n<B>(acc[k], t[k], cnt);
+        for (int k = 0; k < E; ++k) acc_add_n<B>(acc[k], t[k], cnt);
     }
     __device__ static inline V from_log(double x) { return x; }
     __device__ static inline double to_log(V v) { return v; }
@@ -397,17 +410,37 @@ struct PolX32 {
         for (int u = 0; u < K; ++u) s += ldexpf(a[u].f * x[u].f, e[u] - em);
         return norm(X32{s, em - bias});
     }
-    // acc[k] += the products of the first cnt of B pairs of four entries
-    template <int B>
-    __device__ static inline void cross_add(Acc *acc, const Raw4 *ra, const Raw4 *rx, int cnt) {
+    // E consecutive entries (2 or 4), undecoded
+    template <int E>
+    struct RawN {
+        float f[E];
+        uint32_t b;
+        __device__ void load(const Store &s, uint64_t i) {
+            if constexpr (E == 4) {
+                const Raw4 r = load4_raw(s, i);
+                f[0] = r.f.x, f[1] = r.f.y, f[2] = r.f.z, f[3] = r.f.w;
+                b = r.b;
+            } else {
+                const float2 r = *reinterpret_cast<const float2 *>(s.f + i);
+                f[0] = r.x, f[1] = r.y;
+                b = *reinterpret_cast<const uint16_t *>(s.b + i);
+            }
+        }
+        // factor of a product only (see decode4_nz)
+        __device__ V at(int k) const {
+            return X32{f[k], (int)(((b >> (8 * k)) & 0xff) - kX32Bias) << 6};
+        }
+    };
+    // acc[k] += the products of the first cnt of B pairs of E entries
+    template <int E, int B>
+    __device__ static inline void cross_add(Acc *acc, const RawN<E> *ra, const RawN<E> *rx,
+                                            int cnt) {
 #pragma unroll
         for (int u = 0; u < B; ++u) {
             if (u < cnt) {
-                V a[4], x[4];
-                decode4_nz(ra[u], a);
-                decode4_nz(rx[u], x);
 #pragma unroll
-                for (int k = 0; k < 4; ++k) acc[k] = add(acc[k], mul_raw(a[k], x[k]));
+                for (int k = 0; k < E; ++k)
+                    acc[k] = add(acc[k], mul_raw(ra[u].at(k), rx[u].at(k)));
             }
         }
     }

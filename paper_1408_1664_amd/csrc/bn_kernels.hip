@@ -1485,27 +1485,26 @@ __device__ inline void stage_alpha(const typename P::Store &alpha, uint64_t NN, 
 }
 
 // acc[k] += sum over the nodes i of the mask `nodes` (tile-high bits, the same
-// for the whole workgroup) of alpha_i[S - i] * X[S ^ i], S = Hf + lo + k, k < 4:
-// forward S ^ i = S - i, backward S ^ i = S + i. Four nodes per batch of loads.
-template <class P>
+// for the whole workgroup) of alpha_i[S - i] * X[S ^ i], S = Hf + lo + k, k < E:
+// forward S ^ i = S - i, backward S ^ i = S + i. B nodes per batch of loads.
+template <class P, int E, int B>
 __device__ inline void cross_terms(const typename P::Store &alpha, const typename P::Store &X,
                                    uint64_t NN, uint32_t Hf, uint32_t nodes, uint32_t lo,
                                    typename P::Acc *acc) {
-    constexpr int B = 4;
     while (nodes) {
-        typename P::Raw4 ra[B], rx[B];
+        typename P::template RawN<E> ra[B], rx[B];
         int cnt = 0;
 #pragma unroll
         for (int u = 0; u < B; ++u) {
             if (nodes) {
                 const int i = __ffs(nodes) - 1;
                 nodes &= nodes - 1;
-                ra[u] = P::load4_raw(alpha, (uint64_t)i * NN + compress_bit(Hf & ~(1u << i), i) + lo);
-                rx[u] = P::load4_raw(X, (uint64_t)(Hf ^ (1u << i)) + lo);
+                ra[u].load(alpha, (uint64_t)i * NN + compress_bit(Hf & ~(1u << i), i) + lo);
+                rx[u].load(X, (uint64_t)(Hf ^ (1u << i)) + lo);
                 cnt = u + 1;
             }
         }
-        P::template cross_add<B>(acc, ra, rx, cnt);
+        P::template cross_add<E, B>(acc, ra, rx, cnt);
     }
 }
 
@@ -1614,16 +1613,20 @@ __device__ inline void sweep_tile(int n, int bL_arg, uint32_t Hm, const Tables &
     const uint32_t Hf = Hm << bL;
     const uint32_t highall = ((1u << nh) - 1u) << bL;
     stage_alpha<P, TH>(alpha, NN, Hf, bL, la);
-    for (uint32_t lo = 4 * t; lo < T; lo += 4 * TH) {
-        typename P::Acc acc[4];
+    // entries per thread: two where that occupies every thread (9-bit tiles), and
+    // then eight nodes' loads in flight (both sweeps at n = 22 254 -> 237 us, n = 25
+    // 1.17 -> 1.14 ms; four or six nodes 243 and 240 us, 1.15 and 1.15 ms)
+    constexpr int E = (BL == 9 && TH == 256) ? 2 : 4;
+    for (uint32_t lo = E * t; lo < T; lo += E * TH) {
+        typename P::Acc acc[E];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
+        for (int k = 0; k < E; ++k) {
             const bool start = FWD ? (Hf == 0 && lo + k == 0) : (Hf == highall && lo + k == T - 1);
             acc[k] = P::acc_of(start ? P::one() : P::zero());
         }
-        cross_terms<P>(alpha, X, NN, Hf, FWD ? Hf : (highall & ~Hf), lo, acc);
+        cross_terms<P, E, E == 2 ? 8 : 4>(alpha, X, NN, Hf, FWD ? Hf : (highall & ~Hf), lo, acc);
 #pragma unroll
-        for (int k = 0; k < 4; ++k) lt[lo + k] = P::norm_v(P::acc_value(acc[k]));
+        for (int k = 0; k < E; ++k) lt[lo + k] = P::norm_v(P::acc_value(acc[k]));
     }
     for (uint32_t x = t; x < T; x += TH) lord[x] = tb.lorder[x];
     __syncthreads();
