@@ -3533,58 +3533,97 @@ k_scores_sets(int n, int m, int d, const uint8_t *__restrict__ data, int r, uint
     }
 }
 
-// BDeu / K2 log marginal likelihood of one family from its cell counts
-// (all variables binary: q = 2^k configurations, r = 2 values); lane L < q
-// takes configuration L (the counts count_cells2 left it), partial sums met
-// by a fixed butterfly. The log-gamma values come from the tables of
-// lgamma_table.
+// The k + 1 family scores of a set of k + 1 binary variables from its counts as
+// count_cells2 leaves them (lane L < 2^k: the two counts of configuration L of
+// variables 0 .. k-1, by the value of variable k). Child k: the row of
+// configuration L is the lane's own pair; child j < k: the rows pair the lanes
+// that differ in bit j, one row per value of variable k, taken by the lane
+// without the bit. Lane t < k + 1 returns the score of child t. Partial sums
+// meet in fixed butterflies; log-gamma values from the tables.
 template <int KP>
-__device__ inline double family_score2(const uint32_t *cnt, int lane, const double *lgt,
-                                       int m1) {
+__device__ inline double set_scores2(const uint32_t *cnt, int lane, const double *lgt, int m1) {
     constexpr int Q = 1 << KP;
     const double *lj = lgt + (2 * KP) * m1, *ljk = lgt + (2 * KP + 1) * m1;
     const double lg_aj = lj[0], lg_ajk = ljk[0];
-    double acc = 0.0;
-    if (lane < Q) {
-        const uint32_t c0 = cnt[0], c1 = cnt[1];
-        const uint32_t nj = c0 + c1;
-        if (nj) {
-            double s = lg_aj - lj[nj];
-            if (c0) s += ljk[c0] - lg_ajk;
-            if (c1) s += ljk[c1] - lg_ajk;
-            acc += s;
+    const bool live = lane < Q;
+    const uint32_t c0 = live ? cnt[0] : 0u, c1 = live ? cnt[1] : 0u;
+    double cells = 0.0;
+    if (c0) cells += ljk[c0] - lg_ajk;
+    if (c1) cells += ljk[c1] - lg_ajk;
+    double mine = 0.0;
+#pragma unroll
+    for (int t = 0; t <= KP; ++t) {
+        double acc = cells;
+        uint32_t n0, n1 = 0;
+        if (t == KP) {
+            n0 = c0 + c1;
+        } else {
+            const uint32_t o0 = __shfl_xor(c0, 1 << t, 16), o1 = __shfl_xor(c1, 1 << t, 16);
+            const bool own = !((lane >> t) & 1);
+            n0 = own ? c0 + o0 : 0u;
+            n1 = own ? c1 + o1 : 0u;
         }
+        if (n0) acc += lg_aj - lj[n0];
+        if (n1) acc += lg_aj - lj[n1];
+#pragma unroll
+        for (int o = 8; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 16);
+        if (lane == t) mine = acc;
     }
-    for (int sft = 8; sft > 0; sft >>= 1) acc += __shfl_xor(acc, sft, 16);
-    return acc;
+    return mine;
 }
 
-// Local scores of all-binary data with d <= 4: 16 lanes per family, 16
-// families per workgroup, counts from the bit planes of pack2.
+// Local scores of all-binary data with d <= 4 by sets of variables, as
+// k_scores_sets: 16 lanes per set, 16 sets per workgroup, counts from the bit
+// planes of pack2. The k + 1 families of a set share its counts and the sum over
+// its cells (n = 25, m = 2000, d = 4: 41 us, by families 143; n = 30, d = 3: 15, 48).
 __global__ void __launch_bounds__(kThreads)
-k_scores2(int n, int W, int m, uint32_t K, const uint32_t *__restrict__ famask,
+k_scores2(int n, int W, int m, int d, uint32_t K, uint32_t sets,
           const uint32_t *__restrict__ bits, const double *__restrict__ lgt,
           double *__restrict__ out) {
-    const int g = threadIdx.x >> 4, lane = threadIdx.x & 15;
-    const uint32_t fam = blockIdx.x * 16 + g;
-    if (fam >= (uint32_t)n * K) return;      // whole 16-lane groups leave together
-    const int i = fam / K;
-    const uint32_t r = fam % K;
-    const uint32_t msk = famask[r];
-    int par[4];
-    int k = 0;
-    for (int p = 0; p < 31 && k < 4; ++p)
-        if ((msk >> p) & 1) par[k++] = p < i ? p : p + 1;
+    const int grp = threadIdx.x >> 4, lane = threadIdx.x & 15;
+    uint32_t c = blockIdx.x * 16 + grp;
+    const bool live = c < sets;
+    if (!live) c = 0;                            // dead groups keep the ballots whole
+    int k1 = 1;
+    while (k1 <= d && c >= binom5((uint32_t)n, k1)) c -= binom5((uint32_t)n, k1++);
+    // members, ascending: the largest p with C(p, t) <= c, over the group's lanes
+    int var[5];
+    const int sh = (threadIdx.x & 48);
+#pragma unroll
+    for (int t = 5; t >= 1; --t) {
+        var[t - 1] = 0;
+        const bool in0 = t <= k1 && binom5((uint32_t)lane, t) <= c;
+        const bool in1 = t <= k1 && binom5((uint32_t)lane + 16u, t) <= c;
+        const uint32_t lo = (uint32_t)(__ballot(in0) >> sh) & 0xffffu;
+        const uint32_t hi = (uint32_t)(__ballot(in1) >> sh) & 0xffffu;
+        if (t <= k1) {
+            const int p = __popc(lo) + __popc(hi) - 1;
+            c -= binom5((uint32_t)p, t);
+            var[t - 1] = p;
+        }
+    }
+    if (!live) return;
     uint32_t cnt[32];
     double sc = 0.0;
-    switch (k) {
-        case 0: count_cells2<0>(bits, W, lane, i, par, cnt); sc = family_score2<0>(cnt, lane, lgt, m + 1); break;
-        case 1: count_cells2<1>(bits, W, lane, i, par, cnt); sc = family_score2<1>(cnt, lane, lgt, m + 1); break;
-        case 2: count_cells2<2>(bits, W, lane, i, par, cnt); sc = family_score2<2>(cnt, lane, lgt, m + 1); break;
-        case 3: count_cells2<3>(bits, W, lane, i, par, cnt); sc = family_score2<3>(cnt, lane, lgt, m + 1); break;
-        default: count_cells2<4>(bits, W, lane, i, par, cnt); sc = family_score2<4>(cnt, lane, lgt, m + 1); break;
+    switch (k1) {
+        case 1: count_cells2<0>(bits, W, lane, var[0], var, cnt); sc = set_scores2<0>(cnt, lane, lgt, m + 1); break;
+        case 2: count_cells2<1>(bits, W, lane, var[1], var, cnt); sc = set_scores2<1>(cnt, lane, lgt, m + 1); break;
+        case 3: count_cells2<2>(bits, W, lane, var[2], var, cnt); sc = set_scores2<2>(cnt, lane, lgt, m + 1); break;
+        case 4: count_cells2<3>(bits, W, lane, var[3], var, cnt); sc = set_scores2<3>(cnt, lane, lgt, m + 1); break;
+        default: count_cells2<4>(bits, W, lane, var[4], var, cnt); sc = set_scores2<4>(cnt, lane, lgt, m + 1); break;
     }
-    if (lane == 0) out[fam] = sc;
+    if (lane < k1) {
+        uint32_t rank = 0;
+        int i = 0, size = 0;
+        for (int t = 0; t < k1 - 1; ++t) rank += binom5((uint32_t)(n - 1), t);
+#pragma unroll
+        for (int t = 0; t < 5; ++t) {
+            if (t < k1 && t == lane) i = var[t];
+            if (t < k1 && t != lane)
+                rank += binom5((uint32_t)(t < lane ? var[t] : var[t] - 1), ++size);
+        }
+        out[(size_t)i * K + rank] = sc;
+    }
 }
 
 // -------------------------------------------------------------- launchers
@@ -3669,8 +3708,9 @@ hipError_t launch_scores(int n, int m, const uint8_t *data, const uint8_t *arity
     if (bits) {
         // all-binary data, d <= 4: counts from the bit planes
         const int W = (m + 31) / 32;
-        hipLaunchKernelGGL(k_scores2, dim3((unsigned)((n * K + 15) / 16)), dim3(kThreads), 0, st,
-                           n, W, m, K, famask, (const uint32_t *)bits, (const double *)lgt, out);
+        const uint32_t sets = host_kcount(n, d + 1) - 1;
+        hipLaunchKernelGGL(k_scores2, dim3((sets + 15) / 16), dim3(kThreads), 0, st, n, W, m, d, K,
+                           sets, (const uint32_t *)bits, (const double *)lgt, out);
         BN_CHECK_LAUNCH();
         return hipSuccess;
     }

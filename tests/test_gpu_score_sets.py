@@ -25,3 +25,28 @@ def test_scores_by_sets(n, r, d, m, kind):
     for i in range(n):
         at = [(x & ((1 << i) - 1)) | ((x >> i) << (i + 1)) for x in masks]
         np.testing.assert_allclose(got[i], ref[i, at], rtol=1e-12, atol=1e-10)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kind", ["bdeu", "k2"])
+@pytest.mark.parametrize("n,d,m", [(2, 1, 1), (3, 7, 31), (6, 4, 33), (17, 2, 64), (18, 4, 700),
+                                   (12, 0, 100), (31, 1, 95)])
+def test_binary_scores_by_sets(n, d, m, kind):
+    """Sets counted from bit planes, 16 lanes each: n around the 16 lanes that
+    unrank a set, sample counts around a plane's word."""
+    ds = datagen.random_dag_dataset(n, m, 2, min(3, n - 1), 1.0, seed=60 + n)
+    print(f"binary score sets n={n} d={d} m={m} {kind}", flush=True)
+    got = bn.local_scores(ds.data, ds.arity, d, score=kind, ess=1.5)
+    if n <= 18:
+        ref = O.local_scores(ds.data, ds.arity, d, O.K2 if kind == "k2" else O.BDEU, 1.5)
+        masks = [x for k in range(min(d, n - 1) + 1) for x in range(1 << (n - 1))
+                 if bin(x).count("1") == k]
+        for i in range(n):
+            at = [(x & ((1 << i) - 1)) | ((x >> i) << (i + 1)) for x in masks]
+            np.testing.assert_allclose(got[i], ref[i, at], rtol=1e-12, atol=1e-10)
+        return
+    # one parent at most: each row against the same pair of variables alone
+    for i, j in [(0, 1), (0, n - 1), (n - 1, 0), (15, 16), (16, 15), (n - 2, n - 1)]:
+        pair = bn.local_scores(ds.data[[i, j]], [2, 2], 1, score=kind, ess=1.5)
+        np.testing.assert_allclose(got[i, [0, 1 + (j if j < i else j - 1)]], pair[0], rtol=1e-12,
+                                   atol=1e-10)
