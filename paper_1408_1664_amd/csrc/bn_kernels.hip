@@ -804,7 +804,10 @@ k_alpha_seeds(int n, int d, uint32_t K, uint32_t KS, int use_prk, Tables tb,
         const uint32_t seedoff = Kcount(bn, bA, s - 1);
         for (uint32_t base = 0; base < nseed; base += kThreads) {
             const uint32_t cnt = min(nseed - base, (uint32_t)kThreads);
-            const uint32_t ni = kThreads / cnt;        // lanes per seed
+            // lanes per seed: at most 16, whose parts one lane then adds in turn (with
+            // every lane of the workgroup on the one seed of size 0 that chain took
+            // most of the kernel: n = 16 17 -> 8 us, n = 20, d = 4 25 -> 15 us)
+            const uint32_t ni = min(min((uint32_t)kThreads / cnt, 16u), items);
             const uint32_t seed = base + t % cnt, il = t / cnt;
             double acc = 0.0;
             if (il < ni) {
@@ -3149,9 +3152,22 @@ __device__ inline void edge_sum(int v, int u, int n, uint32_t K,
     }
     const int pu = u < v ? u : u - 1;
     typename P::Acc acc = P::acc_of(P::zero());
-    for (uint32_t r = t; r < K; r += kThreads) {
-        if (u >= 0 && !((famask[r] >> pu) & 1)) continue;
-        P::acc_add(acc, P::mul(beta[(size_t)v * K + r], gam[(size_t)v * K + r]));
+    // four sets per step, their loads together (one at a time, skipping the sets
+    // without u before the loads, was 55 us at n = 25 instead of 33)
+    constexpr int U = 4;
+    for (uint32_t r0 = t; r0 < K; r0 += U * kThreads) {
+        uint32_t fm[U];
+        V b[U], g[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const uint32_t r = min(r0 + k * kThreads, K - 1);
+            fm[k] = u < 0 ? 1u : famask[r] >> pu;
+            b[k] = beta[(size_t)v * K + r];
+            g[k] = gam[(size_t)v * K + r];
+        }
+#pragma unroll
+        for (int k = 0; k < U; ++k)
+            if ((fm[k] & 1u) && r0 + k * kThreads < K) P::acc_add(acc, P::mul(b[k], g[k]));
     }
     const V tot = block_reduce(P::acc_value(acc), red, add);
     if (t == 0) {
@@ -3846,7 +3862,8 @@ hipError_t launch_lattice(const LatticeArgs &a, const typename P::Store &alpha,
                 rec(9);
             } else {
                 int tl = 0;
-                while (tl < 6 && tl < hA && ((uint64_t)n << (hA - tl - 1)) >= 4096) ++tl;
+                const unsigned least = nblkA < 16384u ? 1024u : 4096u;
+                while (tl < 6 && tl < hA && ((uint64_t)n << (hA - tl - 1)) >= least) ++tl;
                 hipLaunchKernelGGL(HIP_KERNEL_NAME(k_alpha_lin<P>), dim3(nblkA >> tl), dim3(kThreads), smL,
                                    st, n, d, a.KS, a.lin_mode == 2 ? 1 : 0, tl, (const double *)a.Zs,
                                    (const double *)a.betal, a.K,
