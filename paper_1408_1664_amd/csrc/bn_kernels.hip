@@ -1027,8 +1027,19 @@ k_alpha_seeds_blk(int n, int d, uint32_t K, uint32_t KS, int b, uint32_t nhiMax,
                 }
                 const uint32_t *hp = hiP + m * nhiMax;
                 const uint32_t nsub = hcnt[d - m];
+                // eight scores in flight, added in order (one at a time this kernel
+                // took 40 us at n = 22 instead of 38, n = 25 125 instead of 112)
                 double acc = 0.0;
-                for (uint32_t jj = 0; jj < nsub; ++jj) acc += bi[lp + hp[jj]];
+                for (uint32_t j0 = 0; j0 < nsub; j0 += 8) {
+                    double x[8];
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) {
+                        const uint32_t j = j0 + k;
+                        x[k] = j < nsub ? bi[lp + hp[min(j, nsub - 1)]] : 0.0;
+                    }
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) acc += x[k];
+                }
                 v[r] = acc;
             }
         }
