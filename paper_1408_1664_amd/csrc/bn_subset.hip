@@ -12,14 +12,23 @@
 // each one read and one write of every entry.
 //   k_subset_tile      the low 12 bits of each 4096-entry tile, in registers
 //                      in three layouts with two LDS transposes (256 threads
-//                      x 16 entries); an upward truncated transform first
-//                      clears every input with more than d ones;
+//                      x 16 entries);
 //   k_subset_group     the remaining bits in passes of at most 9 (split
 //                      evenly), 32 columns x 2^B patterns per workgroup, two
 //                      register layouts joined through LDS;
 //   k_subset_bits<B>   a remainder of B <= 4 bits (nbits 13..16), entirely
 //                      in registers.
 // nbits <= 12: one workgroup in LDS (k_subset_small).
+//
+// An upward transform truncated to |S| <= d only has inputs with at most d
+// ones. A row of entries that agree in the bits not yet summed (those of the
+// running pass and above) is zero as long as it has more than d ones there, so
+// a pass neither reads such rows nor runs a workgroup whose bits above the pass
+// have more than d ones: nobody reads what it would have written until a later
+// pass writes it. Every entry is still written, once, by the last pass, which
+// takes as many bits as it can (up to 9); what the others move shrinks with
+// K(bits above, d) / 2^(bits above). At 2^27 entries, d = 3, the transform moves
+// 1.8 GB instead of 6.4: 1.17 -> 0.33 ms; the sums are those of the dense passes.
 #include <hip/hip_runtime.h>
 
 #include <stdint.h>
@@ -74,6 +83,7 @@ k_subset_tile(F x, double sign, int trunc_d) {
     using V = typename F::V;
     __shared__ V gb[4096 + 256];
     const int t = threadIdx.x;
+    if (trunc_d >= 0 && __popc(blockIdx.x) > trunc_d) return;   // no input in the tile
     const uint64_t base = (uint64_t)blockIdx.x << 12;
     V v[16];
     // layout A: y = t * 16 + r, bits 0..3 in registers
@@ -114,14 +124,17 @@ k_subset_tile(F x, double sign, int trunc_d) {
 // take consecutive lo, so every register load and store is one 2 KB run.
 template <class F, bool UP, int B>
 __global__ void __launch_bounds__(kT)
-k_subset_bits(F x, int j0, double sign) {
+k_subset_bits(F x, int j0, double sign, int trunc_d) {
     constexpr int NR = 1 << B;
     const uint64_t col = (uint64_t)blockIdx.x * kT + threadIdx.x;
     const uint64_t lo = col & ((1ull << j0) - 1);
     const uint64_t hi = (col >> j0) << (j0 + B);
     typename F::V v[NR];
+    const int left = trunc_d >= 0 ? trunc_d - __popcll(hi) : B;   // ones a row may add
+    if (left < 0) return;
 #pragma unroll
-    for (int r = 0; r < NR; ++r) v[r] = x.load(hi | ((uint64_t)r << j0) | lo);
+    for (int r = 0; r < NR; ++r)
+        v[r] = __builtin_popcount(r) <= left ? x.load(hi | ((uint64_t)r << j0) | lo) : F::zero();
 #pragma unroll
     for (int q = 0; q < B; ++q) reg_step<F, UP, NR>(v, q, sign);
 #pragma unroll
@@ -137,9 +150,9 @@ k_subset_bits(F x, int j0, double sign) {
 // 0..TP-1. Bit 4 is a register bit in both, so the exchange runs in two
 // rounds (bit 4 = 0, then 1) through half the entries' worth of LDS. Global
 // accesses are runs of W doubles.
-template <class F, bool UP, int B, int LW>
+template <class F, bool UP, int B, int LW, bool TRUNC>
 __global__ void __launch_bounds__(1 << (B + LW - 5))
-k_subset_group(F x, int j0, double sign) {
+k_subset_group(F x, int j0, double sign, int trunc_d) {
     using V = typename F::V;
     constexpr int W = 1 << LW;
     constexpr int TP = B - 5;
@@ -155,8 +168,18 @@ k_subset_group(F x, int j0, double sign) {
     const uint64_t hi = (w >> cb) << (j0 + B);
     const uint64_t xb = hi | lo;
     V v[32];
+    if constexpr (TRUNC) {
+        const int left = trunc_d - __popcll(hi);       // ones a row may add
+        if (left < 0) return;                          // whole workgroups
+        const int mine = left - __popc(tp);
 #pragma unroll
-    for (int r = 0; r < 32; ++r) v[r] = x.load(xb + ((uint64_t)((tp << 5) | r) << j0));
+        for (int r = 0; r < 32; ++r)
+            v[r] = __builtin_popcount(r) <= mine ? x.load(xb + ((uint64_t)((tp << 5) | r) << j0))
+                                                 : F::zero();
+    } else {
+#pragma unroll
+        for (int r = 0; r < 32; ++r) v[r] = x.load(xb + ((uint64_t)((tp << 5) | r) << j0));
+    }
 #pragma unroll
     for (int q = 0; q < 5; ++q) reg_step<F, UP, 32>(v, q, sign);
     if constexpr (TP > 0) {
@@ -189,15 +212,20 @@ k_subset_group(F x, int j0, double sign) {
     }
 }
 
-template <class F, bool UP, int LW>
-void launch_group(int B, int nbits, F x, int j0, double sign, hipStream_t st) {
+template <class F, bool UP, int LW, bool TRUNC>
+void launch_group(int B, int nbits, F x, int j0, double sign, int trunc_d, hipStream_t st) {
     const dim3 grid((unsigned)(1ull << (nbits - B - LW)));
+    auto go = [&](auto bits) {
+        constexpr int b = decltype(bits)::value;
+        hipLaunchKernelGGL((k_subset_group<F, UP, b, LW, TRUNC>), grid, dim3(1 << (b - 5 + LW)), 0,
+                           st, x, j0, sign, trunc_d);
+    };
     switch (B) {
-        case 5: hipLaunchKernelGGL((k_subset_group<F, UP, 5, LW>), grid, dim3(1 << LW), 0, st, x, j0, sign); break;
-        case 6: hipLaunchKernelGGL((k_subset_group<F, UP, 6, LW>), grid, dim3(1 << (1 + LW)), 0, st, x, j0, sign); break;
-        case 7: hipLaunchKernelGGL((k_subset_group<F, UP, 7, LW>), grid, dim3(1 << (2 + LW)), 0, st, x, j0, sign); break;
-        case 8: hipLaunchKernelGGL((k_subset_group<F, UP, 8, LW>), grid, dim3(1 << (3 + LW)), 0, st, x, j0, sign); break;
-        default: hipLaunchKernelGGL((k_subset_group<F, UP, 9, LW>), grid, dim3(1 << (4 + LW)), 0, st, x, j0, sign); break;
+        case 5: go(std::integral_constant<int, 5>{}); break;
+        case 6: go(std::integral_constant<int, 6>{}); break;
+        case 7: go(std::integral_constant<int, 7>{}); break;
+        case 8: go(std::integral_constant<int, 8>{}); break;
+        default: go(std::integral_constant<int, 9>{}); break;
     }
 }
 
@@ -232,21 +260,32 @@ hipError_t run(F x, int nbits, double sign, int trunc_d, hipStream_t st) {
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int rem = nbits - 12;
-    const int npass = (rem + 8) / 9;          // at most 9 bits per pass, split evenly
+    // at most 9 bits per pass, split evenly; truncated, the first pass takes what
+    // full later ones leave
+    const int npass = (rem + 8) / 9;
     for (int i = 0, j0 = 12; i < npass; ++i) {
-        const int B = rem / npass + (i < rem % npass ? 1 : 0);
+        const int B = trunc_d >= 0 ? (i ? 9 : rem - 9 * (npass - 1))
+                                   : rem / npass + (i < rem % npass ? 1 : 0);
         if (B >= 5) {
             // runs of 32 doubles (256 B); in the FP32-scaled form runs of 64
             // entries, so that the byte plane too moves whole 64-byte segments
-            launch_group<F, UP, std::is_same<F, X32F>::value ? 6 : 5>(B, nbits, x, j0, sign, st);
+            constexpr int LW = std::is_same<F, X32F>::value ? 6 : 5;
+            if (UP && trunc_d >= 0)
+                launch_group<F, UP, LW, UP>(B, nbits, x, j0, sign, trunc_d, st);
+            else
+                launch_group<F, UP, LW, false>(B, nbits, x, j0, sign, -1, st);
         } else {
             // 2^(nbits - B) columns, 256 per workgroup (nbits - B >= 12)
             const dim3 grid((unsigned)(1ull << (nbits - B - 8)));
             switch (B) {
-                case 1: hipLaunchKernelGGL((k_subset_bits<F, UP, 1>), grid, dim3(kT), 0, st, x, j0, sign); break;
-                case 2: hipLaunchKernelGGL((k_subset_bits<F, UP, 2>), grid, dim3(kT), 0, st, x, j0, sign); break;
-                case 3: hipLaunchKernelGGL((k_subset_bits<F, UP, 3>), grid, dim3(kT), 0, st, x, j0, sign); break;
-                default: hipLaunchKernelGGL((k_subset_bits<F, UP, 4>), grid, dim3(kT), 0, st, x, j0, sign); break;
+                case 1: hipLaunchKernelGGL((k_subset_bits<F, UP, 1>), grid, dim3(kT), 0, st, x, j0, sign,
+                                       trunc_d); break;
+                case 2: hipLaunchKernelGGL((k_subset_bits<F, UP, 2>), grid, dim3(kT), 0, st, x, j0, sign,
+                                       trunc_d); break;
+                case 3: hipLaunchKernelGGL((k_subset_bits<F, UP, 3>), grid, dim3(kT), 0, st, x, j0, sign,
+                                       trunc_d); break;
+                default: hipLaunchKernelGGL((k_subset_bits<F, UP, 4>), grid, dim3(kT), 0, st, x, j0, sign,
+                                       trunc_d); break;
             }
         }
         e = hipGetLastError();
