@@ -592,6 +592,15 @@ struct PolX32 {
         *e = k;
         return (float)ldexp(z, -(k << 6));
     }
+    // The same for positive normal z, on the exponent field in the high word
+    // (991 = 1022 - 31: the significand's 64 binary orders begin there): two
+    // FP64 instructions fewer.
+    __device__ static inline float lin_encode_normal(double z, int *e) {
+        const uint32_t s = (uint32_t)__double2hiint(z) - (991u << 20);
+        *e = (int)s >> 26;
+        return (float)__hiloint2double((int)((s & 0x03ffffffu) + (991u << 20)),
+                                       __double2loint(z));
+    }
 };
 
 // -------------------------------------------------------- combinatorics

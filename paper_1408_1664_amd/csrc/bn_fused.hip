@@ -31,7 +31,7 @@
 // the one of the materialised sweeps.
 //
 // Sweep tiles are the 9 low bits of the full mask under a high part H of
-// popcount h (one launch per layer, as k_fwd / k_bwd). For a cross node i
+// popcount h (one launch per layer, as k_sweeps). For a cross node i
 // (a bit of H in the forward sweep, a high bit outside H in the backward
 // one) the tile needs alpha_i over one whole block; for an in-tile node i < 9
 // it needs half a block: the block's compressed bit 8 is the full mask's
@@ -389,7 +389,7 @@ __device__ inline void sweep_items(const FSweep &a, Ctx &c, PolX32::Store X, uin
 // the cross nodes; wave w takes items w, w + 4, ... Each cross item adds
 // alpha_i * X over the whole tile to the wave's sums; the four waves' sums
 // then meet in LDS in a fixed order (bitwise deterministic) and the in-tile
-// layers run as in k_fwd / k_bwd. Every node runs in plain doubles when
+// layers run as in k_sweeps. Every node runs in plain doubles when
 // all_lin (flin[32]) is set, else in the number system.
 template <bool FWD, int NP>
 __global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(4, 4)))

@@ -681,34 +681,6 @@ k_alpha_fb(int n, int d, uint32_t K, int use_prk, Tables tb,
     }
 }
 
-// A double held in LDS as two 32-bit words (4-byte alignment): it moves with
-// 32-bit LDS instructions. The alpha tile's transposes run at about twice
-// the speed this way than with 64-bit LDS instructions.
-struct W2 {
-    uint32_t lo, hi;
-};
-__device__ inline W2 w2_of(double x) {
-    W2 w;
-    __builtin_memcpy(&w, &x, 8);
-    return w;
-}
-__device__ inline double dbl_of(W2 w) {
-    double x;
-    __builtin_memcpy(&x, &w, 8);
-    return x;
-}
-// The same, as two separate planes of 32-bit words: every access is then a
-// 32-bit LDS instruction on consecutive or 33-strided words, free of bank
-// conflicts under the pad32 layout.
-__device__ inline void put_w2(uint32_t *lo, uint32_t *hi, uint32_t ix, double x) {
-    const W2 w = w2_of(x);
-    lo[ix] = w.lo;
-    hi[ix] = w.hi;
-}
-__device__ inline double get_w2(const uint32_t *lo, const uint32_t *hi, uint32_t ix) {
-    return dbl_of(W2{lo[ix], hi[ix]});
-}
-
 __device__ inline void fb_push(uint32_t *fb, uint32_t id) {
     const uint32_t k = atomicAdd(fb, 1u);
     fb[1 + k] = id;
@@ -925,9 +897,6 @@ __device__ inline void store_tile_lin<PolX32, 16>(const PolX32::Store &st, uint6
     store_tile_lin_x32<16>(st, ubase, toff, stride, v, qr, T, cnt);
 }
 
-// Padded LDS index for 2^12-entry halves: one spare word every 16.
-__device__ inline uint32_t pad16(uint32_t x) { return x + (x >> 4); }
-
 // Colex rank of the set bits of a 4-bit mask (bit p is element p).
 __host__ __device__ constexpr uint32_t colex4(uint32_t r) {
     uint32_t c = 0;
@@ -1080,167 +1049,134 @@ k_alpha_seeds_blk(int n, int d, uint32_t K, uint32_t KS, int b, uint32_t nhiMax,
     }
 }
 
-// One 12-bit half of a linear alpha tile (see k_alpha_lin).
-template <class P, int hb>
-__device__ __forceinline__ void alpha_lin_half(int d, const double *__restrict__ zs,
-                                               const double *__restrict__ zd,
-                                               const typename P::V *sq, const uint16_t *ctab,
-                                               const uint16_t *cb,
-                                               const uint32_t *k13, uint32_t *tlo_,
-                                               uint32_t *thi_, uint32_t pt, int h,
-                                               uint64_t base, typename P::Anchor T,
-                                               typename P::Store alpha,
-                                               unsigned long long *cnt) {
-    using V = typename P::V;
-    constexpr int NR = 16;
-    const int t = threadIdx.x;
-    const int kp = __popc(pt);
-    const uint32_t tlo = t & 15, thi = t >> 4;
-    const int kh = __popc(thi);
-    // pad16 indices written as a lane base plus a constant per register, so
-    // that the constants fold into the LDS offsets:
-    //   A: pad16(pt * 16 + r) = 17 pt + r,
-    //   B: pad16(thi * 256 + r * 16 + tlo) = 272 thi + tlo + 17 r,
-    //   C: pad16(r * 256 + t) = t + t / 16 + 272 r
-    const uint32_t ib = thi * 272 + tlo, ic = t + (t >> 4);
-    double v[NR];
-    // ---- layout A: y = pt * 16 + r, tile bits 0..3. The upper half starts
-    //      from its own seeds plus the lower half's (the zeta step over
-    //      tile bit 12 commutes with the others).
-    if (__any(kp <= d)) {
-        // colex terms of pt's bits (tile bits 4..11) with m ones below them,
-        // and of bit 12 on top for the upper half's second seed
-        uint32_t off[5], offu[5], cpt[5], cup[5];
+// LDS of a linear alpha tile: one 32-bit plane of 16 rows of 64 words per wave
+// (4 spare words per row keep the scattered side of the transpose off each
+// other's banks), a tile's seeds, the seeds of four subtiles, and the sizes of
+// the sets of 10 bits by rank.
+constexpr uint32_t kAlphaRow = 68, kAlphaPlane = 16 * kAlphaRow;
+__host__ __device__ inline uint32_t sets10(int d) {
+    uint32_t kf = 0;
+    for (int k = 0; k <= 10 && k <= d; ++k) kf += cbin(10, k);
+    return kf;
+}
+static size_t alpha_lin_lds(int d, uint32_t KS) {
+    const uint32_t kf = sets10(d);
+    return (size_t)4 * kAlphaPlane * 4 + 8 * (size_t)(KS + (d <= 13 ? cbin(13, d) : 0u)) +
+           (size_t)4 * (kf + 8) * 8 + kf;
+}
+
+// Register bit Q exchanged with lane bit 4 (row16) or 5: entries that differ
+// in it trade places between the register pair and the lane pair.
+template <int NR, bool ROW16>
+__device__ __forceinline__ void swap_lane_bit(double *v, int q) {
 #pragma unroll
-        for (int m = 0; m < 5; ++m) {
-            off[m] = k13[min(kp + m, 14)];
-            offu[m] = k13[min(kp + m + 1, 14)];
-            cpt[m] = ctab[m * 256 + pt];
-            cup[m] = cpt[m] + cb[12 * 14 + min(kp + m + 1, 13)];
-        }
-        // every load is issued (clamped to a valid index of zd) before any is
-        // used; seeds of size d come from zd, smaller ones from zs
-        double u[NR];
-#pragma unroll
-        for (int r = 0; r < NR; ++r) {
-            const int m = __builtin_popcount(r);
-            const uint32_t il = (kp + m <= d) ? off[m] + colex4(r) + cpt[m] : 0u;
-            const uint32_t iu = (hb && kp + m + 1 <= d) ? offu[m] + colex4(r) + cup[m] : 0u;
-            v[r] = (kp + m < d ? zs : zd)[il];
-            u[r] = (kp + m + 1 < d ? zs : zd)[iu];
-        }
-#pragma unroll
-        for (int r = 0; r < NR; ++r) {
-            const int m = __builtin_popcount(r);
-            const double lo = (kp + m <= d) ? v[r] : 0.0;
-            const double up = (hb && kp + m + 1 <= d) ? u[r] : 0.0;
-            v[r] = lo + up;
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) lin_zeta_up<NR>(v, q);
-        if (kp <= d) {
-#pragma unroll
-            for (int r = 0; r < NR; ++r) put_w2(tlo_, thi_, pt * 17 + r, v[r]);
-        }
+    for (int r = 0; r < NR; ++r) {
+        if ((r >> q) & 1) continue;
+        const int s = r | (1 << q);
+        const uint32_t al = (uint32_t)__double2loint(v[r]), ah = (uint32_t)__double2hiint(v[r]);
+        const uint32_t bl = (uint32_t)__double2loint(v[s]), bh = (uint32_t)__double2hiint(v[s]);
+        const auto l = ROW16 ? __builtin_amdgcn_permlane16_swap(al, bl, false, false)
+                             : __builtin_amdgcn_permlane32_swap(al, bl, false, false);
+        const auto h = ROW16 ? __builtin_amdgcn_permlane16_swap(ah, bh, false, false)
+                             : __builtin_amdgcn_permlane32_swap(ah, bh, false, false);
+        v[r] = __hiloint2double((int)h[0], (int)l[0]);
+        v[s] = __hiloint2double((int)h[1], (int)l[1]);
     }
-    __syncthreads();
-    // ---- layout B: y = thi * 256 + r * 16 + tlo, tile bits 4..7
+}
+
+// Order of one wave's LDS accesses: they complete in the order of issue, so
+// only the compiler has to keep it.
+__device__ __forceinline__ void wave_lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// Stores of 16 entries per lane, entry r * 64 + lane, z = v[r] in the number
+// system's form. The significands go out as they stand (256 B per wave
+// store); the exponent bytes are transposed through the wave's LDS plane so
+// that a lane stores 16 consecutive ones (1 KB per wave store).
+__device__ __forceinline__ void alpha_store_x32(const PolX32::Store &alpha, uint64_t ub,
+                                                uint32_t lane, uint32_t *pl, const double *v,
+                                                const X32 *qr, int T, unsigned long long *cnt) {
+    constexpr int NR = 16;
+    float *fp = alpha.f + ub;
+    uint8_t *bytes = reinterpret_cast<uint8_t *>(pl);
+    double qf[5];
+    int qb[5];
 #pragma unroll
-    for (int r = 0; r < NR; ++r) v[r] = get_w2(tlo_, thi_, ib + r * 17);
+    for (int m = 0; m < 5; ++m) {
+        qf[m] = (double)qr[m].f;
+        qb[m] = ((T + qr[m].e) >> 6) + kX32Bias;
+    }
+    // fast path: every entry a positive normal double with its byte in 1..255
+    float fq[NR];
+    int bq[NR], bmin = 255, bmax = 1;
+    uint32_t hmin = 0x7fefffffu, hmax = 0x00100000u;
 #pragma unroll
-    for (int r = 0; r < NR; ++r)
-        if (kh + __builtin_popcount(r) > d) v[r] = 0.0;      // slot never written
-#pragma unroll
-    for (int q = 0; q < 4; ++q) lin_zeta_up<NR>(v, q);
-    __syncthreads();
-#pragma unroll
-    for (int r = 0; r < NR; ++r) put_w2(tlo_, thi_, ib + r * 17, v[r]);
-    __syncthreads();
-    // ---- layout C: y = r * 256 + t, tile bits 8..11
-#pragma unroll
-    for (int r = 0; r < NR; ++r) v[r] = get_w2(tlo_, thi_, ic + r * 272);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) lin_zeta_up<NR>(v, q);
-    // ---- alpha = q(|S|) t(S), |S| = h + hb + |t| + |r|
-    V qr[5];
-    const int ht = h + hb + __popc(t);
-#pragma unroll
-    for (int m = 0; m < 5; ++m) qr[m] = sq[min(ht + m, 31)];
-    if constexpr (std::is_same<P, PolX32>::value) {
-        // Significands go out from layout C (256 B per wave store); the
-        // exponent bytes are transposed through LDS so that each thread
-        // stores 16 consecutive bytes (1 KB per wave store): byte stores of
-        // 64 B per wave would cost partial-line reads and writes in L2.
-        const uint64_t ub = base + hb * 4096;
-        float *fp = alpha.f + ub;
-        uint8_t *bytes = reinterpret_cast<uint8_t *>(tlo_);
-        uint32_t nsat = 0, nfl = 0, bq[NR];
-        double qf[5];
-        int qb[5];
-#pragma unroll
-        for (int m = 0; m < 5; ++m) {
-            qf[m] = (double)qr[m].f;
-            qb[m] = ((T + qr[m].e) >> 6) + kX32Bias;
-        }
-        // fast path: every entry positive with its byte in 1..255
-        float fq[NR];
-        bool ok = true;
+    for (int r = 0; r < NR; ++r) {
+        const int m = __builtin_popcount(r);
+        const double z = v[r] * qf[m];
+        int k;
+        const uint32_t hi = (uint32_t)__double2hiint(z);
+        fq[r] = PolX32::lin_encode_normal(z, &k);
+        bq[r] = qb[m] + k;
+        bmin = min(bmin, bq[r]);
+        bmax = max(bmax, bq[r]);
+        hmin = min(hmin, hi);
+        hmax = max(hmax, hi);
+    }
+    if (bmin < 1 || bmax > 255 || hmin < 0x00100000u || hmax > 0x7fefffffu) {
+        uint32_t nsat = 0, nfl = 0;
 #pragma unroll
         for (int r = 0; r < NR; ++r) {
-            const int m = __builtin_popcount(r);
-            const double z = v[r] * qf[m];
+            const double z = v[r] * qf[__builtin_popcount(r)];
             int k;
-            fq[r] = PolX32::lin_encode(z, &k);
-            bq[r] = (uint32_t)(qb[m] + k);
-            ok = ok && z > 0.0 && bq[r] - 1u < 255u;
+            const float f = PolX32::lin_encode(z, &k);
+            const int b = qb[__builtin_popcount(r)] + k;
+            const bool zero = !(z > 0.0);
+            const bool fl = !zero && b < 1;
+            const bool sat = !zero && b > 255;
+            nfl += fl ? 1u : 0u;
+            nsat += sat ? 1u : 0u;
+            fq[r] = (zero || fl) ? 0.0f : (sat ? 4.0e9f : f);
+            bq[r] = (zero || fl) ? 0 : (sat ? 255 : b);
         }
-        if (!ok) {
-#pragma unroll
-            for (int r = 0; r < NR; ++r) {
-                const double z = v[r] * qf[__builtin_popcount(r)];
-                const int b = (int)bq[r];
-                const bool zero = !(z > 0.0);
-                const bool fl = !zero && b < 1;
-                const bool sat = !zero && b > 255;
-                nfl += fl ? 1u : 0u;
-                nsat += sat ? 1u : 0u;
-                fq[r] = (zero || fl) ? 0.0f : (sat ? 4.0e9f : fq[r]);
-                bq[r] = (zero || fl) ? 0u : (sat ? 255u : (uint32_t)b);
-            }
-        }
-#pragma unroll
-        for (int r = 0; r < NR; ++r) fp[(uint32_t)(r * kThreads + t)] = fq[r];
-        __syncthreads();                      // every layout-C read of the planes is done
-#pragma unroll
-        for (int r = 0; r < NR; ++r) bytes[r * kThreads + t] = (uint8_t)bq[r];
-        __syncthreads();
-        reinterpret_cast<uint4 *>(alpha.b + ub)[t] = reinterpret_cast<const uint4 *>(bytes)[t];
         if (cnt && (nsat | nfl)) {
             if (nsat) atomicAdd(cnt, (unsigned long long)nsat);
             if (nfl) atomicAdd(cnt + 1, (unsigned long long)nfl);
         }
-    } else {
-        store_tile_lin<P, NR>(alpha, base + hb * 4096, t, kThreads, v, qr, T, cnt);
     }
-    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < NR; ++r) fp[(uint32_t)r * 64u + lane] = fq[r];
+    wave_lds_order();
+#pragma unroll
+    for (int r = 0; r < NR; ++r) bytes[r * 64 + lane] = (uint8_t)bq[r];
+    wave_lds_order();
+    reinterpret_cast<uint4 *>(alpha.b + ub)[lane] = reinterpret_cast<const uint4 *>(bytes)[lane];
 }
 
 // Linear-tile form of k_alpha. A workgroup takes 2^tl consecutive tiles (i, H)
-// of one node in turn, each the same 13-bit tile as k_alpha's, run
-// as two 12-bit halves x = hb * 4096 + y through one half-size LDS buffer,
-// which lets four workgroups share a CU. The zeta step over tile bit 12 is
-// taken first: the upper half starts from its seeds plus the lower half's.
-// The seeds come from k_alpha_seeds, already as
-// doubles under the node's scale (k_prep_lin), and the upward zeta runs on
-// doubles, one FP64 add per step, in three layouts of a half (256 threads x
-// 16 entries): A, y = pattern * 16 + r (bits 0..3 in registers; patterns of
-// bits 4..11 by popcount, so waves holding only structural zeros skip it),
-// seeds read straight from Zs; B, y = thi * 256 + r * 16 + tlo (bits 4..7),
-// which skips slots that still hold structural zeros, so the LDS buffer never
-// needs clearing; C, y = r * 256 + t (bits 8..11), stored from there. Tiles
-// of nodes without a linear scale go to the fallback list for k_alpha_fb;
-// force_fb sends every tile there (tests).
-// Four workgroups per CU (LDS allows it): registers are capped to match.
+// of one node in turn, each the same 13-bit tile as k_alpha's. The seeds come
+// from k_alpha_seeds, already as doubles under the node's scale, and the upward
+// zeta runs on doubles, one FP64 add per step. What bounds a tile is latency:
+// stores, LDS and vector unit are each busy for about half of its time, so the
+// split keeps the waves apart. A tile's seeds of fewer than d bits are few
+// (92 at d = 3) and are read a tile ahead; those of d bits stay in LDS for all
+// the tiles of the node. The three steps over the top bits are taken on the
+// seeds, one G_L of the ten low bits per thread, four subtiles at a time (eight
+// would leave room for two workgroups per CU at d = 4 instead of three); each
+// wave then runs the other ten bits of its own subtile without a barrier:
+//   seeds read from LDS, y = p * 16 + r, steps 0..3 (patterns of more than d
+//   bits read zeros);
+//   register bits 0, 1 traded for lane bits 4, 5 (tile bits 4, 5): steps 4, 5;
+//   one transpose through the wave's LDS plane, low words and then high words,
+//   to y = r * 64 + lane: steps 6..9, stored from there.
+// Two 12-bit halves in three layouts, transposed twice across the workgroup
+// with seven barriers a half, took 22.6 ms at n = 30, d = 3 (FP32-scaled, 80.5
+// GB written), 0.79 and 1.12 ms at n = 25, d = 4 (FP32-scaled, FP64); this takes
+// 18.8, 0.58 and 0.81. Seeds summed by each wave for itself (one barrier a tile)
+// took 19.0 and 0.66; significands stored as they are made instead of in one
+// run 20.4; five waves per SIMD spill (FP32-scaled 25 to 30).
 template <class P>
 __device__ __forceinline__ void alpha_lin_tiles(
     int n, int d, uint32_t KS, int tl, const double *__restrict__ Zs,
@@ -1251,61 +1187,163 @@ __device__ __forceinline__ void alpha_lin_tiles(
     using A = typename P::Anchor;
     constexpr int bA = 13, NR = 16;
     extern __shared__ unsigned char smem[];
-    // a half's doubles as two planes of 32-bit words (pad16 indices)
-    uint32_t *tlo_ = reinterpret_cast<uint32_t *>(smem);
-    uint32_t *thi_ = tlo_ + 4096 + 256;
     __shared__ V sq[32];
-    __shared__ uint8_t ord8[256];
-    __shared__ uint16_t cb[14 * 14];      // C(a, b), a, b <= 13
-    __shared__ uint32_t k13[15];          // K(13, k - 1) = sum_{j < k} C(13, j)
-    // ctab[m * 256 + p]: colex terms of the 8-bit pattern p at tile bits
-    // 4..11 with m ones below it (kept in LDS rather than in registers
-    // across the tile loop)
-    __shared__ uint16_t ctab[5 * 256];
+    __shared__ uint32_t k10[12], k13[15]; // sets of fewer than k of 10 (13) bits
+    // rank of G_L + the top bits of T (a value of three bits) is
+    // seedix[T * 11 + |G_L|] + the rank of G_L among the sets of 10 bits
+    __shared__ uint32_t seedix[8 * 11];
     const int N = n - 1;
     const int hA = N - bA;
     const uint32_t tile0 = blockIdx.x << tl;   // 2^tl consecutive tiles of one node
     const int i = tile0 >> hA;
-    const int t = threadIdx.x;
+    const uint32_t t = threadIdx.x, lane = t & 63u, wave = t >> 6;
     const A T = anc[i];
-    if (t < n) sq[t] = qt[t];
-    if (t < 14 * 14) cb[t] = (uint16_t)cbin(t / 14, t % 14);
-    if (t < 15) {
+    const int dd = min(d, 10);
+    const uint32_t KF = sets10(dd), FS = KF + 8;   // eight zeros end a row
+    const uint32_t nd = d <= 13 ? cbin(13, d) : 0u;
+    uint32_t *pl = reinterpret_cast<uint32_t *>(smem) + wave * kAlphaPlane;
+    double *S = reinterpret_cast<double *>(smem + 4 * kAlphaPlane * 4);
+    double *F = S + KS + nd;
+    uint8_t *size10 = reinterpret_cast<uint8_t *>(F + 4 * FS);
+    // the seeds of fewer than d bits, two per thread read a tile ahead
+    const double *zs = Zs + (size_t)tile0 * KS;
+    double z0 = t < KS ? zs[t] : 0.0, z1 = t + kThreads < KS ? zs[t + kThreads] : 0.0;
+    uint16_t *cb = reinterpret_cast<uint16_t *>(smem);   // C(a, b), a, b <= 13: set-up only
+    if (t < 14 * 14) cb[t] = (uint16_t)cbin((int)t / 14, (int)t % 14);
+    if (t >= 256 - 32) sq[t - (256 - 32)] = qt[min(t - (256 - 32), (uint32_t)n - 1u)];
+    // those of d bits, betal_i(G_L) itself, are the same for every tile of the node
+    {
+        const double *zd = betal + (size_t)i * K + offd;
+        for (uint32_t x = t; x < nd; x += kThreads) S[KS + x] = zd[x];
+    }
+    __syncthreads();
+    if (t < 12) {
         uint32_t o = 0;
-        for (int j = 0; j < t; ++j) o += cbin(13, j);
-        k13[t] = o;
+        for (uint32_t j = 0; j < t && j <= 10; ++j) o += cb[10 * 14 + j];
+        k10[t] = o;
+    } else if (t >= 64 && t < 64 + 15) {
+        uint32_t o = 0;
+        for (uint32_t j = 0; j < t - 64; ++j) o += cb[13 * 14 + j];
+        k13[t - 64] = o;
     }
     __syncthreads();
-    {   // ord8: 8-bit patterns by popcount (then value)
-        const int k = __popc(t);
-        uint32_t r = 0;
-        for (int j = 0; j < k; ++j) r += cb[8 * 14 + j];
-        int j = 0;
-        for (int p = 0; p < 8; ++p)
-            if ((t >> p) & 1) r += cb[p * 14 + (++j)];
-        ord8[r] = (uint8_t)t;
+    if (t < 8 * 11) {
+        const uint32_t T3 = t / 11;
+        const int k = (int)(t % 11);
+        uint32_t r = k13[k + __popc(T3)];
+        int j = k;
+        for (int p = 0; p < 3; ++p)
+            if ((T3 >> p) & 1) r += cb[(10 + p) * 14 + (++j)];
+        seedix[t] = r - k10[k];
     }
+    for (uint32_t g = t; g < KF; g += kThreads) {
+        uint32_t k = 0;
+        for (int j = 1; j <= 10; ++j) k += g >= k10[j] ? 1u : 0u;
+        size10[g] = (uint8_t)k;
+    }
+    if (t < 32) F[(t >> 3) * FS + KF + (t & 7)] = 0.0;
+    // layout A: entries p * 16 + r; p's low bits on lane bits 4, 5
+    uint32_t off[5];
+    {
+        const uint32_t p = ((lane & 15u) << 2) | (lane >> 4);
+        const int kp = __popc(p);
+        uint32_t c[5] = {};
+        for (int b = 0, j = 0; b < 6; ++b)
+            if ((p >> b) & 1) {
+                ++j;
 #pragma unroll
-    for (int m = 0; m < 5; ++m) {
-        uint32_t c = 0;
-        int j = m;
-        for (int p = 0; p < 8; ++p)
-            if ((t >> p) & 1) c += cb[(4 + p) * 14 + (++j)];
-        ctab[m * 256 + t] = (uint16_t)c;
+                for (int m = 0; m < 5; ++m) c[m] += cb[(4 + b) * 14 + m + j];
+            }
+#pragma unroll
+        for (int m = 0; m < 5; ++m)
+            off[m] = wave * FS + (kp + m <= dd ? k10[kp + m] + c[m] : KF);
     }
+    const uint32_t iw = (lane & 15u) * kAlphaRow + (lane >> 4);
+    auto put_seeds = [&]() {
+        if (t < KS) S[t] = z0;
+        if (t + kThreads < KS) S[t + kThreads] = z1;
+        for (uint32_t x = t + 2 * kThreads; x < KS; x += kThreads) S[x] = zs[x];
+    };
+    put_seeds();
     __syncthreads();
-    // size-d seeds: betal_i(G_L) at rank offd + colex(G_L), offd = K(N, d - 1);
-    // indexed like zs (k13[d] + colex), so the base is shifted by k13[d]
-    const double *zd = betal + (size_t)i * K + offd - k13[min(d, 14)];
-    const uint32_t pt = ord8[t];
-    for (int j = 0; j < (1 << tl); ++j) {
-        const uint32_t tile = tile0 + j;
-        const uint32_t H = tile & ((1u << hA) - 1);
-        const int h = __popc(H);
-        const double *zs = Zs + (size_t)tile * KS;
+    const uint32_t last = (1u << tl) - 1u;
+    for (uint32_t jt = 0; jt <= last; ++jt) {
+        const uint32_t H = (tile0 + jt) & ((1u << hA) - 1);
         const uint64_t base = ((uint64_t)i << N) | ((uint64_t)H << bA);
-        alpha_lin_half<P, 0>(d, zs, zd, sq, ctab, cb, k13, tlo_, thi_, pt, h, base, T, alpha, cnt);
-        alpha_lin_half<P, 1>(d, zs, zd, sq, ctab, cb, k13, tlo_, thi_, pt, h, base, T, alpha, cnt);
+        if (jt < last) {
+            zs += KS;
+            if (t < KS) z0 = zs[t];
+            if (t + kThreads < KS) z1 = zs[t + kThreads];
+        }
+#pragma unroll 1
+        for (uint32_t hb = 0; hb < 2; ++hb) {
+            // ---- seeds of the subtiles 4 hb .. 4 hb + 3 after the steps over
+            //      tile bits 10..12
+            for (uint32_t g = t; g < KF; g += kThreads) {
+                const int k = size10[g];
+                auto seed = [&](uint32_t T3) {
+                    return k + __popc(T3) <= d ? S[seedix[T3 * 11 + k] + g] : 0.0;
+                };
+                double w[4];
+#pragma unroll
+                for (uint32_t q = 0; q < 4; ++q) w[q] = seed(q);
+                if (hb) {
+                    double x[4];
+#pragma unroll
+                    for (uint32_t q = 0; q < 4; ++q) x[q] = seed(q + 4);
+#pragma unroll
+                    for (uint32_t q = 0; q < 4; ++q) w[q] += x[q];
+                }
+                w[1] += w[0];
+                w[3] += w[2];
+                w[2] += w[0];
+                w[3] += w[1];
+#pragma unroll
+                for (uint32_t q = 0; q < 4; ++q) F[q * FS + g] = w[q];
+            }
+            __syncthreads();
+            double v[NR];
+#pragma unroll
+            for (int r = 0; r < NR; ++r) v[r] = F[off[__builtin_popcount(r)] + colex4(r)];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) lin_zeta_up<NR>(v, q);
+            swap_lane_bit<NR, true>(v, 0);
+            swap_lane_bit<NR, false>(v, 1);
+#pragma unroll
+            for (int q = 0; q < 2; ++q) lin_zeta_up<NR>(v, q);
+            // entry of register r: tile bits 2, 3 are r's high bits, 4, 5 its low
+            uint32_t lo[NR], hi[NR];
+            wave_lds_order();
+#pragma unroll
+            for (int r = 0; r < NR; ++r)
+                pl[iw + (uint32_t)((r >> 2) << 2 | (r & 3) << 4)] = (uint32_t)__double2loint(v[r]);
+            wave_lds_order();
+#pragma unroll
+            for (int r = 0; r < NR; ++r) lo[r] = pl[lane + kAlphaRow * (uint32_t)r];
+            wave_lds_order();
+#pragma unroll
+            for (int r = 0; r < NR; ++r)
+                pl[iw + (uint32_t)((r >> 2) << 2 | (r & 3) << 4)] = (uint32_t)__double2hiint(v[r]);
+            wave_lds_order();
+#pragma unroll
+            for (int r = 0; r < NR; ++r) hi[r] = pl[lane + kAlphaRow * (uint32_t)r];
+#pragma unroll
+            for (int r = 0; r < NR; ++r) v[r] = __hiloint2double((int)hi[r], (int)lo[r]);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) lin_zeta_up<NR>(v, q);
+            // ---- alpha = q(|S|) t(S)
+            V qr[5];
+            const int ht = __popc(H) + (int)hb + __popc(wave) + __popc(lane);
+#pragma unroll
+            for (int m = 0; m < 5; ++m) qr[m] = sq[min(ht + m, 31)];
+            const uint64_t ub = base + hb * 4096u + wave * 1024u;
+            if constexpr (std::is_same<P, PolX32>::value)
+                alpha_store_x32(alpha, ub, lane, pl, v, qr, T, cnt);
+            else
+                store_tile_lin<P, NR>(alpha, ub, lane, 64u, v, qr, T, cnt);
+            if (hb && jt < last) put_seeds();
+            __syncthreads();
+        }
     }
 }
 
@@ -3854,11 +3892,11 @@ hipError_t launch_lattice(const LatticeArgs &a, const typename P::Store &alpha,
                                    (const int *)a.linok, a.Zs);
             }
             BN_CHECK_LAUNCH();
-            const size_t smL = 8 * (4096 + 256);
+            const size_t smL = alpha_lin_lds(d, a.KS);
             allow_big_lds<k_alpha_lin<P>>();
             rec(8);
-            // 2^tl tiles per workgroup share its set-up (tables in LDS, the
-            // colex terms of the thread's pattern)
+            // 2^tl tiles per workgroup share its set-up (tables and size-d
+            // seeds in LDS)
             // (tl < hA keeps the shift count nonnegative: at n = 14 there
             // is a single tile per node and tl stays 0)
             if (n < 20) {
