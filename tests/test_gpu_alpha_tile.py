@@ -14,7 +14,7 @@ from paper_1408_1664_amd import datagen
 @pytest.mark.gpu
 @pytest.mark.parametrize("precision,tol", [("fp64", 2e-10), ("fp32", 2e-5)])
 @pytest.mark.parametrize("n,d", [(14, 1), (14, 3), (14, 5), (14, 10), (14, 11), (14, 13),
-                                 (15, 4), (16, 6), (20, 2), (21, 4)])
+                                 (15, 4), (16, 6), (20, 2), (20, 6), (21, 4)])
 def test_alpha_tile_equals_number_system(n, d, precision, tol, monkeypatch):
     ds = datagen.random_dag_dataset(n, 120, 2, 3, 1.0, seed=90 + n)
     print(f"alpha tile n={n} d={d} {precision}", flush=True)
