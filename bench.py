@@ -331,17 +331,18 @@ def subset_bench(bn, torch, datagen, nbits=30, steps=5):
                 tot += e0.elapsed_time(e1)
         return tot / steps
 
-    def entry(ms, per_entry):
+    def entry(ms, per_entry, d=-1):
+        # moved: dense passes; a truncated transform skips rows without inputs
         alg = per_entry * (1 << nbits)
         return dict(ms=ms, algorithmic_bytes=alg, GB_s=alg / (ms * 1e-3) / 1e9,
                     frac=alg / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS,
-                    moved_GB_s=passes * alg / (ms * 1e-3) / 1e9)
+                    moved_GB_s=passes * alg / (ms * 1e-3) / 1e9 if d < 0 else None)
 
     base = torch.from_numpy(datagen.subset_values(nbits, 30, "uniform")).cuda()
     xt = torch.empty_like(base)
     for kind, d in [("zeta_up", -1), ("zeta_up", 3), ("zeta_down", -1), ("mobius_up", -1)]:
         ms = timed(lambda: bn.subset_transform(xt, kind, d), lambda: xt.copy_(base))
-        out["fp64"][f"{kind}" + (f"_d{d}" if d >= 0 else "")] = entry(ms, 16)
+        out["fp64"][f"{kind}" + (f"_d{d}" if d >= 0 else "")] = entry(ms, 16, d)
     del base, xt
     torch.cuda.empty_cache()
     f = torch.empty(1 << nbits, dtype=torch.float32, device="cuda")
@@ -352,7 +353,7 @@ def subset_bench(bn, torch, datagen, nbits=30, steps=5):
         b.fill_(200)
     for kind, d in [("zeta_up", -1), ("zeta_up", 3), ("zeta_down", -1)]:
         ms = timed(lambda: bn.subset_transform_x32(f, b, kind, d), restore_x32)
-        out["x32"][f"{kind}" + (f"_d{d}" if d >= 0 else "")] = entry(ms, 10)
+        out["x32"][f"{kind}" + (f"_d{d}" if d >= 0 else "")] = entry(ms, 10, d)
     del f, b
     torch.cuda.empty_cache()
     return out

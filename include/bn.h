@@ -227,9 +227,11 @@ bn_status bn_edge_posteriors_noalloc(const bn_problem *p, bn_precision prec, voi
  * bn_timer_read, valid once that stream has been synchronised, returns the
  * milliseconds of the last solve that used the timer:
  *   ms[0] parameters, tables, local scores and prior/gauges (Eq. 6)
- *   ms[1] alpha, truncated upward zeta (Eq. 7, Alg. 2): one kernel launch
- *   ms[2] forward sweep, all layers (Eq. 9)
- *   ms[3] backward sweep, all layers (Eq. 10)
+ *   ms[1] alpha, truncated upward zeta (Eq. 7, Alg. 2): seeds and tiles
+ *   ms[2] both sweeps, all layers (Eqs. 9 and 10); of separate sweeps (alpha
+ *         never materialised) the forward one
+ *   ms[3] what of the backward sweep outlasts the forward one; of separate
+ *         sweeps the backward one
  *   ms[4] Gamma: product and truncated downward zeta (Eq. 12, Alg. 3)
  *   ms[5] edge sums, invariants and diagnostics (Eq. 11)
  *   ms[6] total
