@@ -3911,7 +3911,12 @@ hipError_t launch_lattice(const LatticeArgs &a, const typename P::Store &alpha,
                 rec(9);
             } else {
                 int tl = 0;
-                const unsigned least = nblkA < 16384u ? 1024u : 4096u;
+                // as many as leave the grid two full rounds of the 1024
+                // workgroups that run together, or four where there are many
+                // tiles (n >= 24): at n = 22 and 23 1024, 2048 and 4096
+                // workgroups at least take 84, 77 and 89, and 151, 143 and 151
+                // us, at n = 25 639, 595 and 587 (8192: 621)
+                const unsigned least = nblkA < 16384u ? 2048u : 4096u;
                 while (tl < 6 && tl < hA && ((uint64_t)n << (hA - tl - 1)) >= least) ++tl;
                 hipLaunchKernelGGL(HIP_KERNEL_NAME(k_alpha_lin<P>), dim3(nblkA >> tl), dim3(kThreads), smL,
                                    st, n, d, a.KS, a.lin_mode == 2 ? 1 : 0, tl, (const double *)a.Zs,
