@@ -18,7 +18,7 @@
 //                      register layouts joined through LDS;
 //   k_subset_bits<B>   a remainder of B <= 4 bits (nbits 13..16), entirely
 //                      in registers.
-// nbits <= 12: one workgroup in LDS (k_subset_small).
+// nbits < 12: one workgroup in LDS (k_subset_small); nbits = 12: one tile.
 //
 // An upward transform truncated to |S| <= d only has inputs with at most d
 // ones. A row of entries that agree in the bits not yet summed (those of the
@@ -229,19 +229,24 @@ void launch_group(int B, int nbits, F x, int j0, double sign, int trunc_d, hipSt
     }
 }
 
-// nbits <= 12: the whole array in LDS, one step per bit.
+// nbits < 12: the whole array in LDS, one step per bit, one pair of entries per
+// thread and turn. Bound by LDS latency and the barriers of its steps. Calls
+// back to back took 10.1 us at 11 bits with every entry visited in each step,
+// and 12 bits 19.5 us that way; 7.0 and (as one register tile) 7.2 now, the
+// rate at which the host enqueues them.
 template <class F, bool UP>
 __global__ void __launch_bounds__(kT)
 k_subset_small(F x, int nbits, double sign, int trunc_d) {
-    __shared__ typename F::V s[4096];
+    __shared__ typename F::V s[2048];
     const uint32_t N = 1u << nbits;
     for (uint32_t i = threadIdx.x; i < N; i += kT)
         s[i] = (trunc_d >= 0 && __popc(i) > trunc_d) ? F::zero() : x.load(i);
     __syncthreads();
     for (int j = 0; j < nbits; ++j) {
-        for (uint32_t i = threadIdx.x; i < N; i += kT) {
-            if (UP && ((i >> j) & 1)) s[i] = F::step(s[i], s[i ^ (1u << j)], sign);
-            if (!UP && !((i >> j) & 1)) s[i] = F::step(s[i], s[i | (1u << j)], sign);
+        for (uint32_t p = threadIdx.x; p < N / 2; p += kT) {
+            const uint32_t lo = (p >> j) << (j + 1) | (p & ((1u << j) - 1u)), hi = lo | 1u << j;
+            if (UP) s[hi] = F::step(s[hi], s[lo], sign);
+            else s[lo] = F::step(s[lo], s[hi], sign);
         }
         __syncthreads();
     }
@@ -250,7 +255,7 @@ k_subset_small(F x, int nbits, double sign, int trunc_d) {
 
 template <class F, bool UP>
 hipError_t run(F x, int nbits, double sign, int trunc_d, hipStream_t st) {
-    if (nbits <= 12) {
+    if (nbits < 12) {
         hipLaunchKernelGGL((k_subset_small<F, UP>), dim3(1), dim3(kT), 0, st, x, nbits, sign,
                            trunc_d);
         return hipGetLastError();
