@@ -1997,20 +1997,19 @@ k_gamma_tile(int n, int d, GammaGeom gg, Tables tb, typename P::Store L, typenam
     gamma_tile<P>(n, d, gg, tb, L, R, qt, Y1, part, H);
 }
 
-// Recomputation in the number system proper of the listed work (list[0]
-// entries, list[1 + j] = H * 64 + e: tile H, every endpoint for e = 0, else
-// endpoint e - 1 alone): the grid walks the list.
+// Recomputation of the listed tiles in the number system proper (list[0]
+// entries, at most ntiles; list[1 + j] = H): the grid walks the list. Only the
+// forced fallback runs it, whose list k_gamma_tile_lin alone writes.
 template <class P>
 __global__ void __launch_bounds__(kThreads)
 k_gamma_tile_fb(int n, int d, GammaGeom gg, Tables tb, typename P::Store L,
                 typename P::Store R, const typename P::V *__restrict__ qt,
                 typename P::V *__restrict__ Y1, typename P::V *__restrict__ part,
-                const uint32_t *list) {
-    const uint32_t ntile = list[0];
-    for (uint32_t it = blockIdx.x; it < ntile; it += gridDim.x) {
+                const uint32_t *list, uint32_t ntiles) {
+    const uint32_t nlist = min(list[0], ntiles);
+    for (uint32_t it = blockIdx.x; it < nlist; it += gridDim.x) {
         __syncthreads();
-        const uint32_t item = list[1 + it];
-        gamma_tile<P>(n, d, gg, tb, L, R, qt, Y1, part, item >> 6, (int)(item & 63) - 1);
+        gamma_tile<P>(n, d, gg, tb, L, R, qt, Y1, part, list[1 + it]);
     }
 }
 
@@ -2034,9 +2033,10 @@ __device__ inline void lin_zeta_down(double *g, int q) {
 // 2^-24 rounding of its stored significand, and 2^-64 in the log form. If
 // Gamma_v(H + empty), the largest entry, overflows after
 // the scaling, or g_v(H + top) is zero, the endpoint's outputs are not stored
-// and (H, v) goes to the list of k_gamma_tile_retry. force_fb sends every
-// tile to the fallback list of k_gamma_tile_fb, which recomputes all of its
-// endpoints (tests).
+// and (H, v) goes to the list of k_gamma_tile_retry. force_fb (tests) sends
+// every tile to the list of k_gamma_tile_fb instead, which recomputes all of
+// its endpoints; the retry list then stays empty, since k_gamma_tile_retry
+// counts the endpoints that it recomputes in fb[0], the length of that list.
 // Layouts (x the 12 tile bits, 256 threads x 16 entries):
 //   A  x = t * 16 + r      bits 0..3 in registers; products formed here. Each
 //      thread owns 16 consecutive masks, so L, Rp and the partners Rp(x + v)
@@ -2237,7 +2237,7 @@ gamma_tile_lin_body(int n, int d, int force_fb, int vsplit, GammaGeom gg, Tables
         // Gamma_v(H + empty) bounds every entry of the tile.
         const bool fine = okv && gb[padx(0)] <= 1.0e300;
         if (!fine) {
-            if (t == 0) fb_push(rt, (H << 5) | (uint32_t)v);   // k_gamma_tile_retry
+            if (t == 0 && !force_fb) fb_push(rt, (H << 5) | (uint32_t)v);
         } else {
             const int hv = gg.hv[v];
             const uint32_t Hc = low ? H : (uint32_t)compress_bit(H, v - bT);
@@ -2275,7 +2275,7 @@ gamma_tile_lin_body(int n, int d, int force_fb, int vsplit, GammaGeom gg, Tables
         for (int v = 4; v < bT && v < n; ++v) endpoint(v);
         for (int v = bT; v < n; ++v) endpoint(v);
     }
-    if (t == 0 && sfail) fb_push(fb, H << 6);             // every endpoint
+    if (t == 0 && sfail) fb_push(fb, H);
 }
 
 // Three waves per SIMD (168 registers, some spill), which measured faster
@@ -2461,7 +2461,8 @@ k_gamma_tile_retry(int n, int d, GammaGeom gg, Tables tb, typename P::Store L,
             }
             if (!ok) {
                 // this endpoint in the number system proper (same LDS layout: the
-                // tables in LDS are written again with the same values)
+                // tables in LDS are written again with the same values); fb[0] is
+                // only a count here, no list
                 if (t == 0) atomicAdd(fb, 1u);
                 __syncthreads();
                 gamma_tile<P>(n, d, gg, tb, L, R, qt, Y1, part, H, v);
@@ -4074,7 +4075,7 @@ static hipError_t launch_gamma_edges(const LatticeArgs &a, const typename P::Sto
                     hipLaunchKernelGGL(HIP_KERNEL_NAME(k_gamma_tile_fb<P>),
                                        dim3(std::min(nblkG, 1024u)), dim3(kThreads), sm, st, n, d,
                                        gg, tb, L, R, (const V *)qt, Y1, part,
-                                       (const uint32_t *)a.fbG);
+                                       (const uint32_t *)a.fbG, nblkG);
                 }
             } else {
                 hipLaunchKernelGGL(HIP_KERNEL_NAME(k_gamma_tile<P>), dim3(nblkG), dim3(kThreads),

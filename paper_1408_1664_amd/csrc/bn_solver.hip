@@ -261,9 +261,9 @@ static Plan plan_of(int n, int d_in, int m, bn_precision prec, bool with_data, b
     P.o_anc = take(32 * 8);
     P.o_linok = take(32 * 4);
     // Gamma lists: endpoints for a second scale (at most one entry per tile and
-    // endpoint), tiles for the fallback (one per failed second chance, and one
-    // per tile when every tile is forced there)
-    P.o_fbG = P.bG == 12 ? take(4 * (1 + ((size_t)(n + 1) << (n - 12)))) : 0;
+    // endpoint); the fallback count, and one entry per tile when every tile is
+    // forced there
+    P.o_fbG = P.bG == 12 ? take(4 * (1 + ((size_t)1 << (n - 12)))) : 0;
     P.o_rtG = P.bG == 12 ? take(4 * (1 + ((size_t)n << (n - 12)))) : 0;
     if (with_post) P.o_post = take(((size_t)n * n + 8) * 8);   // and the diagnostics
     if (with_post) P.o_ps = take((size_t)n * P.K * 8);
