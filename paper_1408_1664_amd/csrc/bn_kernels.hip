@@ -2898,7 +2898,10 @@ k_gamma_small(int n, uint32_t K, int force_log, Tables tb, typename P::Store L,
 // are FP64 adds; the outputs are kept only if every needed one is at least
 // 2^-1000 (the values that fell below 2^-1074, at most 4096, then change none
 // by more than 2^-62 of itself); otherwise, or with force_log (tests), the
-// workgroup runs the zeta in log-adds. One row per workgroup, truncated by
+// workgroup runs the zeta in log-adds. So does one with an entry beyond 3.6e8
+// nats (many millions of samples, or a prior of that size), whose binary
+// exponent the 32-bit row maxima do not hold beside their mark of an empty row.
+// One row per workgroup, truncated by
 // pattern lists and, in the log form, in log-adds, this was 98 us at n = 20
 // (FP64, d = 4), 1.04 ms at n = 25 and 48 us at n = 22 (FP32-scaled, d = 3);
 // now 41 us, 0.28 ms and 24 us.
@@ -2951,7 +2954,7 @@ k_gamma_high1(int n, int d, uint32_t K, int force_log, GammaGeom gg, Tables tb,
         seed_of(bn, bv, s0 + x, &sigma, &cl);
         rowinfo[x] = cl | ((uint32_t)sigma << 27);
     }
-    bool lin = false;
+    bool lin = false, far = false;
     if constexpr (kLog) {
         if (!force_log) {
             lin = true;
@@ -2961,8 +2964,11 @@ k_gamma_high1(int n, int d, uint32_t K, int force_log, GammaGeom gg, Tables tb,
             // share a row, by the wave, then one LDS maximum per row and wave
             int e[16];
 #pragma unroll
-            for (int r = 0; r < 16; ++r)
-                e[r] = (int)ceil(fmax(g[r], -7e8) * 1.4426950408889634074);
+            for (int r = 0; r < 16; ++r) {
+                const bool held = g[r] > -1e300;
+                far = far || (held && fabs(g[r]) > 3.6e8);
+                e[r] = held ? (int)ceil(fmax(g[r], -3.6e8) * 1.4426950408889634074) : -(1 << 30);
+            }
 #pragma unroll
             for (int q = 0; q < 4; ++q)
                 if ((bits >> (8 + q)) & 1) {
@@ -3009,7 +3015,7 @@ k_gamma_high1(int n, int d, uint32_t K, int force_log, GammaGeom gg, Tables tb,
     if constexpr (kLog) {
         if (lin) {
             masked_zeta_down12<Lin64>(g, vec, bits, t);
-            bool small = false;
+            bool small = far;
             outputs([&](uint32_t x, uint32_t, uint32_t) {
                 const double z = vec[padx(x)];
                 // an empty row is zero throughout
