@@ -17,65 +17,12 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "bn_math.h"
+
 namespace bnk {
 
 constexpr int kX32Bias = 200;
 constexpr int kEZero = -(1 << 26);   // exponent carried by an exact zero
-
-// e^x (0 below -1100 and for -inf, +inf where it overflows; no NaN): x = k ln 2
-// + r with |r| <= ln 2 / 2, then the near-minimax polynomial of degree 11 of e^r
-// (Chebyshev interpolation; relative error below 2^-56 before rounding) times
-// 2^k. The log form spends most of its time here: with it in place of the
-// library's exp its Gamma tile takes 2.04 and with log_pos its alpha tile 1.14 ms at
-// n = 25 (kernel trace), where they took 2.30 and 1.59.
-__device__ inline double exp_fast(double x) {
-    x = fmin(fmax(x, -1100.0), 1100.0);
-    const double k = rint(x * 1.4426950408889634074);
-    double r = fma(k, -6.93147180369123816490e-01, x);
-    r = fma(k, -1.90821492927058770002e-10, r);
-    double p = 2.5110049204818658e-08;
-    p = fma(p, r, 2.763265472252779e-07);
-    p = fma(p, r, 2.755724088722987e-06);
-    p = fma(p, r, 2.4801485441561313e-05);
-    p = fma(p, r, 0.00019841269890076403);
-    p = fma(p, r, 0.0013888888952352863);
-    p = fma(p, r, 0.008333333333319589);
-    p = fma(p, r, 0.04166666666648795);
-    p = fma(p, r, 0.1666666666666668);
-    p = fma(p, r, 0.5000000000000019);
-    p = fma(p, r, 1.0);
-    p = fma(p, r, 1.0);
-    return ldexp(p, (int)k);
-}
-
-// the same for x <= 0
-__device__ inline double exp_neg(double x) { return exp_fast(x); }
-
-// ln y for a positive finite y, to about 2^-53 of max(1, |ln y|): y = 2^e m with
-// m in [1/2, 1), s = (m - c) / (m + c) with c = sqrt(1/2), |s| <= 0.172, and
-// ln y = e ln 2 + ln c + 2 atanh s; atanh(s) / s is the Chebyshev interpolant
-// of degree 7 in s^2 (relative error below 2^-58).
-__device__ inline double log_pos(double y) {
-    constexpr double c = 0.7071067811865476;
-    const double m = __builtin_amdgcn_frexp_mant(y);
-    const double e = (double)__builtin_amdgcn_frexp_exp(y);
-    const double num = m - c, den = m + c;
-    double r = __builtin_amdgcn_rcp(den);
-    r = fma(fma(-den, r, 1.0), r, r);
-    r = fma(fma(-den, r, 1.0), r, r);
-    double s = num * r;
-    s = fma(fma(-den, s, num), r, s);
-    const double z = s * s;
-    double p = 0.14809867572313062;
-    p = fma(p, z, 0.15312513114738296);
-    p = fma(p, z, 0.18183632241617026);
-    p = fma(p, z, 0.22222197046404274);
-    p = fma(p, z, 0.2857142876073828);
-    p = fma(p, z, 0.3999999999930191);
-    p = fma(p, z, 0.6666666666666765);
-    p = fma(p, z, 2.0);
-    return fma(e, 0.69314718055994530942, fma(s, p, -0.3465735902799726));
-}
 
 // ---------------------------------------------------------------- FP64 log
 struct PolLog {
@@ -90,12 +37,12 @@ struct PolLog {
     __device__ static inline V add(V a, V b) {
         V hi = fmax(a, b), lo = fmin(a, b);
         if (lo == -__builtin_huge_val()) return hi;
-        return hi + log_pos(1.0 + exp_neg(lo - hi));
+        return hi + log1p_unit(exp_neg(lo - hi));
     }
     __device__ static inline V mul_raw(V a, V b) { return a + b; }
     __device__ static inline V norm_v(V a) { return a; }
     // Running sum of many terms: s * e^m, rescaled when a larger term comes
-    // in. One exp per term (add() takes an exp and a log); the log is
+    // in. One exp per term (add() takes an exp and a log1p); the log is
     // taken once, by acc_value.
     struct Acc {
         double m, s;
@@ -245,7 +192,7 @@ struct PolLog {
         return true;
     }
     __device__ static inline double to_lin(V x, Anchor T) {
-        return x > -1e300 ? exp_fast(x - T) : 0.0;
+        return x > -1e300 ? exp_scaled(x - T, 0) : 0.0;
     }
     // a scale that puts the value 2^e2 at 2^940 (room for 4096 such terms)
     __device__ static inline Anchor anchor_high(int e2) {
@@ -253,12 +200,12 @@ struct PolLog {
     }
     __device__ static inline double prod_lin(V a, V b, V c, Anchor T) {
         const double s = a + b + c;
-        return s > -1e300 ? exp_fast(s - T) : 0.0;
+        return s > -1e300 ? exp_scaled(s - T, 0) : 0.0;
     }
     // prod_lin with the first two factors already multiplied (mul_raw)
     __device__ static inline double prod2_lin(V ab, V c, Anchor T) {
         const double s = ab + c;
-        return s > -1e300 ? exp_fast(s - T) : 0.0;
+        return s > -1e300 ? exp_scaled(s - T, 0) : 0.0;
     }
     __device__ static inline V from_lin(double y, Anchor T) {
         return y > 0.0 ? log_pos(y) + T : zero();
