@@ -181,34 +181,39 @@ struct PolLog {
         return (k & 1) ? r.p[k >> 1].y : r.p[k >> 1].x;
     }
     __device__ static inline V at16_nz(const Raw16 &r, int k) { return at16(r, k); }
-    // Linear tiles: a value x is held as the plain double x * 2^-T (T a
-    // natural-log offset here) so that a zeta over the tile costs one FP64
-    // add per step. anchor_of places the reference value a at 2^-1000,
-    // leaving about 2,000 binary orders of headroom above it.
-    using Anchor = double;
+    // Linear tiles: a value x is held as the plain double e^(x - off) 2^sh, so
+    // that a zeta over the tile costs one FP64 add per step. The two parts of the
+    // scale stay apart: the power of two is exact both ways, and x - off is small
+    // for the values near off, so that they come back with the rounding errors of
+    // small logarithms (with one offset of off - sh ln 2 every value took one of
+    // size 2^-44). anchor_of places the reference value a at 2^-1000, leaving
+    // about 2,000 binary orders of headroom above it.
+    struct Anchor {
+        double off;
+        int sh;
+    };
     __device__ static inline bool anchor_of(V a, Anchor *T) {
         if (!(a > -1e300)) return false;
-        *T = a + 1000.0 * 0.69314718055994530942;
+        *T = Anchor{a, -1000};
+        return true;
+    }
+    // the same place for a, with the offset at the largest value mx
+    __device__ static inline bool anchor_below(V a, V mx, Anchor *T) {
+        if (!(a > -1e300)) return false;
+        *T = Anchor{mx, -1000 - (int)rint(fmax(a - mx, -4000.0) * 1.4426950408889634074)};
         return true;
     }
     __device__ static inline double to_lin(V x, Anchor T) {
-        return x > -1e300 ? exp_scaled(x - T, 0) : 0.0;
+        return x > -1e300 ? exp_scaled(x - T.off, T.sh) : 0.0;
     }
     // a scale that puts the value 2^e2 at 2^940 (room for 4096 such terms)
     __device__ static inline Anchor anchor_high(int e2) {
-        return (double)(e2 - 940) * 0.69314718055994530942;
+        return Anchor{(double)e2 * 0.69314718055994530942, 940};
     }
-    __device__ static inline double prod_lin(V a, V b, V c, Anchor T) {
-        const double s = a + b + c;
-        return s > -1e300 ? exp_scaled(s - T, 0) : 0.0;
-    }
-    // prod_lin with the first two factors already multiplied (mul_raw)
-    __device__ static inline double prod2_lin(V ab, V c, Anchor T) {
-        const double s = ab + c;
-        return s > -1e300 ? exp_scaled(s - T, 0) : 0.0;
-    }
+    // the product of two factors (the first already a product, mul_raw)
+    __device__ static inline double prod2_lin(V ab, V c, Anchor T) { return to_lin(ab + c, T); }
     __device__ static inline V from_lin(double y, Anchor T) {
-        return y > 0.0 ? log_pos(y) + T : zero();
+        return y > 0.0 ? log_scaled(y, T.sh) + T.off : zero();
     }
     // from_lin(y) * q
     __device__ static inline V from_lin_q(double y, V q, Anchor T) {
@@ -475,16 +480,14 @@ struct PolX32 {
         *T = ((e + 1032) >> 6) << 6;
         return true;
     }
+    __device__ static inline bool anchor_below(V a, V, Anchor *T) { return anchor_of(a, T); }
     __device__ static inline double to_lin(V x, Anchor T) {
         return ldexp((double)x.f, max(x.e - T, -2000));
     }
     // a scale (a multiple of 64) that puts the value 2^e2 within 2^888 ..
     // 2^951 (room for 4096 such terms below 2^1000)
     __device__ static inline Anchor anchor_high(int e2) { return ((e2 - 888) >> 6) << 6; }
-    __device__ static inline double prod_lin(V a, V b, V c, Anchor T) {
-        return ldexp((double)(a.f * b.f * c.f), max(a.e + b.e + c.e - T, -2000));
-    }
-    // prod_lin with the first two factors already multiplied (mul_raw, f up
+    // the product of two factors, the first already a product (mul_raw, f up
     // to 2^64). A zero factor has significand 0, so no exponent clamp is
     // needed: ldexp of 0 is 0 for any exponent.
     __device__ static inline double prod2_lin(V ab, V c, Anchor T) {

@@ -395,8 +395,9 @@ k_scores_w(int n, int m, const uint8_t *__restrict__ data, const uint8_t *__rest
 //
 // Per-node scale for the linear alpha tiles. Every alpha_i(S) / q(|S|) is a
 // sum of B_i(G) over G subset S that includes B_i(empty), and none exceeds
-// K(n-1, d) max_G B_i(G). Node i therefore gets one power of two (a log
-// offset for the log-space system) that puts B_i(empty) near 2^-1000, and
+// K(n-1, d) max_G B_i(G). Node i therefore gets one power of two (in the
+// log-space system with an offset besides, the largest score) that puts
+// B_i(empty) near 2^-1000, and
 // the node is held in plain doubles when max_G B_i(G) / B_i(empty) is below
 // 2^1900: no partial sum can then leave the double range (K(n-1, d) <
 // 2^31). betal_i(r) = B_i(r) under that scale. Nodes that do not qualify
@@ -450,7 +451,7 @@ __global__ void k_prep(int n, int d, uint32_t K, const uint32_t *binom,
     if (betal) {
         const typename P::V b0 = gauged(log_rho[0] + logp[(size_t)i * K]);
         const double l2 = P::log2_of(gauged(mx));
-        lin = P::anchor_of(b0, &T) && l2 - P::log2_of(b0) <= 1900.0;
+        lin = P::anchor_below(b0, gauged(mx), &T) && l2 - P::log2_of(b0) <= 1900.0;
         if (chunk == 0 && t == 0) {
             anc[i] = T;
             linok[i] = lin ? 1 : 0;
@@ -2754,7 +2755,7 @@ k_gamma_highA12_log(int n, int d, uint32_t KA, int force_trunc, GammaGeom gg, Ta
         return;
     }
 #pragma unroll
-    for (int r = 0; r < 16; ++r) g[r] = g[r] > -1e300 ? ldexp(exp_neg(g[r] - mx), 960) : 0.0;
+    for (int r = 0; r < 16; ++r) g[r] = g[r] > -1e300 ? exp_below(g[r] - mx, 960) : 0.0;
     dense_zeta_down12_regs<Lin64>(g, vec, t);
     bool small = false;
     for (uint32_t pi = t; pi < KA; pi += kThreads) {
@@ -2762,10 +2763,9 @@ k_gamma_highA12_log(int n, int d, uint32_t KA, int force_trunc, GammaGeom gg, Ta
         if (__popc(x) <= tr) small = small || !(vec[padx(x)] >= 0x1p-1000);
     }
     if (!__syncthreads_or(small || force_trunc ? 1 : 0)) {
-        const double off = mx - 960.0 * 0.69314718055994530942;
         for (uint32_t pi = t; pi < KA; pi += kThreads) {
             const double y = vec[padx(tb.pat[pi])];
-            out_at(pi) = y > 0.0 ? log_pos(y) + off : -__builtin_huge_val();
+            out_at(pi) = y > 0.0 ? log_scaled(y, 960) + mx : -__builtin_huge_val();
         }
         return;
     }
@@ -2871,13 +2871,12 @@ k_gamma_small(int n, uint32_t K, int force_log, Tables tb, typename P::Store L,
             double y[16];
 #pragma unroll
             for (int r = 0; r < 16; ++r)
-                y[r] = g[r] > -1e300 ? ldexp(exp_neg(g[r] - mx), 960) : 0.0;
+                y[r] = g[r] > -1e300 ? exp_below(g[r] - mx, 960) : 0.0;
             masked_zeta_down12<Lin64>(y, vec, bits, t);
             bool small = false;
             each([&](uint32_t, uint32_t at) { small = small || !(vec[at] >= 0x1p-1000); });
             if (!__syncthreads_or(small ? 1 : 0)) {
-                const double off = mx - 960.0 * 0.69314718055994530942;
-                each([&](uint32_t r, uint32_t at) { out[r] = log_pos(vec[at]) + off; });
+                each([&](uint32_t r, uint32_t at) { out[r] = log_scaled(vec[at], 960) + mx; });
                 return;
             }
         }
@@ -2989,7 +2988,7 @@ k_gamma_high1(int n, int d, uint32_t K, int force_log, GammaGeom gg, Tables tb,
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const double M = rowmax[row_of((r << 8) | t)] * 0.69314718055994530942;
-                g[r] = g[r] > -1e300 ? ldexp(exp_neg(g[r] - M), 960) : 0.0;
+                g[r] = g[r] > -1e300 ? exp_below(g[r] - M, 960) : 0.0;
             }
         }
     }
@@ -3025,7 +3024,7 @@ k_gamma_high1(int n, int d, uint32_t K, int force_log, GammaGeom gg, Tables tb,
                 outputs([&](uint32_t x, uint32_t ri, uint32_t y) {
                     const double z = vec[padx(x)];
                     put(ri, y,
-                        z > 0.0 ? log_pos(z) + (rowmax[row_of(x)] - 960) * 0.69314718055994530942
+                        z > 0.0 ? log_scaled(z, 960) + rowmax[row_of(x)] * 0.69314718055994530942
                                 : -__builtin_huge_val());
                 });
                 return;

@@ -258,7 +258,7 @@ static Plan plan_of(int n, int d_in, int m, bn_precision prec, bool with_data, b
     P.o_zw9 = P.fused ? take(nz9 * 8) : 0;
     P.o_emax = take(32 * 4);
     P.o_flin = take(64 * 4);
-    P.o_anc = take(32 * 8);
+    P.o_anc = take(32 * 16);
     P.o_linok = take(32 * 4);
     // Gamma lists: endpoints for a second scale (at most one entry per tile and
     // endpoint); the fallback count, and one entry per tile when every tile is
