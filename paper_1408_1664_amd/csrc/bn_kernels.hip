@@ -3488,13 +3488,16 @@ __device__ inline uint32_t binom5(uint32_t p, int t) {
 // Scores of data whose variables all have arity r, d <= 4: one wave per SET of
 // 1 .. d + 1 variables instead of one per family. The families (i, U - i) of a
 // set U of k + 1 variables share their table of r^(k+1) counts, and with one
-// arity their cell hyperparameters too, so the table and the sum over its cells
-// of lgamma(a_jk + N_jk) - lgamma(a_jk) are computed once for all k + 1 of
-// them; each family then adds its row terms lgamma(a_j) - lgamma(a_j + N_j), a
-// marginal of the same table. The counting (LDS atomics, 4 samples per lane
+// arity their cell hyperparameters too, so the table and its cells' terms
+// lgamma(a_jk + N_jk) - lgamma(a_jk) are computed once for all k + 1 of them;
+// each family then sums them row by row, with lgamma(a_j) - lgamma(a_j + N_j) of
+// the row, a marginal of the same table (one sum over all cells for the whole
+// set cancels only at the end: rounding errors 10% larger). The counting (LDS atomics, 4 samples per lane
 // and load) bounds it: at n = 20, r = 3, m = 1000, d = 4 the 15,504 + 6,195
 // sets take about 55 us where a wave per family (100,720 of them) took 306 us.
-// Sets in order of size, then colex. Values >= r are counted nowhere. TAB: the
+// Sets in order of size, then colex. A value >= r (the device entry points do not
+// look at the data) is counted in some other cell or in none: the key is tested
+// against the table's size, so it never leaves it. TAB: the
 // log-gamma values come from lgamma_table, else each is evaluated in place
 // (the same values).
 template <bool TAB>
@@ -3502,12 +3505,13 @@ __global__ void __launch_bounds__(kThreads)
 k_scores_sets(int n, int m, int d, const uint8_t *__restrict__ data, int r, uint32_t K,
               uint32_t sets, int max_bins, int kind, double ess, const double *__restrict__ lgt,
               double *__restrict__ out) {
-    extern __shared__ int hist_all[];
+    extern __shared__ unsigned char smem[];
     typedef unsigned short us2 __attribute__((ext_vector_type(2)));
     const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
     uint32_t c = blockIdx.x * 4u + (uint32_t)w;
     if (c >= sets) return;                       // whole waves
-    int *hist = hist_all + w * max_bins;
+    double *cell = reinterpret_cast<double *>(smem) + w * max_bins;
+    int *hist = reinterpret_cast<int *>(smem + (size_t)32 * max_bins) + w * max_bins;
     // size and members: the largest p with C(p, t) <= c, found over the lanes
     int k1 = 1;
     while (k1 <= d && c >= binom5((uint32_t)n, k1)) c -= binom5((uint32_t)n, k1++);
@@ -3564,25 +3568,29 @@ k_scores_sets(int n, int m, int d, const uint8_t *__restrict__ data, int r, uint
     auto lg_row = [&](int v) { return TAB ? lj[v] : lgamma(a_j + v); };
     auto lg_cell = [&](int v) { return TAB ? ljk[v] : lgamma(a_jk + v); };
     const double lg_aj = lg_row(0), lg_ajk = lg_cell(0);
-    double cells = 0.0;
     for (int b = l; b < bins; b += 64) {
         const int v = hist[b];
-        if (v) cells += lg_cell(v) - lg_ajk;
+        cell[b] = v ? lg_cell(v) - lg_ajk : 0.0;
     }
+    __builtin_amdgcn_wave_barrier();
     // rows of the family whose child is digit t: cells that agree elsewhere
     double mine = 0.0;                           // lane t: the score of child var[t]
     int stride = 1;
 #pragma unroll
     for (int t = 0; t < 5; ++t) {
         if (t < k1) {
-            double acc = cells;
+            double acc = 0.0;
             const uint32_t inv = (65536u + (uint32_t)stride - 1u) / (uint32_t)stride;
             for (int row = l; row < rows; row += 64) {
                 const int hi = (int)(((uint32_t)row * inv) >> 16);    // row / stride, rows < 2048
                 const int base = hi * stride * r + (row - hi * stride);
                 int nj = 0;
-                for (int v = 0; v < r; ++v) nj += hist[base + v * stride];
-                if (nj) acc += lg_aj - lg_row(nj);
+                double sj = 0.0;
+                for (int v = 0; v < r; ++v) {
+                    nj += hist[base + v * stride];
+                    sj += cell[base + v * stride];
+                }
+                if (nj) acc += sj + lg_aj - lg_row(nj);
             }
             for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
             if (l == t) mine = acc;
@@ -3608,9 +3616,12 @@ k_scores_sets(int n, int m, int d, const uint8_t *__restrict__ data, int r, uint
 // count_cells2 leaves them (lane L < 2^k: the two counts of configuration L of
 // variables 0 .. k-1, by the value of variable k). Child k: the row of
 // configuration L is the lane's own pair; child j < k: the rows pair the lanes
-// that differ in bit j, one row per value of variable k, taken by the lane
-// without the bit. Lane t < k + 1 returns the score of child t. Partial sums
-// meet in fixed butterflies; log-gamma values from the tables.
+// that differ in bit j, one row per value of variable k: value 0 taken by the
+// lane without the bit, 1 by the other, which trade the terms of their cells.
+// Lane t < k + 1 returns the score of child t. Whole rows (whose large terms
+// have cancelled) meet in a butterfly over the row index, the child's parents in
+// order and the highest first, so that the sums are those of a family alone;
+// log-gamma values from the tables.
 template <int KP>
 __device__ inline double set_scores2(const uint32_t *cnt, int lane, const double *lgt, int m1) {
     constexpr int Q = 1 << KP;
@@ -3618,26 +3629,25 @@ __device__ inline double set_scores2(const uint32_t *cnt, int lane, const double
     const double lg_aj = lj[0], lg_ajk = ljk[0];
     const bool live = lane < Q;
     const uint32_t c0 = live ? cnt[0] : 0u, c1 = live ? cnt[1] : 0u;
-    double cells = 0.0;
-    if (c0) cells += ljk[c0] - lg_ajk;
-    if (c1) cells += ljk[c1] - lg_ajk;
+    const double l0 = c0 ? ljk[c0] - lg_ajk : 0.0, l1 = c1 ? ljk[c1] - lg_ajk : 0.0;
     double mine = 0.0;
 #pragma unroll
     for (int t = 0; t <= KP; ++t) {
-        double acc = cells;
-        uint32_t n0, n1 = 0;
+        uint32_t nj;
+        double sj;
         if (t == KP) {
-            n0 = c0 + c1;
+            nj = c0 + c1;
+            sj = l0 + l1;
         } else {
-            const uint32_t o0 = __shfl_xor(c0, 1 << t, 16), o1 = __shfl_xor(c1, 1 << t, 16);
             const bool own = !((lane >> t) & 1);
-            n0 = own ? c0 + o0 : 0u;
-            n1 = own ? c1 + o1 : 0u;
+            nj = (own ? c0 : c1) + __shfl_xor(own ? c1 : c0, 1 << t, 16);
+            sj = (own ? l0 : l1) + __shfl_xor(own ? l1 : l0, 1 << t, 16);
         }
-        if (n0) acc += lg_aj - lj[n0];
-        if (n1) acc += lg_aj - lj[n1];
+        double acc = nj ? sj + lg_aj - lj[nj] : 0.0;
+        if (t < KP) acc += __shfl_xor(acc, 1 << t, 16);      // variable k
 #pragma unroll
-        for (int o = 8; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 16);
+        for (int j = KP - 1; j >= 0; --j)
+            if (j != t) acc += __shfl_xor(acc, 1 << j, 16);
         if (lane == t) mine = acc;
     }
     return mine;
@@ -3645,8 +3655,8 @@ __device__ inline double set_scores2(const uint32_t *cnt, int lane, const double
 
 // Local scores of all-binary data with d <= 4 by sets of variables, as
 // k_scores_sets: 16 lanes per set, 16 sets per workgroup, counts from the bit
-// planes of pack2. The k + 1 families of a set share its counts and the sum over
-// its cells (n = 25, m = 2000, d = 4: 41 us, by families 143; n = 30, d = 3: 15, 48).
+// planes of pack2. The k + 1 families of a set share its counts and its cells'
+// terms (n = 25, m = 2000, d = 4: 41 us, by families 143; n = 30, d = 3: 15, 48).
 __global__ void __launch_bounds__(kThreads)
 k_scores2(int n, int W, int m, int d, uint32_t K, uint32_t sets,
           const uint32_t *__restrict__ bits, const double *__restrict__ lgt,
@@ -3789,7 +3799,9 @@ hipError_t launch_scores(int n, int m, const uint8_t *data, const uint8_t *arity
         // sets of 1 .. d + 1 variables
         const uint32_t sets = host_kcount(n, d + 1) - 1;
         const dim3 grid((sets + 3) / 4);
-        const size_t sm = (size_t)4 * max_bins * sizeof(int);
+        const size_t sm = (size_t)4 * max_bins * (sizeof(double) + sizeof(int));
+        allow_big_lds<k_scores_sets<true>>();
+        allow_big_lds<k_scores_sets<false>>();
         if (tables) {
             hipLaunchKernelGGL(k_scores_sets<true>, grid, dim3(kThreads), sm, st, n, m, d, data,
                                uniform_r, K, sets, max_bins, kind, ess, (const double *)lgt, out);

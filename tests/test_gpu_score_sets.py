@@ -50,3 +50,24 @@ def test_binary_scores_by_sets(n, d, m, kind):
         pair = bn.local_scores(ds.data[[i, j]], [2, 2], 1, score=kind, ess=1.5)
         np.testing.assert_allclose(got[i, [0, 1 + (j if j < i else j - 1)]], pair[0], rtol=1e-12,
                                    atol=1e-10)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kind", ["bdeu", "k2"])
+@pytest.mark.parametrize("n,r,d,m", [(3, 2, 1, 40), (12, 2, 4, 2000), (17, 2, 3, 700), (11, 3, 4, 1000),
+                                     (14, 3, 2, 999), (9, 4, 4, 300), (8, 6, 3, 500), (4, 45, 1, 3000)])
+def test_sets_score_as_families_do(n, r, d, m, kind):
+    """Scoring a set's families together changes no bit of any score: against
+    the same data beside one variable of another arity, whose families are
+    scored one by one. Its parent sets without that variable are ranked first
+    within each size, in the same order."""
+    ds = datagen.random_dag_dataset(n, m, r, min(3, n - 1), 0.5, seed=80 + n + r)
+    print(f"score sets against families n={n} r={r} d={d} m={m} {kind}", flush=True)
+    got = bn.local_scores(ds.data, ds.arity, d, score=kind, ess=1.5)
+    other = np.arange(m, dtype=np.uint8)[None] % (r + 1)
+    mixed = bn.local_scores(np.vstack([ds.data, other]), np.append(ds.arity, r + 1), d, score=kind,
+                            ess=1.5)
+    K = [bn.num_parent_sets(n + 1, k) for k in range(-1, d + 1)]
+    L = [bn.num_parent_sets(n, k) for k in range(-1, d + 1)]
+    at = np.concatenate([np.arange(K[k], K[k] + L[k + 1] - L[k]) for k in range(d + 1)])
+    assert np.array_equal(got, mixed[:n, at])
