@@ -148,6 +148,11 @@ struct SetupArgs {
     uint32_t *bits;
     double *lgt;
 };
+// Ranges of Gamma tiles that the layer sums of L(S) Rp(S) are taken over: at
+// most 32, about 256 tiles each; 0 where the sweep tiles serve (n < 12).
+inline int inv_chunks(int n) {
+    return n < 12 ? 0 : n < 20 ? 1 : n < 25 ? 1 << (n - 20) : 32;
+}
 hipError_t launch_setup(const Tables &tb, int bL, int W, int bG, int bA, int d, uint32_t N,
                         uint32_t K, const ParamBlock &pb, const SetupArgs &sa, hipStream_t st);
 // sum_{k < h} C(nh, k): the first entry of layer h in Tables::hord

@@ -3236,7 +3236,6 @@ __device__ inline void edge_sum(int v, int u, int n, uint32_t K,
 // Every layer sum over |S| = k of L(S) Rp(S) must equal L(V). inv_tile: the
 // sum over in-tile layer l of tile H, to part; inv_layer: the layer-k sum over
 // the c-th of `chunks` ranges of tiles, to layer[k * chunks + c].
-constexpr int kInvChunks = 32;   // at most, about 256 tiles each
 template <class P>
 __device__ inline void inv_tile(uint32_t H, int l, int bL, const Tables &tb,
                                 const typename P::Store &L, const typename P::Store &R,
@@ -4165,7 +4164,7 @@ static hipError_t launch_gamma_edges(const LatticeArgs &a, const typename P::Sto
     rec(5);
     // layer sums of L(S) Rp(S): partials per tile come from the Gamma tile
     // kernel (12-bit tiles), else they are taken per sweep tile
-    const int tiled = a.bG == 12 ? std::min(kInvChunks, std::max(1, (1 << (n - 12)) / 256)) : 0;
+    const int tiled = inv_chunks(n);
     const unsigned ninv = tiled ? (unsigned)((n + 1) * tiled) : (unsigned)(a.bL + 1) << nh;
     hipLaunchKernelGGL(k_finish<P>, dim3((unsigned)(n * (n + 1)) + ninv), dim3(kThreads), 0, st, n,
                        a.K, tiled, tiled ? 12 : a.bL, tb, (const uint32_t *)tb.famask,

@@ -211,11 +211,11 @@ static Plan plan_of(int n, int d_in, int m, bn_precision prec, bool with_data, b
     P.o_arity = take(64);
     P.o_rho = take(34 * 8);
     P.o_q = take(32 * 8);
-    P.o_cnt = take(2 * 8);
-    P.o_done = take(17 * 128);
+    P.o_done = take(17 * 128 + 2 * 8);
+    P.o_cnt = P.o_done + 17 * 128;
     P.o_diag = take(16 * 8);
     P.o_resid = take(32 * 8);
-    P.o_layer = take(33 * 32 * V);     // layer sums of L(S) Rp(S), 32 tile ranges each
+    P.o_layer = take((size_t)(n + 1) * inv_chunks(n) * V);   // layer sums of L(S) Rp(S)
     P.o_qt = take(32 * V);
     P.o_gexp = take(64 * 8);
     P.o_logp = take((size_t)n * P.K * 8);
@@ -236,13 +236,14 @@ static Plan plan_of(int n, int d_in, int m, bn_precision prec, bool with_data, b
         P.o_L_f = take(NS * 8);
         P.o_R_f = take(NS * 8);
     }
-    P.o_Y1 = take((size_t)P.y1_elems * V);
+    // up to n = 12 no endpoint has bits above the tile: Gamma has no first part
+    P.o_Y1 = n > 12 ? take((size_t)P.y1_elems * V) : 0;
     if (P.two_level) P.o_Y2 = take((size_t)P.y2_elems * V);
     P.o_gam = take((size_t)n * P.K * V);
-    P.o_part = take(std::max(((size_t)1 << nh) * (P.bL + 1),
-                             n >= 12 ? ((size_t)1 << (n - 12)) * 13 : (size_t)0) * V);
+    P.o_part = take((n >= 12 ? ((size_t)1 << (n - 12)) * 13 : ((size_t)1 << nh) * (P.bL + 1)) * V);
     P.o_fbA = P.fused ? take(8) : (P.bA == 13 ? take(4 * (1 + ((size_t)n << (N - 13)))) : 0);
-    P.o_betal = take((size_t)n * P.K * 8);
+    // n = 13: alpha, which reads these scores, is done before Gamma writes Y1
+    P.o_betal = n == 13 && !P.fused ? P.o_Y1 : take((size_t)n * P.K * 8);
     // Linear alpha tiles keep their seeds (K(13, d) doubles per tile) in the
     // workspace when those take at most 16 GiB; otherwise alpha runs in the
     // number system proper.
