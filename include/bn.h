@@ -102,6 +102,11 @@ typedef struct {
     uint64_t flushed;              /* FP32-scaled: nonzero entries rounded to 0 below
                                       the bottom of the exponent range               */
     double ms_scores, ms_alpha, ms_fwd, ms_bwd, ms_gamma, ms_edges, ms_total;
+                                   /* HIP events, as ms[0] to ms[6] of bn_timer_read:
+                                      the two sweeps run side by side, so ms_fwd is the
+                                      time of both and ms_bwd what of the backward one
+                                      outlasts the forward one (alpha never
+                                      materialised: each sweep's own)               */
     double ms_queue;               /* serving: submit -> admission (host clock)      */
     double ms_latency;             /* serving: submit -> completion observed          */
     uint64_t fallback_tiles;       /* zeta tiles (alpha, Gamma) whose range did not fit
@@ -128,6 +133,12 @@ size_t bn_num_parent_sets(int32_t n, int32_t d);
  */
 bn_status bn_local_scores(const bn_problem *p, double *log_score);
 
+/* Frees what finished blocking calls have left for later ones: at most four
+ * device workspaces of up to 64 MiB, each with 1 MiB of pinned host memory and
+ * seven events. For programs that need the memory elsewhere, or are about to
+ * reset the device. Calls that are running keep theirs. Always BN_OK. */
+bn_status bn_release_idle(void);
+
 /* Device workspace needed by bn_edge_posteriors_dev for a given problem
  * shape. The sample count m enters because the workspace also holds the
  * score step's per-sample tables (bit planes of binary data and log-gamma
@@ -141,7 +152,8 @@ bn_status bn_workspace_bytes(int32_t n, int32_t d, int32_t m, bn_precision prec,
  * scores by Eq. 6, alpha by Eq. 7, the forward and backward sums of Eqs. 9
  * and 10, Gamma by Eq. 12, and P(u -> v | D) by Eq. 11, divided by F(V) =
  * P(D)). Uses a device workspace of its own (up to 64 MiB of it is kept for
- * later blocking calls, by at most four of them), copies the data, runs every
+ * later blocking calls, by at most four of them, until an allocation of this
+ * library fails or bn_release_idle() is called), copies the data, runs every
  * step on the current HIP device and blocks until done.
  *   post: host, n*n doubles, post[u*n + v] = P(u -> v | D); diagonal 0.
  *   rep:  nullable; per-phase times are measured with HIP events.

@@ -88,6 +88,8 @@ def lib():
         P, I32, U64 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_uint64
         L.bn_num_parent_sets.argtypes = [I32, I32]
         L.bn_num_parent_sets.restype = ctypes.c_size_t
+        L.bn_release_idle.argtypes = []
+        L.bn_release_idle.restype = ctypes.c_int
         L.bn_local_scores.argtypes = [P, P]
         L.bn_local_scores.restype = ctypes.c_int
         L.bn_workspace_bytes.argtypes = [I32, I32, I32, ctypes.c_int, P]
@@ -186,6 +188,12 @@ def workspace_bytes(n: int, d: int, m: int, precision="fp32") -> int:
     _check(lib().bn_workspace_bytes(n, d, m, _PREC[precision], ctypes.byref(b)),
            "bn_workspace_bytes")
     return int(b.value)
+
+
+def release_idle() -> None:
+    """Frees the device memory, staging blocks and events that finished blocking
+    calls keep for later ones (at most four workspaces of up to 64 MiB)."""
+    _check(lib().bn_release_idle(), "bn_release_idle")
 
 
 def edge_posteriors(data, arity, d, precision="fp64", score="bdeu", ess=1.0, log_rho=None,

@@ -97,6 +97,9 @@ struct HipMem {
     static bool alloc(size_t bytes, void **p) {
         if (hipMalloc(p, bytes) == hipSuccess) return true;
         (void)hipGetLastError();
+        release_idle_sessions();             // the blocking calls' idle memory
+        if (hipMalloc(p, bytes) == hipSuccess) return true;
+        (void)hipGetLastError();
         return false;
     }
     static void release(void *p) { (void)hipFree(p); }

@@ -41,6 +41,9 @@ struct Plan {
 
 bn_status validate(const bn_problem *p, bool host_data, bool check_values);
 Plan make_plan(int n, int d, int m, bn_precision prec, bool with_data, bool with_post);
+// Frees the device memory, staging blocks and events that finished blocking
+// calls have left for later ones.
+void release_idle_sessions();
 bn_status enqueue_solve(const Plan &P, const bn_problem *p, const uint8_t *dev_data, char *ws,
                         hipStream_t st, double *dev_post, double *dev_diag, PhaseEvents *ev,
                         double *dev_ps = nullptr);

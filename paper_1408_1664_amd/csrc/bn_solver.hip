@@ -15,6 +15,7 @@
 #include "../../include/bn.h"
 #include "bn_device.h"
 #include "bn_kernels.h"
+#include "bn_sessions.h"
 #include "bn_solver.h"
 
 namespace bnk {
@@ -502,102 +503,76 @@ bn_status enqueue_solve(const Plan &P, const bn_problem *p, const uint8_t *dev_d
     return run_lattice(P, ws, a, st, ev);
 }
 
-// What a blocking call needs besides its problem: device memory, a pinned
-// staging block and the phase events. hipMalloc, hipFree and seven events cost a
-// small solve as much as its kernels (n = 18: 200 of 430 us), so finished
-// calls leave theirs for the next one: at most kIdleSessions of them in a
-// process, with at most kKeepBytes of device memory each (larger blocks are
-// freed by the call that made them), and all of it is freed when an allocation
-// of these calls fails. A session belongs to one call at a time and is idle only
-// after its stream was synchronised, so threads and streams never share one.
-constexpr size_t kKeepBytes = (size_t)64 << 20;
-constexpr size_t kIdleSessions = 4;
-constexpr size_t kPinBytes = (size_t)1 << 20;   // larger transfers go straight to the caller
-struct HostSession {
-    int dev = -1;
-    char *ws = nullptr;
-    size_t bytes = 0;
-    char *pin = nullptr;
-    PhaseEvents ev{};
-    bool events = false;
-    void free_ws() {
-        if (ws) (void)hipFree(ws);
-        ws = nullptr;
-        bytes = 0;
+// The device calls of the blocking calls' sessions (bn_sessions.h).
+struct HipSessions {
+    using Events = PhaseEvents;
+    static bool current(int *dev) { return hipGetDevice(dev) == hipSuccess; }
+    // unique in the process; 0 for memory that is gone
+    static uint64_t id_of(void *p) {
+        unsigned long long id = 0;
+        if (hipPointerGetAttribute(&id, HIP_POINTER_ATTRIBUTE_BUFFER_ID, (hipDeviceptr_t)p) !=
+            hipSuccess) {
+            (void)hipGetLastError();
+            return 0;
+        }
+        return id;
     }
-    void destroy() {
-        free_ws();
-        if (pin) (void)hipHostFree(pin);
-        for (hipEvent_t &e : ev.ev)
+    static bool holds(void *p, uint64_t id) { return id_of(p) == id; }
+    static bool alloc(size_t bytes, char **p, uint64_t *id, bool *lost) {
+        size_t free_b = 0, total_b = 0;
+        *lost = hipMemGetInfo(&free_b, &total_b) != hipSuccess;
+        if (*lost || bytes > free_b || hipMalloc((void **)p, bytes) != hipSuccess) {
+            (void)hipGetLastError();
+            *p = nullptr;
+            return false;
+        }
+        *id = id_of(*p);
+        return true;
+    }
+    static void release(char *p) { (void)hipFree(p); }
+    static bool alloc_pinned(size_t bytes, char **p, uint64_t *id) {
+        if (hipHostMalloc((void **)p, bytes) != hipSuccess) {
+            (void)hipGetLastError();
+            *p = nullptr;
+            return false;
+        }
+        *id = id_of(*p);
+        return true;
+    }
+    static void release_pinned(char *p) { (void)hipHostFree(p); }
+    static bool make_events(Events &ev) {
+        for (int k = 0; k < 7; ++k) {
+            if (!ev.ev[k] && hipEventCreate(&ev.ev[k]) != hipSuccess) {
+                (void)hipGetLastError();
+                ev.ev[k] = nullptr;
+                destroy_events(ev);
+                return false;
+            }
+        }
+        return true;
+    }
+    static void destroy_events(Events &ev) {
+        for (hipEvent_t &e : ev.ev) {
             if (e) (void)hipEventDestroy(e);
-        *this = HostSession{};
+            e = nullptr;
+        }
     }
 };
-static std::mutex g_idle_mu;
-static std::vector<HostSession> g_idle;
+using HostSession = Session<HipSessions>;
+static SessionPool<HipSessions> g_sessions;
+constexpr size_t kPinBytes = SessionPool<HipSessions>::kPinBytes;
 
-// a session on the current device with at least `bytes` of device memory
 static bn_status take_session(size_t bytes, bool events, HostSession *out) {
-    HostSession s;
-    if (hipGetDevice(&s.dev) != hipSuccess) return BN_EDEVICE;
-    {
-        std::lock_guard<std::mutex> lk(g_idle_mu);
-        // the smallest idle block that fits, else any session of the device
-        int best = -1;
-        for (int k = 0; k < (int)g_idle.size(); ++k) {
-            const HostSession &c = g_idle[k];
-            if (c.dev != s.dev) continue;
-            if (best < 0) best = k;
-            const size_t cur = g_idle[best].bytes;
-            if (c.bytes >= bytes && (cur < bytes || c.bytes < cur)) best = k;
-        }
-        if (best >= 0) {
-            s = g_idle[best];
-            g_idle.erase(g_idle.begin() + best);
-        }
+    using Got = SessionPool<HipSessions>::Got;
+    switch (g_sessions.take(bytes, events, out)) {
+        case Got::ok: return BN_OK;
+        case Got::no_memory: return BN_ENOMEM;
+        default: return BN_EDEVICE;
     }
-    if (s.bytes < bytes) {
-        s.free_ws();
-        auto fits = [&] {
-            size_t free_b = 0, total_b = 0;
-            return hipMemGetInfo(&free_b, &total_b) == hipSuccess && bytes <= free_b &&
-                   hipMalloc(&s.ws, bytes) == hipSuccess;
-        };
-        if (!fits()) {
-            (void)hipGetLastError();
-            std::vector<HostSession> idle;
-            {
-                std::lock_guard<std::mutex> lk(g_idle_mu);
-                idle.swap(g_idle);
-            }
-            for (HostSession &c : idle) c.destroy();
-            s.ws = nullptr;
-            if (!fits()) {
-                (void)hipGetLastError();
-                s.ws = nullptr;
-                s.destroy();
-                return BN_ENOMEM;
-            }
-        }
-        s.bytes = bytes;
-    }
-    if (!s.pin && hipHostMalloc((void **)&s.pin, kPinBytes) != hipSuccess) {
-        (void)hipGetLastError();
-        s.pin = nullptr;                     // transfers then use the caller's memory
-    }
-    if (events && !s.events) {
-        for (int k = 0; k < 7; ++k) (void)hipEventCreate(&s.ev.ev[k]);
-        s.events = true;
-    }
-    *out = s;
-    return BN_OK;
 }
-static void give_session(HostSession &s) {
-    if (s.bytes > kKeepBytes) s.free_ws();
-    std::lock_guard<std::mutex> lk(g_idle_mu);
-    if (g_idle.size() < kIdleSessions) g_idle.push_back(s);
-    else s.destroy();
-}
+static void give_session(HostSession &s, bn_status rs) { g_sessions.give(s, rs == BN_OK); }
+
+void release_idle_sessions() { g_sessions.release(); }
 
 // Sample data to the device, through the pinned block where it fits.
 static bool put_data(const HostSession &s, uint8_t *dev, const uint8_t *host, size_t bytes,
@@ -630,7 +605,7 @@ bn_status local_scores_host(const bn_problem *p, double *log_score) {
                        st) != hipSuccess)
         rs = BN_EDEVICE;
     if (hipStreamSynchronize(st) != hipSuccess) rs = BN_EDEVICE;
-    give_session(hs);
+    give_session(hs, rs);
     return rs;
 }
 
@@ -646,7 +621,7 @@ bn_status edge_posteriors_host(const bn_problem *p, bn_precision prec, double *p
     s = take_session(P.total, timing, &hs);
     if (s != BN_OK) return s;
     char *ws = hs.ws;
-    PhaseEvents &ev = hs.ev;
+    PhaseEvents &ev = hs.ev;              // without events the times read 0
     hipStream_t st = nullptr;
     uint8_t *dev_data = reinterpret_cast<uint8_t *>(ws + P.o_data);
     // the diagnostics follow the posteriors, the parent sets follow both: one
@@ -657,7 +632,7 @@ bn_status edge_posteriors_host(const bn_problem *p, bn_precision prec, double *p
     double *dev_ps = ps ? reinterpret_cast<double *>(ws + P.o_ps) : nullptr;
     bn_status rs = put_data(hs, dev_data, p->data, (size_t)P.n * P.m, st) ? BN_OK : BN_EDEVICE;
     if (rs == BN_OK)
-        rs = enqueue_solve(P, p, dev_data, ws, st, dev_post, dev_diag, timing ? &ev : nullptr,
+        rs = enqueue_solve(P, p, dev_data, ws, st, dev_post, dev_diag, timing && hs.events ? &ev : nullptr,
                            dev_ps);
     double diag[16] = {0};
     const size_t ps_bytes = (size_t)P.n * P.K * 8;
@@ -694,9 +669,11 @@ bn_status edge_posteriors_host(const bn_problem *p, bn_precision prec, double *p
         rep->flushed = (uint64_t)diag[3];
         rep->fallback_tiles = (uint64_t)diag[7];
         float ms[7] = {0};
-        for (int k = 1; k < 7; ++k) (void)hipEventElapsedTime(&ms[k], ev.ev[k - 1], ev.ev[k]);
         float tot = 0;
-        (void)hipEventElapsedTime(&tot, ev.ev[0], ev.ev[6]);
+        if (hs.events) {
+            for (int k = 1; k < 7; ++k) (void)hipEventElapsedTime(&ms[k], ev.ev[k - 1], ev.ev[k]);
+            (void)hipEventElapsedTime(&tot, ev.ev[0], ev.ev[6]);
+        }
         rep->ms_scores = ms[1];
         rep->ms_alpha = ms[2];
         rep->ms_fwd = ms[3];
@@ -724,7 +701,7 @@ bn_status edge_posteriors_host(const bn_problem *p, bn_precision prec, double *p
                     cnt[0], cnt[1], cnt[2]);
         }
     }
-    give_session(hs);
+    give_session(hs, rs);
     return rs;
 }
 
@@ -767,7 +744,7 @@ bn_status feature_posterior_host(const bn_problem *p, bn_precision prec, const d
     if (rs == BN_OK && hipMemcpyAsync(d1, dev_diag, 64, hipMemcpyDeviceToHost, st) != hipSuccess)
         rs = BN_EDEVICE;
     if (hipStreamSynchronize(st) != hipSuccess) rs = BN_EDEVICE;
-    give_session(hs);
+    give_session(hs, rs);
     if (rs != BN_OK) return rs;
     *out = d1[0] > -HUGE_VAL ? std::exp(d1[0] - d0[0]) : 0.0;
     if (log_pair) {
@@ -847,6 +824,11 @@ extern "C" {
 size_t bn_num_parent_sets(int32_t n, int32_t d) {
     if (n < 1 || d < 0) return 0;
     return (size_t)bnk::kcount_u64(n - 1, std::min(d, n - 1));
+}
+
+bn_status bn_release_idle(void) {
+    bnk::release_idle_sessions();
+    return BN_OK;
 }
 
 bn_status bn_local_scores(const bn_problem *p, double *log_score) {
