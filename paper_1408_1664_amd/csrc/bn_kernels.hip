@@ -3488,7 +3488,7 @@ __device__ inline uint32_t binom5(uint32_t p, int t) {
 // 1 .. d + 1 variables instead of one per family. The families (i, U - i) of a
 // set U of k + 1 variables share their table of r^(k+1) counts, and with one
 // arity their cell hyperparameters too, so the table and its cells' terms
-// lgamma(a_jk + N_jk) - lgamma(a_jk) are computed once for all k + 1 of them;
+// lgamma(a_jk + N_jk) - lgamma(a_jk) are taken once for all k + 1 of them (HELD: in LDS);
 // each family then sums them row by row, with lgamma(a_j) - lgamma(a_j + N_j) of
 // the row, a marginal of the same table (one sum over all cells for the whole
 // set cancels only at the end: rounding errors 10% larger). The counting (LDS atomics, 4 samples per lane
@@ -3499,7 +3499,7 @@ __device__ inline uint32_t binom5(uint32_t p, int t) {
 // against the table's size, so it never leaves it. TAB: the
 // log-gamma values come from lgamma_table, else each is evaluated in place
 // (the same values).
-template <bool TAB>
+template <bool TAB, bool HELD>
 __global__ void __launch_bounds__(kThreads)
 k_scores_sets(int n, int m, int d, const uint8_t *__restrict__ data, int r, uint32_t K,
               uint32_t sets, int max_bins, int kind, double ess, const double *__restrict__ lgt,
@@ -3509,8 +3509,8 @@ k_scores_sets(int n, int m, int d, const uint8_t *__restrict__ data, int r, uint
     const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
     uint32_t c = blockIdx.x * 4u + (uint32_t)w;
     if (c >= sets) return;                       // whole waves
-    double *cell = reinterpret_cast<double *>(smem) + w * max_bins;
-    int *hist = reinterpret_cast<int *>(smem + (size_t)32 * max_bins) + w * max_bins;
+    double *cell = reinterpret_cast<double *>(smem) + w * max_bins;       // HELD
+    int *hist = reinterpret_cast<int *>(smem + (HELD ? (size_t)32 * max_bins : 0)) + w * max_bins;
     // size and members: the largest p with C(p, t) <= c, found over the lanes
     int k1 = 1;
     while (k1 <= d && c >= binom5((uint32_t)n, k1)) c -= binom5((uint32_t)n, k1++);
@@ -3567,11 +3567,11 @@ k_scores_sets(int n, int m, int d, const uint8_t *__restrict__ data, int r, uint
     auto lg_row = [&](int v) { return TAB ? lj[v] : lgamma(a_j + v); };
     auto lg_cell = [&](int v) { return TAB ? ljk[v] : lgamma(a_jk + v); };
     const double lg_aj = lg_row(0), lg_ajk = lg_cell(0);
-    for (int b = l; b < bins; b += 64) {
-        const int v = hist[b];
-        cell[b] = v ? lg_cell(v) - lg_ajk : 0.0;
+    auto term = [&](int v) { return v ? lg_cell(v) - lg_ajk : 0.0; };
+    if constexpr (HELD) {
+        for (int b = l; b < bins; b += 64) cell[b] = term(hist[b]);
+        __builtin_amdgcn_wave_barrier();
     }
-    __builtin_amdgcn_wave_barrier();
     // rows of the family whose child is digit t: cells that agree elsewhere
     double mine = 0.0;                           // lane t: the score of child var[t]
     int stride = 1;
@@ -3586,8 +3586,10 @@ k_scores_sets(int n, int m, int d, const uint8_t *__restrict__ data, int r, uint
                 int nj = 0;
                 double sj = 0.0;
                 for (int v = 0; v < r; ++v) {
-                    nj += hist[base + v * stride];
-                    sj += cell[base + v * stride];
+                    const int c = hist[base + v * stride];
+                    nj += c;
+                    if constexpr (HELD) sj += cell[base + v * stride];
+                    else sj += term(c);
                 }
                 if (nj) acc += sj + lg_aj - lg_row(nj);
             }
@@ -3798,15 +3800,22 @@ hipError_t launch_scores(int n, int m, const uint8_t *data, const uint8_t *arity
         // sets of 1 .. d + 1 variables
         const uint32_t sets = host_kcount(n, d + 1) - 1;
         const dim3 grid((sets + 3) / 4);
-        const size_t sm = (size_t)4 * max_bins * (sizeof(double) + sizeof(int));
-        allow_big_lds<k_scores_sets<true>>();
-        allow_big_lds<k_scores_sets<false>>();
-        if (tables) {
-            hipLaunchKernelGGL(k_scores_sets<true>, grid, dim3(kThreads), sm, st, n, m, d, data,
-                               uniform_r, K, sets, max_bins, kind, ess, (const double *)lgt, out);
-        } else
-            hipLaunchKernelGGL(k_scores_sets<false>, grid, dim3(kThreads), sm, st, n, m, d, data,
-                               uniform_r, K, sets, max_bins, kind, ess, (const double *)lgt, out);
+        // The cells' terms stay in LDS while that leaves five workgroups per CU
+        // (640 cells: n = 20, m = 1000, d = 4 with three states 75 us for the score
+        // phase, 81 with the terms taken from the tables again for each family), or
+        // where there is at most one per CU (n = 10, six states, d = 3: 31 against
+        // 36 us); above, fewer workgroups cost more than the loads (four states, d =
+        // 4: 138 against 106 us).
+        const bool held = max_bins <= 640 || grid.x <= 256;
+        const size_t sm = (size_t)4 * max_bins * (sizeof(int) + (held ? sizeof(double) : 0));
+        auto go = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, grid, dim3(kThreads), sm, st, n, m, d, data, uniform_r, K,
+                               sets, max_bins, kind, ess, (const double *)lgt, out);
+        };
+        allow_big_lds<k_scores_sets<true, true>>();
+        allow_big_lds<k_scores_sets<false, true>>();
+        if (tables) held ? go(k_scores_sets<true, true>) : go(k_scores_sets<true, false>);
+        else held ? go(k_scores_sets<false, true>) : go(k_scores_sets<false, false>);
     } else if (max_bins <= kScoreWaveBins) {
         hipLaunchKernelGGL(k_scores_w, dim3((unsigned)((n * (uint64_t)K + 3) / 4)), dim3(kThreads),
                            (size_t)4 * max_bins * sizeof(int), st, n, m, data, arity, K, kind, ess,
