@@ -165,6 +165,7 @@ hipError_t launch_add_log(double *logp, const double *log_f, size_t count, hipSt
 // scored together, with log-gamma values from tables (`tables`) or evaluated
 // in place; lgt: the tables, 10 (m + 1) doubles.
 // Planes and tables are those of launch_setup.
+constexpr int kScoreWaveBins = 2048;   // cells of a wave's table in the score kernels
 hipError_t launch_scores(int n, int m, const uint8_t *data, const uint8_t *arity, uint32_t K,
                          int kind, double ess, const uint32_t *famask, int max_bins,
                          double *out, hipStream_t st, uint32_t *bits, int uniform_r, int d,

@@ -123,8 +123,8 @@ __device__ inline void ranked_chunk(const uint32_t *bn, int w, int d, uint32_t x
 struct TableGrid {
     uint32_t s, a, i, f, h, p, b, g;   // cumulative ends of the ranges
 };
-__device__ void pack2(uint32_t id, int n, int m, int W, const uint8_t *__restrict__ data,
-                      uint32_t *__restrict__ bits);
+__device__ void pack2(uint32_t wave0, uint32_t step, int n, int m, int W,
+                      const uint8_t *__restrict__ data, uint32_t *__restrict__ bits);
 __device__ void lgamma_table(uint32_t x0, uint32_t step, int m, int r, int kind, double ess,
                              double *__restrict__ lgt);
 __global__ void k_setup(Tables tb, LaneOrder oc, TableGrid g, int bL, int W, int bG, int bA,
@@ -213,7 +213,8 @@ __global__ void k_setup(Tables tb, LaneOrder oc, TableGrid g, int bL, int W, int
         if (t < 2) sa.cnt[t] = 0ull;
         if (t < 17) sa.done[32 * t] = 0u;
     } else if (blk < g.b) {
-        pack2((blk - g.p) * kThreads + t, N + 1, sa.m, (sa.m + 31) / 32, sa.data, sa.bits);
+        pack2(((blk - g.p) * kThreads + t) >> 6, (g.b - g.p) * (kThreads / 64), N + 1, sa.m,
+              (sa.m + 31) / 32, sa.data, sa.bits);
     } else {
         lgamma_table((blk - g.b) * kThreads + t, (g.g - g.b) * kThreads, sa.m, sa.table_r,
                      sa.kind, sa.ess, sa.lgt);
@@ -297,7 +298,6 @@ __global__ void k_scores(int n, int m, const uint8_t *__restrict__ data,
 // order; the wave barriers keep the compiler from moving them). Each lane
 // takes four samples per step, with every load of the step issued before
 // the counts.
-constexpr int kScoreWaveBins = 2048;
 __global__ void __launch_bounds__(kThreads)
 k_scores_w(int n, int m, const uint8_t *__restrict__ data, const uint8_t *__restrict__ arity,
            uint32_t K, int kind, double ess, const uint32_t *__restrict__ famask, int max_bins,
@@ -3378,18 +3378,21 @@ hipError_t launch_add_log(double *logp, const double *log_f, size_t count, hipSt
 // ------------------------------------------- a1: local scores, binary data
 // All-binary data as two bit planes per variable: plane 1 marks the samples
 // with value 1, plane 0 those with value 0 (a value out of range is in
-// neither, and so ignored, as in k_scores). W 32-bit words per plane.
-__device__ void pack2(uint32_t id, int n, int m, int W, const uint8_t *__restrict__ data,
-                      uint32_t *__restrict__ bits) {
-    const uint32_t W2 = (uint32_t)(W + 1) / 2, wave = id >> 6, lane = id & 63;
-    const uint32_t j = wave / W2, w = 2 * (wave - j * W2);
-    if (j >= (uint32_t)n) return;
-    const uint32_t s = w * 32 + lane;
-    const int x = s < (uint32_t)m ? data[(size_t)j * m + s] : 255;
-    const uint64_t zero = __ballot(x == 0), one = __ballot(x == 1);
-    if (lane < 2 && w + lane < (uint32_t)W) {
-        bits[((size_t)j * 2 + 0) * W + w + lane] = (uint32_t)(zero >> (32 * lane));
-        bits[((size_t)j * 2 + 1) * W + w + lane] = (uint32_t)(one >> (32 * lane));
+// neither, and so ignored, as in k_scores). W 32-bit words per plane; a wave
+// takes 64 samples of one variable, then those `step` waves further on (n m
+// samples may be more than 2^32, the most threads of a launch).
+__device__ void pack2(uint32_t wave0, uint32_t step, int n, int m, int W,
+                      const uint8_t *__restrict__ data, uint32_t *__restrict__ bits) {
+    const uint32_t W2 = (uint32_t)(W + 1) / 2, lane = threadIdx.x & 63;
+    for (uint32_t wave = wave0; wave < (uint32_t)n * W2; wave += step) {
+        const uint32_t j = wave / W2, w = 2 * (wave - j * W2);
+        const uint32_t s = w * 32 + lane;
+        const int x = s < (uint32_t)m ? data[(size_t)j * m + s] : 255;
+        const uint64_t zero = __ballot(x == 0), one = __ballot(x == 1);
+        if (lane < 2 && w + lane < (uint32_t)W) {
+            bits[((size_t)j * 2 + 0) * W + w + lane] = (uint32_t)(zero >> (32 * lane));
+            bits[((size_t)j * 2 + 1) * W + w + lane] = (uint32_t)(one >> (32 * lane));
+        }
     }
 }
 
@@ -3755,7 +3758,7 @@ hipError_t launch_setup(const Tables &tb, int bL, int W, int bG, int bA, int d, 
     g.f = g.i + blocks(K);
     g.h = g.f + blocks(1ull << (N + 1 - bL));
     g.p = g.h + 1;
-    g.b = g.p + (sa.bits ? blocks((uint64_t)(N + 1) * ((sa.m + 63) / 64) * 64) : 0);
+    g.b = g.p + (sa.bits ? std::min(blocks((uint64_t)(N + 1) * (((uint64_t)sa.m + 63) / 64) * 64), 16384u) : 0);
     g.g = g.b + (sa.table_r > 0 ? std::min(blocks(10ull * (sa.m + 1)), 1024u) : 0);
     hipLaunchKernelGGL(k_setup, dim3(g.g), dim3(kThreads), 0, st, tb,
                        ord_tables.o[std::min(std::max(d, 0), 8)], g, bL, W, bG, bA, d, (int)N, K,

@@ -371,7 +371,7 @@ static bn_status enqueue_scores(const Plan &P, const bn_problem *p, const uint8_
     sa.kind = kind;
     sa.ess = p->ess;
     sa.bits = binary ? bits : nullptr;
-    sa.table_r = uniform && (binary || tables) ? p->arity[0] : 0;
+    sa.table_r = binary || (uniform && tables && max_bins <= kScoreWaveBins) ? p->arity[0] : 0;
     sa.lgt = lgt;
     HIPCHK(launch_setup(tb, P.bL, P.W, P.bG, P.bA, P.d, P.N, P.K, pb, sa, st));
     HIPCHK(launch_scores(P.n, P.m, dev_data, sa.arity, P.K, kind, p->ess, tb.famask, max_bins,
