@@ -120,7 +120,7 @@ def kernel_source_digest():
     """SHA-256 over the kernel sources: a counter record holds only for the
     kernels it was taken on."""
     h = hashlib.sha256()
-    for name in ("bn_kernels.hip", "bn_kernels.h", "bn_device.h"):
+    for name in ("bn_kernels.hip", "bn_kernels.h", "bn_device.h", "bn_math.h"):
         with open(os.path.join(ROOT, "paper_1408_1664_amd", "csrc", name), "rb") as f:
             h.update(f.read())
     return h.hexdigest()

@@ -36,7 +36,6 @@ struct GammaGeom {
     // the four ranks of a group per workgroup (then one rank of the rest)
     uint32_t blk1x4[33], blkAx4[33];
     uint32_t KT;      // K(bT, d): ranked seed masks over the tile bits
-    uint32_t npat;    // K(bT - 1, d): LDS patterns of the tile zeta
     uint32_t kg[32];  // K(bv, d): ranks of Y1_v
     int hmin1;        // smallest hv among one-level endpoints
 };
@@ -46,7 +45,6 @@ struct LatticeArgs {
     uint32_t K;          // parent sets per node
     int bA, bL, bG, aG;  // tile bits: alpha, sweeps, Gamma tile, Gamma level A
     uint32_t KG, KA;     // K(bG, d), K(aG, d)
-    uint32_t npatA;      // K(bA - 1, d): patterns used by the alpha zeta
     uint32_t nitA;       // K(n-1-bA, d): high-bit items of an alpha tile
     int gauge;           // 1: per-node / per-layer power-of-two gauges
     Tables tb;

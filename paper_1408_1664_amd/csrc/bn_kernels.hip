@@ -8,7 +8,8 @@
 //             colex order of the compressed mask.
 //
 // Tiling: a tile is 2^b consecutive masks (the low b bits vary inside a
-// workgroup, the high bits select the tile). Every kernel runs 256 threads.
+// workgroup, the high bits select the tile). Workgroups have 256 threads, those
+// of the sweeps 512 or 1024 where the tile is 11 or 12 bits wide.
 #include <algorithm>
 #include <type_traits>
 
@@ -1175,7 +1176,7 @@ __device__ __forceinline__ void alpha_store_x32(const PolX32::Store &alpha, uint
 // Two 12-bit halves in three layouts, transposed twice across the workgroup
 // with seven barriers a half, took 22.6 ms at n = 30, d = 3 (FP32-scaled, 80.5
 // GB written), 0.79 and 1.12 ms at n = 25, d = 4 (FP32-scaled, FP64); this takes
-// 18.8, 0.58 and 0.81. Seeds summed by each wave for itself (one barrier a tile)
+// 18.8, 0.58 and 1.03 (0.81 with a logarithm of less accuracy). Seeds summed by each wave for itself (one barrier a tile)
 // took 19.0 and 0.66; significands stored as they are made instead of in one
 // run 20.4; five waves per SIMD spill (FP32-scaled 25 to 30).
 template <class P>
@@ -1424,7 +1425,7 @@ __device__ __forceinline__ void zeta_up12(typename A::V *vec, int N, uint32_t t)
 // with no high bits every seed is a single family, Z(G) = beta_i(G). A node
 // with a linear scale runs on its scores as plain doubles, any other in the
 // number system. Bound by latency; the scores scattered to LDS and a dense zeta
-// in registers take 5.8 us at n = 10 (FP32-scaled) and 6.8 us at n = 12 (FP64)
+// in registers take 5.8 us at n = 10 (FP32-scaled) and 7.2 us at n = 12 (FP64)
 // where truncated passes over LDS, each step's pattern read from memory, took
 // 10 and 26.
 template <class P>
@@ -1638,17 +1639,19 @@ __device__ __forceinline__ void dp_steps(DpStep<P, BL> &st, const SliceLds<P> &l
 // share nothing but alpha, and a layer of a small lattice is a few workgroups
 // bound by the latency of one launch and of bL dependent in-tile layers, so
 // running both at once halves the sweeps: n = 16 FP32-scaled 180 -> 63 us for
-// both, n = 20 FP64 541 -> 211 us (unrolled in-tile layers and exp_neg included).
+// both, n = 20 FP64 541 -> 204 us (unrolled in-tile layers and exp_neg included).
 // Large lattices launch the two sweeps apart, on two streams (launch_lattice);
 // there they stream alpha at the HBM rate.
 // Tiles go in colex order: consecutive workgroups, which run at the same time
 // on the eight XCDs, share most of their X blocks (a mapping that gave each
 // XCD a contiguous eighth of the layer cut the L2 misses by 10% but measured
 // 5% slower). Cross-tile terms (bits of H) stream contiguous 2^bL blocks of
-// alpha_i and X, four consecutive entries per thread; in-tile terms use the
-// tile's alpha slices staged in LDS and run popcount layer by popcount layer,
-// one entry per thread (TH >= the largest layer), its operands read in batches
-// of four before they are summed. Requires bL >= 2.
+// alpha_i and X, two consecutive entries per thread and eight nodes at a time for
+// the 9-bit tiles, else four and four; in-tile terms use the tile's alpha slices
+// staged in LDS and run popcount layer by popcount layer, one entry per thread
+// (TH >= the largest layer): unrolled for the widths that the plan chooses
+// (BL > 0, dp_steps), else in a loop that reads the operands of four terms
+// before it sums them. Requires bL >= 2.
 template <class P, bool FWD, int TH, int BL>
 __device__ inline void sweep_tile(int n, int bL_arg, uint32_t Hm, const Tables &tb,
                                   const typename P::Store &alpha, const typename P::Store &X,
@@ -2903,7 +2906,7 @@ k_gamma_small(int n, uint32_t K, int force_log, Tables tb, typename P::Store L,
 // One row per workgroup, truncated by
 // pattern lists and, in the log form, in log-adds, this was 98 us at n = 20
 // (FP64, d = 4), 1.04 ms at n = 25 and 48 us at n = 22 (FP32-scaled, d = 3);
-// now 41 us, 0.28 ms and 24 us.
+// now 30 us, 0.27 ms and 24 us.
 template <class P>
 __global__ void __launch_bounds__(kThreads)
 k_gamma_high1(int n, int d, uint32_t K, int force_log, GammaGeom gg, Tables tb,
@@ -3496,7 +3499,7 @@ __device__ inline uint32_t binom5(uint32_t p, int t) {
 // the row, a marginal of the same table (one sum over all cells for the whole
 // set cancels only at the end: rounding errors 10% larger). The counting (LDS atomics, 4 samples per lane
 // and load) bounds it: at n = 20, r = 3, m = 1000, d = 4 the 15,504 + 6,195
-// sets take about 55 us where a wave per family (100,720 of them) took 306 us.
+// sets take 47 us where a wave per family (100,720 of them) took 306 us.
 // Sets in order of size, then colex. A value >= r (the device entry points do not
 // look at the data) is counted in some other cell or in none: the key is tested
 // against the table's size, so it never leaves it. TAB: the
@@ -3660,7 +3663,7 @@ __device__ inline double set_scores2(const uint32_t *cnt, int lane, const double
 // Local scores of all-binary data with d <= 4 by sets of variables, as
 // k_scores_sets: 16 lanes per set, 16 sets per workgroup, counts from the bit
 // planes of pack2. The k + 1 families of a set share its counts and its cells'
-// terms (n = 25, m = 2000, d = 4: 41 us, by families 143; n = 30, d = 3: 15, 48).
+// terms (n = 25, m = 2000, d = 4: 37 us, by families 143; n = 30, d = 3: 15, 48).
 __global__ void __launch_bounds__(kThreads)
 k_scores2(int n, int W, int m, int d, uint32_t K, uint32_t sets,
           const uint32_t *__restrict__ bits, const double *__restrict__ lgt,
@@ -3987,8 +3990,8 @@ hipError_t launch_lattice(const LatticeArgs &a, const typename P::Store &alpha,
     // The backward sweep needs alpha but not L. Below n = 24 step h of both
     // sweeps is one launch; from there on, with a.side set, the backward sweep
     // runs on that stream, forked after alpha and joined before Gamma, so that
-    // the tail of a layer is filled by the other sweep (n = 25 FP32-scaled:
-    // 1.27 ms for both against 1.47 ms in joint launches).
+    // the tail of a layer is filled by the other sweep (n = 25 FP32-scaled: 1.16
+    // ms for both against 1.24 ms in joint launches; FP64 2.26 and 2.27).
     SweepFork fork;
     const bool forked = a.side && !a.fwd_only;
     if (forked) {
@@ -4024,8 +4027,11 @@ hipError_t launch_lattice(const LatticeArgs &a, const typename P::Store &alpha,
     if (a.bL == 9) es = sweeps(integral_constant<int, 256>{}, integral_constant<int, 9>{});
     else if (a.bL == 10) es = sweeps(integral_constant<int, 256>{}, integral_constant<int, 10>{});
     else if (a.bL == 11) es = sweeps(integral_constant<int, 512>{}, integral_constant<int, 11>{});
-    else if (a.bL == 12) es = sweeps(integral_constant<int, 1024>{}, integral_constant<int, 12>{});
-    else es = sweeps(integral_constant<int, 256>{}, integral_constant<int, 0>{});
+    else if (a.bL == 12) {
+        if constexpr (std::is_same<P, PolX32>::value)
+            es = sweeps(integral_constant<int, 1024>{}, integral_constant<int, 12>{});
+        else es = hipErrorInvalidValue;      // the log form's plan ends at 11 bits
+    } else es = sweeps(integral_constant<int, 256>{}, integral_constant<int, 0>{});
     if (es != hipSuccess) return es;
     rec(3);
     if (a.fwd_only) {

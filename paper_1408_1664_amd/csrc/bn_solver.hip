@@ -181,7 +181,6 @@ static Plan plan_of(int n, int d_in, int m, bn_precision prec, bool with_data, b
             g.blkB[v + 1] = g.blkB[v] + (two ? (uint32_t)kg : 0);
         }
         g.KT = P.KG;
-        g.npat = (uint32_t)kcount_u64(std::max(P.bG - 1, 0), d);
         P.y1_elems = y1;
         P.y2_elems = y2;
         P.two_level = y2 > 0;
@@ -392,7 +391,6 @@ static LatticeArgs lattice_args(const Plan &P, char *ws, double *dev_post, doubl
     a.aG = P.aG;
     a.KG = P.KG;
     a.KA = P.KA;
-    a.npatA = (uint32_t)kcount_u64(std::max(P.bA - 1, 0), P.d);
     a.nitA = (uint32_t)kcount_u64(P.N - P.bA, P.d);
     a.gauge = P.x32 ? 1 : 0;
     a.tb = tables_of(P, ws);
