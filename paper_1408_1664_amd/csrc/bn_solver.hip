@@ -113,8 +113,9 @@ static Plan plan_of(int n, int d_in, int m, bn_precision prec, bool with_data, b
     // large, HBM-bound sweeps; n = 16 63 us against 67 with 10 and 70 with 11
     // bits, n = 22 254 against 269 and 290). Log form: 11 bits where that saves
     // a launch (n = 11, 12: 46 against 54 us before the layers were unrolled),
-    // else 10, whose cross terms keep all 256 threads busy (n = 20 211 us
-    // against 213 with 9 and 228 with 11 bits).
+    // else 10, whose cross terms keep all 256 threads busy (n = 20 209 us
+    // against 204 with 9 and 226 with 11 bits, n = 25 2.26 ms against 2.47 and
+    // 3.13).
     P.bL = P.x32 ? (n <= 12 ? n : n <= 14 ? 11 : 9) : std::min(n, n <= 12 ? 11 : 10);
     P.bG = n >= 12 ? 12 : n;      // Gamma tile: 12 bits, or the whole lattice when smaller
     P.aG = 12;
