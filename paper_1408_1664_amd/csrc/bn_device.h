@@ -203,8 +203,9 @@ struct PolLog {
         *T = Anchor{mx, -1000 - (int)rint(fmax(a - mx, -4000.0) * 1.4426950408889634074)};
         return true;
     }
+    // 0 for a zero (-inf): the scales' powers of two lie within 2^-1000 .. 2^960
     __device__ static inline double to_lin(V x, Anchor T) {
-        return x > -1e300 ? exp_scaled(x - T.off, T.sh) : 0.0;
+        return exp_scaled(x - T.off, T.sh);
     }
     // a scale that puts the value 2^e2 at 2^940 (room for 4096 such terms)
     __device__ static inline Anchor anchor_high(int e2) {

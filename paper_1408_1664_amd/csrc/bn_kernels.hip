@@ -2758,7 +2758,7 @@ k_gamma_highA12_log(int n, int d, uint32_t KA, int force_trunc, GammaGeom gg, Ta
         return;
     }
 #pragma unroll
-    for (int r = 0; r < 16; ++r) g[r] = g[r] > -1e300 ? exp_below(g[r] - mx, 960) : 0.0;
+    for (int r = 0; r < 16; ++r) g[r] = exp_below(g[r] - mx, 960);
     dense_zeta_down12_regs<Lin64>(g, vec, t);
     bool small = false;
     for (uint32_t pi = t; pi < KA; pi += kThreads) {
@@ -2873,8 +2873,7 @@ k_gamma_small(int n, uint32_t K, int force_log, Tables tb, typename P::Store L,
         if (!force_log && mx > -1e300) {
             double y[16];
 #pragma unroll
-            for (int r = 0; r < 16; ++r)
-                y[r] = g[r] > -1e300 ? exp_below(g[r] - mx, 960) : 0.0;
+            for (int r = 0; r < 16; ++r) y[r] = exp_below(g[r] - mx, 960);
             masked_zeta_down12<Lin64>(y, vec, bits, t);
             bool small = false;
             each([&](uint32_t, uint32_t at) { small = small || !(vec[at] >= 0x1p-1000); });
@@ -2991,7 +2990,7 @@ k_gamma_high1(int n, int d, uint32_t K, int force_log, GammaGeom gg, Tables tb,
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const double M = rowmax[row_of((r << 8) | t)] * 0.69314718055994530942;
-                g[r] = g[r] > -1e300 ? exp_below(g[r] - M, 960) : 0.0;
+                g[r] = exp_below(g[r] - M, 960);
             }
         }
     }

@@ -5,7 +5,7 @@
 // (largest error in units of the last place over 4 million arguments per
 // range, device library in parentheses): e^x 0.87 (0.88), ln y 0.63 (0.64),
 // ln(1 + x) 0.63 (0.64). At n = 25, d = 4 the log form's alpha tile takes 1.41 ms
-// with the library's functions and 1.03 with these, its Gamma tile 2.18 and 2.02,
+// with the library's functions and 1.03 with these, its Gamma tile 2.18 and 1.84,
 // the sweeps' kernels 5.03 and 4.55. The host form is for the tests.
 #pragma once
 #include <math.h>
