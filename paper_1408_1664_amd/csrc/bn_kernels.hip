@@ -1176,9 +1176,10 @@ __device__ __forceinline__ void alpha_store_x32(const PolX32::Store &alpha, uint
 // Two 12-bit halves in three layouts, transposed twice across the workgroup
 // with seven barriers a half, took 22.6 ms at n = 30, d = 3 (FP32-scaled, 80.5
 // GB written), 0.79 and 1.12 ms at n = 25, d = 4 (FP32-scaled, FP64); this takes
-// 18.8, 0.58 and 1.03 (0.81 with a logarithm of less accuracy). Seeds summed by each wave for itself (one barrier a tile)
-// took 19.0 and 0.66; significands stored as they are made instead of in one
-// run 20.4; five waves per SIMD spill (FP32-scaled 25 to 30).
+// 18.8, 0.58 and 1.03 (0.81 with a logarithm of less accuracy). Seeds summed by
+// each wave for itself (one barrier a tile) took 19.0 and 0.66; significands
+// stored as they are made instead of in one run 20.4; five waves per SIMD spill
+// (FP32-scaled 25 to 30).
 template <class P>
 __device__ __forceinline__ void alpha_lin_tiles(
     int n, int d, uint32_t KS, int tl, const double *__restrict__ Zs,
@@ -2902,10 +2903,9 @@ k_gamma_small(int n, uint32_t K, int force_log, Tables tb, typename P::Store L,
 // workgroup runs the zeta in log-adds. So does one with an entry beyond 3.6e8
 // nats (many millions of samples, or a prior of that size), whose binary
 // exponent the 32-bit row maxima do not hold beside their mark of an empty row.
-// One row per workgroup, truncated by
-// pattern lists and, in the log form, in log-adds, this was 98 us at n = 20
-// (FP64, d = 4), 1.04 ms at n = 25 and 48 us at n = 22 (FP32-scaled, d = 3);
-// now 30 us, 0.27 ms and 24 us.
+// One row per workgroup, truncated by pattern lists and, in the log form, in
+// log-adds, this was 98 us at n = 20 (FP64, d = 4), 1.04 ms at n = 25 and 48 us
+// at n = 22 (FP32-scaled, d = 3); now 29 us, 0.25 ms and 24 us.
 template <class P>
 __global__ void __launch_bounds__(kThreads)
 k_gamma_high1(int n, int d, uint32_t K, int force_log, GammaGeom gg, Tables tb,
@@ -3493,17 +3493,17 @@ __device__ inline uint32_t binom5(uint32_t p, int t) {
 // 1 .. d + 1 variables instead of one per family. The families (i, U - i) of a
 // set U of k + 1 variables share their table of r^(k+1) counts, and with one
 // arity their cell hyperparameters too, so the table and its cells' terms
-// lgamma(a_jk + N_jk) - lgamma(a_jk) are taken once for all k + 1 of them (HELD: in LDS);
-// each family then sums them row by row, with lgamma(a_j) - lgamma(a_j + N_j) of
-// the row, a marginal of the same table (one sum over all cells for the whole
-// set cancels only at the end: rounding errors 10% larger). The counting (LDS atomics, 4 samples per lane
-// and load) bounds it: at n = 20, r = 3, m = 1000, d = 4 the 15,504 + 6,195
-// sets take 47 us where a wave per family (100,720 of them) took 306 us.
-// Sets in order of size, then colex. A value >= r (the device entry points do not
-// look at the data) is counted in some other cell or in none: the key is tested
-// against the table's size, so it never leaves it. TAB: the
-// log-gamma values come from lgamma_table, else each is evaluated in place
-// (the same values).
+// lgamma(a_jk + N_jk) - lgamma(a_jk) are taken once for all k + 1 of them (HELD:
+// in LDS); each family then sums them row by row, with lgamma(a_j) -
+// lgamma(a_j + N_j) of the row, a marginal of the same table (one sum over all
+// cells for the whole set cancels only at the end: rounding errors 10% larger).
+// The counting (LDS atomics, 4 samples per lane and load) bounds it: at n = 20, r
+// = 3, m = 1000, d = 4 the 15,504 + 6,195 sets take 47 us where a wave per family
+// (100,720 of them) took 306 us. Sets in order of size, then colex. A value >= r
+// (the device entry points do not look at the data) is counted in some other cell
+// or in none: the key is tested against the table's size, so it never leaves it.
+// TAB: the log-gamma values come from lgamma_table, else each is evaluated in
+// place (the same values).
 template <bool TAB, bool HELD>
 __global__ void __launch_bounds__(kThreads)
 k_scores_sets(int n, int m, int d, const uint8_t *__restrict__ data, int r, uint32_t K,
@@ -3760,7 +3760,8 @@ hipError_t launch_setup(const Tables &tb, int bL, int W, int bG, int bA, int d, 
     g.f = g.i + blocks(K);
     g.h = g.f + blocks(1ull << (N + 1 - bL));
     g.p = g.h + 1;
-    g.b = g.p + (sa.bits ? std::min(blocks((uint64_t)(N + 1) * (((uint64_t)sa.m + 63) / 64) * 64), 16384u) : 0);
+    const uint64_t planes = (uint64_t)(N + 1) * (((uint64_t)sa.m + 63) / 64) * 64;
+    g.b = g.p + (sa.bits ? std::min(blocks(planes), 16384u) : 0);
     g.g = g.b + (sa.table_r > 0 ? std::min(blocks(10ull * (sa.m + 1)), 1024u) : 0);
     hipLaunchKernelGGL(k_setup, dim3(g.g), dim3(kThreads), 0, st, tb,
                        ord_tables.o[std::min(std::max(d, 0), 8)], g, bL, W, bG, bA, d, (int)N, K,

@@ -61,8 +61,9 @@ BN_MATH double exp_neg(double x) { return exp_below(x, 0); }
 
 // k ln 2 + ln(1 + f + flo) for sqrt(1/2) <= 1 + f <= sqrt(2) and an integer k,
 // flo a rounding error of f: with s = f / (2 + f) and z = s^2,
-// ln(1 + f) = f - f^2 / 2 + s (f^2 / 2 + z p(z)), p the Chebyshev interpolant of
-// degree 7 of (2 atanh(s) / s - 2) / z (error below 2^-60). The large terms are
+// ln(1 + f) = f - f^2 / 2 + s (f^2 / 2 + z p(z)) (the form that fdlibm's log has),
+// p the Chebyshev interpolant of degree 7 of (2 atanh(s) / s - 2) / z (error below
+// 2^-60). The large terms are
 // summed with their rounding errors and the quotient s is kept unrounded where
 // it counts, so that the result is exact for k = 0 and small f, where it is f.
 BN_MATH double log_parts(double f, double flo, double k) {
