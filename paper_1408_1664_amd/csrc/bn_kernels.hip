@@ -3419,20 +3419,21 @@ __device__ inline void count_scatter(uint32_t *cnt, int lane) {
     }
 }
 
-// Counts of one family of k parents over words w = lane, lane + 16, ...:
+// Counts of one family of k parents over words w = lane, lane + LS, ...:
 // cell (c << 1) | v, c the parents' values as bits, v the child's value, is
-// the popcount of the AND of the matching planes. The 16 lanes' partial
+// the popcount of the AND of the matching planes. Of LS = 64 lanes those that
+// agree in their low four bits add their counts first; 16 lanes' partial
 // counts are then summed and scattered by a butterfly that, at lane bit b,
 // halves the configurations a lane keeps by configuration bit b (b < k), or
 // sums all it holds (b >= k): lane L < 2^k ends with the two counts of
 // configuration L in cnt[0] and cnt[1].
-template <int KP>
+template <int KP, int LS>
 __device__ inline void count_cells2(const uint32_t *__restrict__ bits, int W, int lane,
                                     int child, const int *par, uint32_t *cnt) {
     constexpr int NC = 2 << KP;
 #pragma unroll
     for (int c = 0; c < NC; ++c) cnt[c] = 0;
-    for (int w = lane; w < W; w += 16) {
+    for (int w = lane; w < W; w += LS) {
         uint32_t a[NC];
         a[0] = bits[((size_t)child * 2 + 0) * W + w];
         a[1] = bits[((size_t)child * 2 + 1) * W + w];
@@ -3451,6 +3452,14 @@ __device__ inline void count_cells2(const uint32_t *__restrict__ bits, int W, in
         }
 #pragma unroll
         for (int c = 0; c < NC; ++c) cnt[c] += __popc(a[c]);
+    }
+    if constexpr (LS == 64) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            cnt[c] += __shfl_xor(cnt[c], 32);
+            cnt[c] += __shfl_xor(cnt[c], 16);
+        }
+        lane &= 15;
     }
     count_scatter<KP, 3>(cnt, lane);
     count_scatter<KP, 2>(cnt, lane);
@@ -3660,15 +3669,17 @@ __device__ inline double set_scores2(const uint32_t *cnt, int lane, const double
 }
 
 // Local scores of all-binary data with d <= 4 by sets of variables, as
-// k_scores_sets: 16 lanes per set, 16 sets per workgroup, counts from the bit
+// k_scores_sets: LS lanes per set (16, or a wave where there are few sets and many
+// samples; its four groups of 16 then all have the scores), counts from the bit
 // planes of pack2. The k + 1 families of a set share its counts and its cells'
 // terms (n = 25, m = 2000, d = 4: 37 us, by families 143; n = 30, d = 3: 15, 48).
+template <int LS>
 __global__ void __launch_bounds__(kThreads)
 k_scores2(int n, int W, int m, int d, uint32_t K, uint32_t sets,
           const uint32_t *__restrict__ bits, const double *__restrict__ lgt,
           double *__restrict__ out) {
-    const int grp = threadIdx.x >> 4, lane = threadIdx.x & 15;
-    uint32_t c = blockIdx.x * 16 + grp;
+    const int lane = threadIdx.x & 15, first = threadIdx.x & (LS - 1);
+    uint32_t c = blockIdx.x * (kThreads / LS) + threadIdx.x / LS;
     const bool live = c < sets;
     if (!live) c = 0;                            // dead groups keep the ballots whole
     int k1 = 1;
@@ -3693,13 +3704,13 @@ k_scores2(int n, int W, int m, int d, uint32_t K, uint32_t sets,
     uint32_t cnt[32];
     double sc = 0.0;
     switch (k1) {
-        case 1: count_cells2<0>(bits, W, lane, var[0], var, cnt); sc = set_scores2<0>(cnt, lane, lgt, m + 1); break;
-        case 2: count_cells2<1>(bits, W, lane, var[1], var, cnt); sc = set_scores2<1>(cnt, lane, lgt, m + 1); break;
-        case 3: count_cells2<2>(bits, W, lane, var[2], var, cnt); sc = set_scores2<2>(cnt, lane, lgt, m + 1); break;
-        case 4: count_cells2<3>(bits, W, lane, var[3], var, cnt); sc = set_scores2<3>(cnt, lane, lgt, m + 1); break;
-        default: count_cells2<4>(bits, W, lane, var[4], var, cnt); sc = set_scores2<4>(cnt, lane, lgt, m + 1); break;
+        case 1: count_cells2<0, LS>(bits, W, first, var[0], var, cnt); sc = set_scores2<0>(cnt, lane, lgt, m + 1); break;
+        case 2: count_cells2<1, LS>(bits, W, first, var[1], var, cnt); sc = set_scores2<1>(cnt, lane, lgt, m + 1); break;
+        case 3: count_cells2<2, LS>(bits, W, first, var[2], var, cnt); sc = set_scores2<2>(cnt, lane, lgt, m + 1); break;
+        case 4: count_cells2<3, LS>(bits, W, first, var[3], var, cnt); sc = set_scores2<3>(cnt, lane, lgt, m + 1); break;
+        default: count_cells2<4, LS>(bits, W, first, var[4], var, cnt); sc = set_scores2<4>(cnt, lane, lgt, m + 1); break;
     }
-    if (lane < k1) {
+    if (first < k1) {
         uint32_t rank = 0;
         int i = 0, size = 0;
         for (int t = 0; t < k1 - 1; ++t) rank += binom5((uint32_t)(n - 1), t);
@@ -3797,8 +3808,18 @@ hipError_t launch_scores(int n, int m, const uint8_t *data, const uint8_t *arity
         // all-binary data, d <= 4: counts from the bit planes
         const int W = (m + 31) / 32;
         const uint32_t sets = host_kcount(n, d + 1) - 1;
-        hipLaunchKernelGGL(k_scores2, dim3((sets + 15) / 16), dim3(kThreads), 0, st, n, W, m, d, K,
-                           sets, (const uint32_t *)bits, (const double *)lgt, out);
+        // A wave per set where 16 lanes each would leave CUs without a workgroup and
+        // the samples are many enough to pay for the larger sum (m = 10^6, n = 8, d = 4:
+        // score phase 327 us with 64 lanes, 1271 with 16, 1176 for a family each; m =
+        // 8400, n = 10, d = 3: 26, 32 and 46; at m = 2000 they are equal).
+        const bool wide = (sets + 15) / 16 <= 256 && W >= 64;
+        const uint32_t per = wide ? 4 : 16;
+        auto go = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3((sets + per - 1) / per), dim3(kThreads), 0, st, n, W, m,
+                               d, K, sets, (const uint32_t *)bits, (const double *)lgt, out);
+        };
+        if (wide) go(k_scores2<64>);
+        else go(k_scores2<16>);
         BN_CHECK_LAUNCH();
         return hipSuccess;
     }

@@ -71,3 +71,13 @@ def test_sets_score_as_families_do(n, r, d, m, kind):
     L = [bn.num_parent_sets(n, k) for k in range(-1, d + 1)]
     at = np.concatenate([np.arange(K[k], K[k] + L[k + 1] - L[k]) for k in range(d + 1)])
     assert np.array_equal(got, mixed[:n, at])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,d,m", [(2, 1, 2016), (2, 1, 2017), (3, 2, 2049), (8, 4, 4096), (10, 3, 2081),
+                                   (13, 4, 2048), (13, 4, 2016), (16, 4, 2048)])
+def test_a_wave_per_binary_set(n, d, m):
+    """Few binary sets with many samples take a wave each (from 64 words of
+    samples on): the same bits as family by family, at word counts around the
+    64 lanes and on both sides of the number of sets."""
+    test_sets_score_as_families_do(n, 2, d, m, "bdeu")
