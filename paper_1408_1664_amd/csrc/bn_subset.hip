@@ -25,10 +25,12 @@
 // running pass and above) is zero as long as it has more than d ones there, so
 // a pass neither reads such rows nor runs a workgroup whose bits above the pass
 // have more than d ones: nobody reads what it would have written until a later
-// pass writes it. Every entry is still written, once, by the last pass, which
-// takes as many bits as it can (up to 9); what the others move shrinks with
-// K(bits above, d) / 2^(bits above). At 2^27 entries, d = 3, the transform moves
-// 1.8 GB instead of 6.4: 1.17 -> 0.33 ms; the sums are those of the dense passes.
+// pass writes it. Every entry is still written by the last pass; what the others
+// move shrinks with K(bits above, d) / 2^(bits above), most where the last pass
+// takes as many bits as it can. Where this saves too little (split_bits) the
+// passes are those of the dense form, after a tile pass that clears the entries of
+// more than d ones. At 2^27 entries, d = 3, the transform moves 1.8 GB instead of
+// 6.4: 1.17 -> 0.33 ms; the sums are those of the dense passes.
 #include <hip/hip_runtime.h>
 
 #include <stdint.h>
@@ -50,7 +52,11 @@ __device__ inline uint32_t padx16(uint32_t x) { return x + (x >> 4); }
 // a + sign * b (sign -1: the Moebius step, doubles only).
 struct F64 {
     using V = double;
+    using Raw = double;                // an entry as it lies in memory
     double *x;
+    __device__ Raw raw(uint64_t i) const { return x[i]; }
+    __device__ static Raw raw_zero() { return 0.0; }
+    __device__ static V decode(Raw r) { return r; }
     __device__ V load(uint64_t i) const { return x[i]; }
     __device__ void store(uint64_t i, V v) const { x[i] = v; }
     __device__ static V zero() { return 0.0; }
@@ -58,8 +64,12 @@ struct F64 {
 };
 struct X32F {
     using V = X32;
+    using Raw = PolX32::Raw;
     PolX32::Store s;
     unsigned long long *cnt;   // [0] saturated, [1] flushed (null: not counted)
+    __device__ Raw raw(uint64_t i) const { return PolX32::load_raw(s, i); }
+    __device__ static Raw raw_zero() { return Raw{0.0f, 0u}; }
+    __device__ static V decode(Raw r) { return PolX32::decode_raw(r); }
     __device__ V load(uint64_t i) const { return PolX32::load(s, i); }
     __device__ void store(uint64_t i, V v) const { PolX32::store(s, i, v, cnt); }
     __device__ static V zero() { return PolX32::zero(); }
@@ -77,13 +87,35 @@ __device__ inline void reg_step(typename F::V *v, int q, double sign) {
     }
 }
 
+// v[r] = the entry at base + r 2^j0 for the r of at most `most` ones, zero for the
+// others, which are not read. All loads of one number of ones go out together and
+// none is decoded before the last has gone out (one predicated load at a time,
+// each waited for, made the FP32-scaled form slower than without skipping).
+template <class F, int LB>
+__device__ inline void load_rows(const F &x, uint64_t base, int j0, int most, typename F::V *v) {
+    constexpr int NR = 1 << LB;
+    typename F::Raw raw[NR];
+#pragma unroll
+    for (int r = 0; r < NR; ++r) raw[r] = F::raw_zero();
+#pragma unroll
+    for (int k = 0; k <= LB; ++k) {
+        if (k <= most) {
+#pragma unroll
+            for (int r = 0; r < NR; ++r)
+                if (__builtin_popcount(r) == k) raw[r] = x.raw(base + ((uint64_t)r << j0));
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < NR; ++r) v[r] = F::decode(raw[r]);
+}
+
 template <class F, bool UP>
 __global__ void __launch_bounds__(kT)
-k_subset_tile(F x, double sign, int trunc_d) {
+k_subset_tile(F x, double sign, int trunc_d, int skip_d) {
     using V = typename F::V;
     __shared__ V gb[4096 + 256];
     const int t = threadIdx.x;
-    if (trunc_d >= 0 && __popc(blockIdx.x) > trunc_d) return;   // no input in the tile
+    if (__popc(blockIdx.x) > skip_d) return;     // no input in the tile, and nobody reads it
     const uint64_t base = (uint64_t)blockIdx.x << 12;
     V v[16];
     // layout A: y = t * 16 + r, bits 0..3 in registers
@@ -122,7 +154,7 @@ k_subset_tile(F x, double sign, int trunc_d) {
 // + t splits into lo (the low j0 bits) and hi (the bits above the group);
 // its registers hold the 2^B entries hi | r << j0 | lo. Consecutive threads
 // take consecutive lo, so every register load and store is one 2 KB run.
-template <class F, bool UP, int B>
+template <class F, bool UP, int B, bool TRUNC>
 __global__ void __launch_bounds__(kT)
 k_subset_bits(F x, int j0, double sign, int trunc_d) {
     constexpr int NR = 1 << B;
@@ -130,11 +162,14 @@ k_subset_bits(F x, int j0, double sign, int trunc_d) {
     const uint64_t lo = col & ((1ull << j0) - 1);
     const uint64_t hi = (col >> j0) << (j0 + B);
     typename F::V v[NR];
-    const int left = trunc_d >= 0 ? trunc_d - __popcll(hi) : B;   // ones a row may add
-    if (left < 0) return;
+    if constexpr (TRUNC) {
+        const int left = trunc_d - __popcll(hi);       // ones a row may add
+        if (left < 0) return;
+        load_rows<F, B>(x, hi | lo, j0, left, v);
+    } else {
 #pragma unroll
-    for (int r = 0; r < NR; ++r)
-        v[r] = __builtin_popcount(r) <= left ? x.load(hi | ((uint64_t)r << j0) | lo) : F::zero();
+        for (int r = 0; r < NR; ++r) v[r] = x.load(hi | ((uint64_t)r << j0) | lo);
+    }
 #pragma unroll
     for (int q = 0; q < B; ++q) reg_step<F, UP, NR>(v, q, sign);
 #pragma unroll
@@ -171,11 +206,7 @@ k_subset_group(F x, int j0, double sign, int trunc_d) {
     if constexpr (TRUNC) {
         const int left = trunc_d - __popcll(hi);       // ones a row may add
         if (left < 0) return;                          // whole workgroups
-        const int mine = left - __popc(tp);
-#pragma unroll
-        for (int r = 0; r < 32; ++r)
-            v[r] = __builtin_popcount(r) <= mine ? x.load(xb + ((uint64_t)((tp << 5) | r) << j0))
-                                                 : F::zero();
+        load_rows<F, 5>(x, xb + ((uint64_t)(tp << 5) << j0), j0, left - __popc(tp), v);
     } else {
 #pragma unroll
         for (int r = 0; r < 32; ++r) v[r] = x.load(xb + ((uint64_t)((tp << 5) | r) << j0));
@@ -212,8 +243,27 @@ k_subset_group(F x, int j0, double sign, int trunc_d) {
     }
 }
 
-template <class F, bool UP, int LW, bool TRUNC>
-void launch_group(int B, int nbits, F x, int j0, double sign, int trunc_d, hipStream_t st) {
+// One pass over bits j0 .. j0 + B - 1.
+template <class F, bool UP, bool TRUNC>
+void launch_pass(int B, int nbits, F x, int j0, double sign, int trunc_d, hipStream_t st) {
+    if (B < 5) {
+        // 2^(nbits - B) columns, 256 per workgroup (nbits - B >= 12)
+        auto go = [&](auto bits) {
+            hipLaunchKernelGGL((k_subset_bits<F, UP, decltype(bits)::value, TRUNC>),
+                               dim3((unsigned)(1ull << (nbits - B - 8))), dim3(kT), 0, st, x, j0,
+                               sign, trunc_d);
+        };
+        switch (B) {
+            case 1: go(std::integral_constant<int, 1>{}); break;
+            case 2: go(std::integral_constant<int, 2>{}); break;
+            case 3: go(std::integral_constant<int, 3>{}); break;
+            default: go(std::integral_constant<int, 4>{}); break;
+        }
+        return;
+    }
+    // runs of 32 doubles (256 B); in the FP32-scaled form runs of 64 entries, so
+    // that the byte plane too moves whole 64-byte segments
+    constexpr int LW = std::is_same<F, X32F>::value ? 6 : 5;
     const dim3 grid((unsigned)(1ull << (nbits - B - LW)));
     auto go = [&](auto bits) {
         constexpr int b = decltype(bits)::value;
@@ -227,6 +277,50 @@ void launch_group(int B, int nbits, F x, int j0, double sign, int trunc_d, hipSt
         case 8: go(std::integral_constant<int, 8>{}); break;
         default: go(std::integral_constant<int, 9>{}); break;
     }
+}
+
+// The share of b-bit patterns that have at most d ones.
+inline double share(int b, int d) {
+    double c = 1.0, s = 0.0;
+    for (int k = 0; k <= d && k <= b; ++k) {
+        s += c;
+        c = c * (b - k) / (k + 1);
+    }
+    return s / (double)(1ull << b);
+}
+
+// The bits above the tile in passes of at most 9, into B: split evenly, or, for a
+// truncated transform, with full passes last if that moves less; returns whether
+// rows without inputs are to be skipped. A skipping pass reads the rows of at most
+// d ones in its bits and those above, and writes those of at most d ones above it;
+// 9 bits at once run at 0.8 of the rate of fewer in the FP32-scaled form (3.7
+// against 4.5 TB/s). Skipping less than 15% of what all passes move is not worth
+// its branches (2^17 entries FP32-scaled, d = 3: 11.4 against 10.9 us). 2^28
+// entries, dense and now: FP64 d = 2 2.47 and 0.52 ms, d = 7 2.47 and 1.89;
+// FP32-scaled d = 3 1.71 and 0.68, d = 12 1.70 both (2.49 with full passes last
+// and the loads one by one); 2^22 entries d = 12 38.5 us both (54.2).
+template <class F>
+bool split_bits(int rem, int trunc_d, int *B) {
+    const int np = (rem + 8) / 9;
+    int full[4];
+    for (int i = 0; i < np; ++i) {
+        B[i] = rem / np + (i < rem % np ? 1 : 0);
+        full[i] = i ? 9 : rem - 9 * (np - 1);
+    }
+    if (trunc_d < 0) return false;
+    auto moved = [&](const int *b, int d) {
+        double s = 2.0 * share(rem, d);                 // the tiles
+        for (int i = 0, above = rem; i < np; ++i) {
+            const double m = share(above, d) + share(above - b[i], d);
+            s += b[i] == 9 && std::is_same<F, X32F>::value ? 1.25 * m : m;
+            above -= b[i];
+        }
+        return s;
+    };
+    const int *best = moved(full, trunc_d) < moved(B, trunc_d) ? full : B;
+    if (moved(best, trunc_d) > 0.85 * moved(B, rem)) return false;
+    for (int i = 0; i < np; ++i) B[i] = best[i];
+    return true;
 }
 
 // nbits < 12: the whole array in LDS, one step per bit, one pair of entries per
@@ -260,42 +354,17 @@ hipError_t run(F x, int nbits, double sign, int trunc_d, hipStream_t st) {
                            trunc_d);
         return hipGetLastError();
     }
+    int bits[4];
+    const bool skip = split_bits<F>(nbits - 12, UP ? trunc_d : -1, bits);
     hipLaunchKernelGGL((k_subset_tile<F, UP>), dim3((unsigned)(1ull << (nbits - 12))), dim3(kT), 0,
-                       st, x, sign, trunc_d);
+                       st, x, sign, trunc_d, skip ? trunc_d : 32);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const int rem = nbits - 12;
-    // at most 9 bits per pass, split evenly; truncated, the first pass takes what
-    // full later ones leave
-    const int npass = (rem + 8) / 9;
-    for (int i = 0, j0 = 12; i < npass; ++i) {
-        const int B = trunc_d >= 0 ? (i ? 9 : rem - 9 * (npass - 1))
-                                   : rem / npass + (i < rem % npass ? 1 : 0);
-        if (B >= 5) {
-            // runs of 32 doubles (256 B); in the FP32-scaled form runs of 64
-            // entries, so that the byte plane too moves whole 64-byte segments
-            constexpr int LW = std::is_same<F, X32F>::value ? 6 : 5;
-            if (UP && trunc_d >= 0)
-                launch_group<F, UP, LW, UP>(B, nbits, x, j0, sign, trunc_d, st);
-            else
-                launch_group<F, UP, LW, false>(B, nbits, x, j0, sign, -1, st);
-        } else {
-            // 2^(nbits - B) columns, 256 per workgroup (nbits - B >= 12)
-            const dim3 grid((unsigned)(1ull << (nbits - B - 8)));
-            switch (B) {
-                case 1: hipLaunchKernelGGL((k_subset_bits<F, UP, 1>), grid, dim3(kT), 0, st, x, j0, sign,
-                                       trunc_d); break;
-                case 2: hipLaunchKernelGGL((k_subset_bits<F, UP, 2>), grid, dim3(kT), 0, st, x, j0, sign,
-                                       trunc_d); break;
-                case 3: hipLaunchKernelGGL((k_subset_bits<F, UP, 3>), grid, dim3(kT), 0, st, x, j0, sign,
-                                       trunc_d); break;
-                default: hipLaunchKernelGGL((k_subset_bits<F, UP, 4>), grid, dim3(kT), 0, st, x, j0, sign,
-                                       trunc_d); break;
-            }
-        }
+    for (int i = 0, j0 = 12; j0 < nbits; j0 += bits[i++]) {
+        if (skip) launch_pass<F, UP, UP>(bits[i], nbits, x, j0, sign, trunc_d, st);
+        else launch_pass<F, UP, false>(bits[i], nbits, x, j0, sign, -1, st);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
-        j0 += B;
     }
     return hipSuccess;
 }
